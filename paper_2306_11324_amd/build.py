@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libigafmm.so")
-SOURCES = ["geometry_host.cpp", "tree_host.cpp", "kernels.hip", "gmres.hip", "api.hip"]
+SOURCES = ["geometry_host.cpp", "tree_host.cpp", "near.hip", "kernels.hip", "gmres.hip", "api.hip"]
 ARCH = os.environ.get("IGAFMM_ARCH", "gfx950")
 
 

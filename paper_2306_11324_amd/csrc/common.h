@@ -24,6 +24,7 @@ constexpr int PGMAX = 3;        // polynomial degree of the geometry per element
 constexpr int NBZ = (PGMAX + 1) * (PGMAX + 1);
 constexpr int QMAX = 10;        // interpolation degree
 constexpr int NLOCMAX = (PMAX + 1) * (PMAX + 1);
+constexpr int NGMAX = 16;         // largest Gauss order per direction
 
 // Kernel of the sound-soft family of operators: ck K* + cv V (complex cv)
 struct SoftMix {
@@ -322,6 +323,41 @@ inline igb_status op_reserve(igb_op op, DevBuf& b, size_t bytes, const char* who
     return st;
 }
 
+// device buffers, charged to the calling entry point's context (dev_malloc);
+// acct (if given) also counts them for the handle that owns them
+template <class T>
+inline igb_status upload(DevBuf& b, const T* src, size_t n, size_t* acct) {
+    if (igb_status st = dev_malloc(b, n * sizeof(T), "device upload")) return st;
+    if (n == 0) return IGB_OK;
+    if (acct) *acct += b.bytes;
+    if (src) IGB_HIP(hipMemcpy(b.ptr, src, n * sizeof(T), hipMemcpyHostToDevice));
+    return IGB_OK;
+}
+
+inline igb_status alloc(DevBuf& b, size_t bytes, size_t* acct) {
+    if (igb_status st = dev_malloc(b, bytes, "device allocation")) return st;
+    if (acct) *acct += b.bytes;
+    return IGB_OK;
+}
+
+// f(std::integral_constant<int, P>) for the degree p = 0..PMAX of the discrete spaces
+template <class F>
+inline igb_status with_degree(int p, const char* who, F&& f) {
+    switch (p) {
+        case 0: return f(std::integral_constant<int, 0>{});
+        case 1: return f(std::integral_constant<int, 1>{});
+        case 2: return f(std::integral_constant<int, 2>{});
+        case 3: return f(std::integral_constant<int, 3>{});
+        default:
+            set_error("%s: spline degree p = %d not built (0 <= p <= %d)", who, p, PMAX);
+            return IGB_ERR_UNSUPPORTED;
+    }
+}
+
+// Gauss-Legendre rules on [0,1]: nodes and weights per order 1..NGMAX, [order][2][NGMAX]
+std::vector<double> gauss_table();
+void gauss01_host(int n, std::vector<double>& x, std::vector<double>& w);
+
 // host stages
 igb_status geometry_build(igb_ctx ctx, const igb_patch* patches, int npatch, int m, int p,
                           igb_geom g);
@@ -329,8 +365,9 @@ igb_status tree_build(igb_op op);
 igb_status near_classify(igb_op op);
 igb_status near_pattern(igb_op op);
 
-// device stages (kernels.hip)
+// device stages (near.hip: near_field_device; the others kernels.hip)
 igb_status upload_geometry(igb_geom g);
+igb_status near_field_device(igb_op op, hipStream_t s);
 igb_status assemble_near_device(igb_op op, hipStream_t s);
 igb_status assemble_far_device(igb_op op, hipStream_t s);
 igb_status alloc_work(igb_op op, int nrhs);
