@@ -15,6 +15,7 @@ namespace igb {
 // Near field: regular element pairs (tensor Gauss of order n on both elements)
 // --------------------------------------------------------------------------
 constexpr int NEAR_THREADS = 256;
+constexpr int MASS_ORDER = 6;   // Gauss order per direction of the mass matrix on identical pairs
 
 struct NearArgs {
     const double* bez;
@@ -33,10 +34,11 @@ struct NearArgs {
     SoftMix mix;             // kernel of the sound-soft family
     HardMix hmix;            // kernel of the sound-hard family
     double2 cm;              // multiple of the mass matrix added on identical pairs
-    // singular rules: per class (0 vertex, 1 edge, 2 identical) points (s1,s2,r1,r2,w)
+    // touching-pair rules per class (0 vertex, 1 edge, 2 identical): blocks of 10
+    // doubles (duffy_blocks) and the Gauss order n of the tensor grid in each block
     const double* rule[3];
-    int rule_n[3];
-    int mass_order;
+    int rule_n[3];     // blocks
+    int rule_ord[3];   // n
 };
 
 // Kernel values at one point pair (element-local coordinates, n~ unnormalised):
@@ -52,18 +54,22 @@ template <bool HARD>
 __device__ __forceinline__ KVal kernel_pair(const double* X, const double* NX, double ax, const double* Y,
                                             const double* NY, double ay, double kappa, SoftMix mix, HardMix hmix) {
     KVal k;
+    const double d0 = X[0] - Y[0], d1 = X[1] - Y[1], d2 = X[2] - Y[2];
+    const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+    const double ir = rsqrt_fast(r2);
+    const double kr = kappa * (r2 * ir);
+    double sn, cs;
+    sincos_fast(kr, sn, cs);
+    const double c4 = 0.07957747154594767 * ir;   // 1/(4 pi r)
     if (!HARD) {
-        k.s = kernel_soft(X, NX, ax, Y, ay, kappa, mix);
+        // ck a_y H (x-y).n~_x + cv a_x a_y G as in kernel_soft
+        const double dn = d0 * NX[0] + d1 * NX[1] + d2 * NX[2];
+        const double h = mix.ck * ay * dn * ir * ir * c4, v = ax * ay * c4;
+        k.s = make_double2(h * (-cs - sn * kr) + v * (mix.cv.x * cs - mix.cv.y * sn),
+                           h * (cs * kr - sn) + v * (mix.cv.x * sn + mix.cv.y * cs));
         k.g = make_double2(0, 0);
         return k;
     }
-    const double d0 = X[0] - Y[0], d1 = X[1] - Y[1], d2 = X[2] - Y[2];
-    const double r = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-    const double ir = 1.0 / r;
-    const double kr = kappa * r;
-    double sn, cs;
-    sincos(kr, &sn, &cs);
-    const double c4 = 0.07957747154594767 * ir;
     const double dny = d0 * NY[0] + d1 * NY[1] + d2 * NY[2];
     const double nn = NX[0] * NY[0] + NX[1] * NY[1] + NX[2] * NY[2];
     // K kernel a_x H (y-x).n~_y = kn (cs + i sn) (i kr - 1), kn = -a_x (x-y).n~_y / (4 pi r^3)
@@ -214,111 +220,313 @@ __global__ __launch_bounds__(NEAR_THREADS) void near_regular(NearArgs A) {
 }
 
 // --------------------------------------------------------------------------
-// Near field: touching element pairs (Duffy-type rules on [0,1]^4), points in
-// batches staged through LDS; output (a,b) accumulated by SPLIT threads each.
+// Near field: touching element pairs (Duffy-type rules on [0,1]^4, duffy_blocks).
+//
+// In every region of the rules the point (s1, s2; r1, r2) of a block (the outer
+// variables fixed) runs over an n x n tensor grid on which (s1, r1) depend on
+// the first grid index alone and (s2, r2) on the second alone, all affinely in
+// the Gauss node.  So with Bernstein polynomials b on the elements, the block's
+// contribution factorises:
+//   sum_beta [b_j(s2) b_l(r2)]_beta  sum_alpha [b_i(s1) b_k(r1)]_alpha K(alpha, beta).
+// A lane takes a line (block, beta): it contracts both control nets along the
+// line's fixed coordinate once, walks alpha (two rational curve points and one
+// kernel value per point pair) and sums the (p+1)^2 products of the inner
+// factor; 64 lines then meet their outer factors on the fp64 matrix cores.  The
+// B-spline extraction is applied once per pair, to the finished matrix.  The
+// element symmetries of the rule are put into the nets and extraction rows as
+// they are read, so the grid is the same for every pair.
+// (Sound-hard: the curl product c_a . c_b, c = d1 phi F_2 - d2 phi F_1, splits into
+// four factorised terms with the kernel times F_i.F_j; the first shares the
+// outer factor of the phi phi term.)
+// Bound by fp64 VALU issue: about 250 instructions per point pair (sound-hard
+// about 450), where the point-wise form needed two surface points and (p+1)^4
+// products per point pair.  Level 5, p = 2, 55 thousand pairs (1.37 10^9 point
+// pairs): 79 -> 17 ms sound-soft, 287 -> 37.5 ms sound-hard (the sound-hard form
+// keeps 72 accumulators and runs one wave per SIMD).
 // --------------------------------------------------------------------------
-template <int P, bool HARD>
-__global__ __launch_bounds__(NEAR_THREADS) void near_singular(NearArgs A) {
-    constexpr int NL = (P + 1) * (P + 1);
-    constexpr int NV = HARD ? 4 : 1;
-    constexpr int BATCH = HARD ? 64 : NEAR_THREADS;
-    constexpr int SPLIT = NEAR_THREADS / (NL * NL) > 0 ? NEAR_THREADS / (NL * NL) : 1;
-    __shared__ KVal kq[BATCH];
-    __shared__ double px[BATCH][NL * NV];
-    __shared__ double py[BATCH][NL * NV];
-    __shared__ double2 red[NEAR_THREADS];
+// wavefront-wide ordering of LDS traffic inside one wave
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// Bernstein polynomials of compile-time degree
+template <int P>
+__device__ __forceinline__ void bern(double s, double* b) {
+    double db[4];
+    bernstein(P, s, b, db);
+}
+
+// entry (k, i) of the degree elevation from p to q >= p: b^q_k = sum_i E(k, i) b^p_i
+__device__ __forceinline__ double elevation(int p, int q, int k, int i) {
+    constexpr double C[4][4] = {{1, 0, 0, 0}, {1, 1, 0, 0}, {1, 2, 1, 0}, {1, 3, 3, 1}};
+    const int r = k - i;
+    return r < 0 || r > q - p ? 0.0 : C[p][i] * C[q - p][r] / C[q][k];
+}
+
+// P: spline degree, G >= the geometry degree of every element (lower degrees are
+// elevated as the net is read)
+template <int P, bool HARD, int G>
+__global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 ? 2 : 1) void near_singular(NearArgs A) {
+    constexpr int P1 = P + 1, NL = P1 * P1, G1 = G + 1, NW = NEAR_THREADS / 64;
+    constexpr int NT = HARD ? 4 : 1;   // factorised terms with their own outer factor
+    __shared__ double net[2][G1][G1][4];      // [x, y][dim 1][dim 2][homogeneous]
+    __shared__ double ext[2][2][P1][P1];      // [x, y][dim][B-spline][Bernstein]
+    __shared__ double2 Tb[NW][64][NL];        // a chunk's inner sums, one term at a time
+    __shared__ double Qb[NW][64][NL];         // and its outer factors
+    __shared__ double2 Mb[NL][NL], Rb[NL][NL];
+    __shared__ double mw[MASS_ORDER * MASS_ORDER], mb[MASS_ORDER * MASS_ORDER * 2 * P1];   // mass matrix points
+    double2* red = &Tb[0][0][0];              // [NW][NL][NL] after the loop
+    static_assert(sizeof(double2) * NW * NL * NL <= sizeof(Tb), "the waves' sums fit");
 
     const int64_t item = blockIdx.x;
     if (item >= A.nlist) return;
-    const int k = A.list[item];
-    const int e = A.pair_e[k], f = A.pair_f[k];
-    const int kind = A.pair_kind[k];
+    const int kp = A.list[item];
+    const int kind = A.pair_kind[kp];
     const int cls = kind & 15;
-    const int te = (kind >> 16) & 7, tf = (kind >> 20) & 7;
     const int ri = cls == 4 ? 2 : cls == 2 ? 1 : 0;
     const double* rule = A.rule[ri];
-    const int Q = A.rule_n[ri];
-    const int tid = threadIdx.x;
-    const ElemRef Re = elem_ref(A.bez, A.pg, A.nel1, e);
-    const ElemRef Rf = elem_ref(A.bez, A.pg, A.nel1, f);
-    const double* Ce_u = A.C1 + Re.ex * (P + 1) * (P + 1);
-    const double* Ce_v = A.C1 + Re.ey * (P + 1) * (P + 1);
-    const double* Cf_u = A.C1 + Rf.ex * (P + 1) * (P + 1);
-    const double* Cf_v = A.C1 + Rf.ey * (P + 1) * (P + 1);
+    const int n = A.rule_ord[ri], nlines = A.rule_n[ri] * n;
+    const double* gx = A.gl + n * 2 * NGMAX;
+    const double* gw = gx + NGMAX;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, g = lane >> 4;
+    const int code[2] = {(kind >> 16) & 7, (kind >> 20) & 7};
+    const ElemRef R[2] = {elem_ref(A.bez, A.pg, A.nel1, A.pair_e[kp]), elem_ref(A.bez, A.pg, A.nel1, A.pair_f[kp])};
 
-    const int out = tid % (NL * NL), part = tid / (NL * NL);
-    const int oa = out / NL, ob = out % NL;
-    double2 acc = make_double2(0, 0);
-    for (int base = 0; base < Q; base += BATCH) {
-        if (tid < BATCH) {
-            const int qi = base + tid;
-            if (qi < Q) {
-                const double* r = rule + int64_t(qi) * 5;
-                double s, t, u, v;
-                d4_apply(te, r[0], r[1], s, t);
-                d4_apply(tf, r[2], r[3], u, v);
-                double gxv[7], gyv[7];
-                point_data<P, HARD>(Re, Ce_u, Ce_v, s, t, 1.0, gxv, px[tid]);
-                point_data<P, HARD>(Rf, Cf_u, Cf_v, u, v, 1.0, gyv, py[tid]);
-                KVal kv = kernel_pair<HARD>(gxv, gxv + 3, gxv[6], gyv, gyv + 3, gyv[6], A.kappa, A.mix, A.hmix);
-                kv.s = cscale(kv.s, r[4]);
-                kv.g = cscale(kv.g, r[4]);
-                kq[tid] = kv;
-            } else {
-                kq[tid].s = make_double2(0, 0);
-                kq[tid].g = make_double2(0, 0);
-#pragma unroll
-                for (int a = 0; a < NL * NV; ++a) {
-                    px[tid][a] = 0;
-                    py[tid][a] = 0;
-                }
-            }
-        }
-        __syncthreads();
-        if (part < SPLIT) {
-            for (int q = part; q < BATCH; q += SPLIT) {
-                const double w = px[q][oa * NV] * py[q][ob * NV];
-                acc.x = fma(w, kq[q].s.x, acc.x);
-                acc.y = fma(w, kq[q].s.y, acc.y);
-                if (HARD) {
-                    double c = 0;
-#pragma unroll
-                    for (int v = 1; v < NV; ++v) c = fma(px[q][oa * NV + v], py[q][ob * NV + v], c);
-                    acc.x = fma(c, kq[q].g.x, acc.x);
-                    acc.y = fma(c, kq[q].g.y, acc.y);
-                }
-            }
-        }
-        __syncthreads();
+    // canonical nets and extraction rows (dim 1 = u unless swapped; flips reverse)
+    for (int t = tid; t < 2 * G1 * G1 * 4; t += NEAR_THREADS) {
+        const int x = t / (G1 * G1 * 4), r = t % (G1 * G1 * 4), i = r / (G1 * 4), j = (r / 4) % G1, c = r % 4;
+        const int cd = code[x];
+        int iu = (cd & 4) ? j : i, iv = (cd & 4) ? i : j;
+        if (cd & 1) iu = G - iu;
+        if (cd & 2) iv = G - iv;
+        const int pu = R[x].pu, pv = R[x].pv;
+        double v = 0;
+        for (int b = 0; b <= pv; ++b)
+            for (int a = 0; a <= pu; ++a)
+                v = fma(elevation(pu, G, iu, a) * elevation(pv, G, iv, b), R[x].bez[(b * (PGMAX + 1) + a) * 4 + c], v);
+        net[x][i][j][c] = v;
     }
-    red[tid] = acc;
+    for (int t = tid; t < 4 * P1 * P1; t += NEAR_THREADS) {
+        const int x = t / (2 * P1 * P1), dim = (t / (P1 * P1)) & 1, a = (t / P1) % P1, k = t % P1;
+        const int cd = code[x];
+        const bool along_u = (dim == 0) == !(cd & 4);
+        const bool flip = along_u ? (cd & 1) : (cd & 2);
+        const double* C = A.C1 + (along_u ? R[x].ex : R[x].ey) * P1 * P1;
+        ext[x][dim][a][k] = C[a * P1 + (flip ? P - k : k)];
+    }
+    // orientation of the canonical coordinates: n~ and the curls change sign with
+    // every swap or flip
+    double sg[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) sg[x] = (__popc(code[x]) & 1) ? -1.0 : 1.0;
+    const double sxy = sg[0] * sg[1];
+    __syncthreads();
+
+    f64x4 accr = {0, 0, 0, 0}, acci = {0, 0, 0, 0};
+    for (int l0 = wave * 64; l0 < nlines; l0 += NW * 64) {
+        // this lane's line; lanes past the last repeat it with weight 0
+        const int ln = min(l0 + lane, nlines - 1), o = ln / n, be = ln % n;
+        const double* B = rule + int64_t(o) * 10;
+        const double a1 = B[0], b1 = B[1], c1 = B[2], d1 = B[3];
+        const double s2 = fma(B[5], gx[be], B[4]), r2 = fma(B[7], gx[be], B[6]);
+        const double wl = l0 + lane < nlines ? B[8] * gw[be] : 0.0;
+        double q[2][G1][4], dq[2][G1][4];   // nets contracted along dim 2: values, d/d dim 2
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            double bb[4], db[4];
+            bernstein(G, x ? r2 : s2, bb, db);
+#pragma unroll
+            for (int i = 0; i < G1; ++i)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    double v = 0, d = 0;
+#pragma unroll
+                    for (int j = 0; j < G1; ++j) {
+                        const double h = net[x][i][j][c];
+                        v = fma(bb[j], h, v);
+                        d = fma(db[j], h, d);
+                    }
+                    q[x][i][c] = v;
+                    dq[x][i][c] = d;
+                }
+        }
+        double2 T[NT][P1][P1];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int i = 0; i < P1; ++i)
+#pragma unroll
+                for (int k = 0; k < P1; ++k) T[t][i][k] = make_double2(0, 0);
+        for (int al = 0; al < n; ++al) {
+            const double ga = gx[al], wa = gw[al];
+            const double st[2] = {fma(b1, ga, a1), fma(d1, ga, c1)};
+            double X[2][3], F1[2][3], F2[2][3], N[2][3], ar[2];
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                double bb[4], db[4];
+                bernstein(G, st[x], bb, db);
+                double p0[4], p1[4], p2[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    p0[c] = bb[0] * q[x][0][c];
+                    p1[c] = db[0] * q[x][0][c];
+                    p2[c] = bb[0] * dq[x][0][c];
+#pragma unroll
+                    for (int i = 1; i < G1; ++i) {
+                        p0[c] = fma(bb[i], q[x][i][c], p0[c]);
+                        p1[c] = fma(db[i], q[x][i][c], p1[c]);
+                        p2[c] = fma(bb[i], dq[x][i][c], p2[c]);
+                    }
+                }
+                const double iw = rcp_fast(p0[3]);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    X[x][c] = p0[c] * iw;
+                    F1[x][c] = (p1[c] - X[x][c] * p1[3]) * iw;
+                    F2[x][c] = (p2[c] - X[x][c] * p2[3]) * iw;
+                }
+                cross3(F1[x], F2[x], N[x]);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) N[x][c] *= sg[x];
+                const double n2 = N[x][0] * N[x][0] + N[x][1] * N[x][1] + N[x][2] * N[x][2];
+                ar[x] = n2 * rsqrt_fast(n2);
+            }
+            const KVal kv = kernel_pair<HARD>(X[0], N[0], ar[0], X[1], N[1], ar[1], A.kappa, A.mix, A.hmix);
+            const double2 S = cscale(kv.s, wa);
+            double bx[4], dbx[4], by[4], dby[4];
+            bernstein(P, st[0], bx, dbx);
+            bernstein(P, st[1], by, dby);
+#pragma unroll
+            for (int i = 0; i < P1; ++i) {
+                const double2 u = cscale(S, bx[i]);
+#pragma unroll
+                for (int k = 0; k < P1; ++k) {
+                    T[0][i][k].x = fma(u.x, by[k], T[0][i][k].x);
+                    T[0][i][k].y = fma(u.y, by[k], T[0][i][k].y);
+                }
+            }
+            if constexpr (HARD) {
+                const double2 Gw = cscale(kv.g, wa * sxy);
+                const double e22 = F2[0][0] * F2[1][0] + F2[0][1] * F2[1][1] + F2[0][2] * F2[1][2];
+                const double e21 = F2[0][0] * F1[1][0] + F2[0][1] * F1[1][1] + F2[0][2] * F1[1][2];
+                const double e12 = F1[0][0] * F2[1][0] + F1[0][1] * F2[1][1] + F1[0][2] * F2[1][2];
+                const double e11 = F1[0][0] * F1[1][0] + F1[0][1] * F1[1][1] + F1[0][2] * F1[1][2];
+                const double2 g22 = cscale(Gw, e22), g21 = cscale(Gw, -e21), g12 = cscale(Gw, -e12), g11 = cscale(Gw, e11);
+#pragma unroll
+                for (int i = 0; i < P1; ++i) {
+                    const double2 u0 = cscale(g22, dbx[i]), u1 = cscale(g21, dbx[i]), u2 = cscale(g12, bx[i]),
+                                  u3 = cscale(g11, bx[i]);
+#pragma unroll
+                    for (int k = 0; k < P1; ++k) {
+                        T[0][i][k].x = fma(u0.x, dby[k], T[0][i][k].x);
+                        T[0][i][k].y = fma(u0.y, dby[k], T[0][i][k].y);
+                        T[1][i][k].x = fma(u1.x, by[k], T[1][i][k].x);
+                        T[1][i][k].y = fma(u1.y, by[k], T[1][i][k].y);
+                        T[2][i][k].x = fma(u2.x, dby[k], T[2][i][k].x);
+                        T[2][i][k].y = fma(u2.y, dby[k], T[2][i][k].y);
+                        T[3][i][k].x = fma(u3.x, by[k], T[3][i][k].x);
+                        T[3][i][k].y = fma(u3.y, by[k], T[3][i][k].y);
+                    }
+                }
+            }
+        }
+        // outer factors (weighted): b_j b_l, and sound-hard b_j d_l, d_j b_l, d_j d_l
+        double bx[4], dbx[4], by[4], dby[4];
+        bernstein(P, s2, bx, dbx);
+        bernstein(P, r2, by, dby);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            wave_lds_sync();   // the previous term's operands are read
+#pragma unroll
+            for (int i = 0; i < P1; ++i)
+#pragma unroll
+                for (int k = 0; k < P1; ++k) {
+                    Tb[wave][lane][i * P1 + k] = T[t][i][k];
+                    Qb[wave][lane][i * P1 + k] = wl * (t < 2 ? bx[i] : dbx[i]) * (t == 0 || t == 2 ? by[k] : dby[k]);
+                }
+            wave_lds_sync();
+            // rows: outer index (j, l); columns: inner index (i, k); rows and columns
+            // past NL repeat the last and are not read
+            const int lc = min(li, NL - 1);
+#pragma unroll
+            for (int st = 0; st < 16; ++st) {
+                const double Aq = Qb[wave][4 * st + g][lc];
+                const double2 Bt = Tb[wave][4 * st + g][lc];
+                accr = __builtin_amdgcn_mfma_f64_16x16x4f64(Aq, Bt.x, accr, 0, 0, 0);
+                acci = __builtin_amdgcn_mfma_f64_16x16x4f64(Aq, Bt.y, acci, 0, 0, 0);
+            }
+        }
+    }
+    // the waves' sums meet in wave order
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int jl = g + 4 * r;
+        if (jl < NL && li < NL) red[(wave * NL + jl) * NL + li] = make_double2(accr[r], acci[r]);
+    }
     __syncthreads();
     if (tid < NL * NL) {
-        double2 sum = make_double2(0, 0);
-        for (int g2 = 0; g2 < SPLIT; ++g2) sum = cadd(sum, red[g2 * NL * NL + tid]);
-        if (cls == 4 && (A.cm.x != 0 || A.cm.y != 0)) {
-            // + cm times the mass matrix on the identical pair: int phi_a phi_b a
-            const int n = A.mass_order;
-            const double* gx = A.gl + n * 2 * NGMAX;
-            const double* gw = gx + NGMAX;
-            double m = 0;
-            for (int i = 0; i < n * n; ++i) {
-                const double ss = gx[i % n], tt = gx[i / n];
-                GeoPt G;
-                eval_geo(Re.bez, Re.pu, Re.pv, ss, tt, G);
-                double nt[3];
-                cross3(G.fs, G.ft, nt);
-                double bu[P + 1], bv[P + 1];
-                eval_basis1<P>(Ce_u, ss, bu, nullptr);
-                eval_basis1<P>(Ce_v, tt, bv, nullptr);
-                const double pa = bv[oa / (P + 1)] * bu[oa % (P + 1)];
-                const double pb = bv[ob / (P + 1)] * bu[ob % (P + 1)];
-                m += gw[i % n] * gw[i / n] * sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]) * pa * pb;
+        double2 s = red[tid];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) s = cadd(s, red[w * NL * NL + tid]);
+        Mb[tid / NL][tid % NL] = s;
+    }
+    __syncthreads();
+    // extraction along dim 1: R[jl][a1 b1], then along dim 2
+    if (tid < NL * NL) {
+        const int jl = tid / NL, a1i = (tid % NL) / P1, b1i = tid % P1;
+        double2 s = make_double2(0, 0);
+        for (int i = 0; i < P1; ++i)
+            for (int k = 0; k < P1; ++k) {
+                const double f = ext[0][0][a1i][i] * ext[1][0][b1i][k];
+                const double2 m = Mb[jl][i * P1 + k];
+                s.x = fma(f, m.x, s.x);
+                s.y = fma(f, m.y, s.y);
             }
-            sum.x += A.cm.x * m;
-            sum.y += A.cm.y * m;
+        Rb[jl][tid % NL] = s;
+    }
+    // mass matrix of identical pairs (element coordinates): points' weight times
+    // measure and basis values
+    const bool mass = cls == 4 && (A.cm.x != 0 || A.cm.y != 0);
+    constexpr int nm = MASS_ORDER;
+    if (mass && tid < nm * nm) {
+        const double* mx = A.gl + nm * 2 * NGMAX;
+        const double ss = mx[tid % nm], tt = mx[tid / nm];
+        GeoPt gp;
+        eval_geo(R[0].bez, R[0].pu, R[0].pv, ss, tt, gp);
+        double nt[3];
+        cross3(gp.fs, gp.ft, nt);
+        mw[tid] = mx[NGMAX + tid % nm] * mx[NGMAX + tid / nm] * sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
+        eval_basis1<P>(A.C1 + R[0].ex * P1 * P1, ss, mb + tid * 2 * P1, nullptr);
+        eval_basis1<P>(A.C1 + R[0].ey * P1 * P1, tt, mb + tid * 2 * P1 + P1, nullptr);
+    }
+    __syncthreads();
+    if (tid < NL * NL) {
+        // output (a, b): element-local indices (v major) to canonical ones
+        const int oa = tid / NL, ob = tid % NL;
+        const int a1i = (code[0] & 4) ? oa / P1 : oa % P1, a2i = (code[0] & 4) ? oa % P1 : oa / P1;
+        const int b1i = (code[1] & 4) ? ob / P1 : ob % P1, b2i = (code[1] & 4) ? ob % P1 : ob / P1;
+        double2 s = make_double2(0, 0);
+        for (int j = 0; j < P1; ++j)
+            for (int l = 0; l < P1; ++l) {
+                const double f = ext[0][1][a2i][j] * ext[1][1][b2i][l];
+                const double2 m = Rb[j * P1 + l][a1i * P1 + b1i];
+                s.x = fma(f, m.x, s.x);
+                s.y = fma(f, m.y, s.y);
+            }
+        if (mass) {
+            double m = 0;
+            for (int i = 0; i < nm * nm; ++i) {
+                const double* u = mb + i * 2 * P1;
+                m = fma(mw[i] * (u[P1 + oa / P1] * u[oa % P1]), u[P1 + ob / P1] * u[ob % P1], m);
+            }
+            s.x += A.cm.x * m;
+            s.y += A.cm.y * m;
         }
-        A.stage[(int64_t(k) - A.slot0) * NL * NL + tid] = sum;
+        A.stage[(int64_t(kp) - A.slot0) * NL * NL + tid] = s;
     }
 }
 
@@ -435,63 +643,60 @@ void gauss01_host(int n, std::vector<double>& x, std::vector<double>& w) {
 
 namespace {
 
-// Duffy-type rules on [0,1]^4 as (s1, s2, r1, r2, w) for the three touching
-// configurations (identical element; shared edge s2 = r2 = 0 with s1 = r1;
-// shared vertex at the origin).  Each coordinate pair (s, r) of the identical
-// and edge cases is written as offset u = |r - s| and position w in [0,1]
-// (Jacobian 1 - u); the singular corner of the remaining cube is removed by
-// splitting it into simplices / pyramids along its largest coordinate rho.
-std::vector<double> duffy_rule(int cls, int n) {
+// Duffy-type rules on [0,1]^4 for the three touching configurations (cls 2:
+// identical element; 1: shared edge s2 = r2 = 0 with s1 = r1; 0: shared vertex at
+// the origin).  Each coordinate pair (s, r) of the identical and edge cases is
+// written as offset u = |r - s| and position w in [0,1] (Jacobian 1 - u); the
+// singular corner of the remaining cube is removed by splitting it into
+// simplices / pyramids along its largest coordinate rho.  As blocks of 10
+// doubles over the n x n Gauss grid (x_alpha, x_beta):
+//   s1 = B0 + B1 x_alpha, r1 = B2 + B3 x_alpha, s2 = B4 + B5 x_beta,
+//   r2 = B6 + B7 x_beta, weight B8 w_alpha w_beta  (B9 unused)
+std::vector<double> duffy_blocks(int cls, int n) {
     std::vector<double> gx, gw;
     gauss01_host(n, gx, gw);
     std::vector<double> out;
-    auto split = [](double u, double w, int sig, double& s, double& r) {
-        double base = w * (1 - u);
-        if (sig > 0) { s = base; r = base + u; }
-        else { s = base + u; r = base; }
+    struct Pair {   // s = s0 + s1 x, r = r0 + r1 x
+        double s0, s1, r0, r1;
     };
+    auto put = [&](const Pair& a, const Pair& b, double w) {
+        out.insert(out.end(), {a.s0, a.s1, a.r0, a.r1, b.s0, b.s1, b.r0, b.r1, w, 0.0});
+    };
+    // the position w = x of a coordinate pair at offset u: base = x (1 - u)
+    auto split = [](double u, bool up) { return up ? Pair{0.0, 1 - u, u, 1 - u} : Pair{u, 1 - u, 0.0, 1 - u}; };
     for (int a = 0; a < n; ++a)
-        for (int b = 0; b < n; ++b)
-            for (int c = 0; c < n; ++c)
-                for (int d = 0; d < n; ++d) {
-                    const double rho = gx[a], t1 = gx[b], t2 = gx[c], t3 = gx[d];
-                    const double W = gw[a] * gw[b] * gw[c] * gw[d];
-                    if (cls == 2) {  // identical: 2 x 2 signs x 2 triangles
-                        for (int sg = 0; sg < 4; ++sg)
-                            for (int tri = 0; tri < 2; ++tri) {
-                                double u1 = tri ? rho * t1 : rho, u2 = tri ? rho : rho * t1;
-                                double s1, r1, s2, r2;
-                                split(u1, t2, (sg & 1) ? -1 : 1, s1, r1);
-                                split(u2, t3, (sg & 2) ? -1 : 1, s2, r2);
-                                out.insert(out.end(), {s1, s2, r1, r2, W * (1 - u1) * (1 - u2) * rho});
-                            }
-                    } else if (cls == 1) {  // edge: 2 signs x 3 pyramids
-                        for (int sg = 0; sg < 2; ++sg)
-                            for (int pyr = 0; pyr < 3; ++pyr) {
-                                double u1, s2, r2;
-                                if (pyr == 0) { u1 = rho; s2 = rho * t1; r2 = rho * t2; }
-                                else if (pyr == 1) { u1 = rho * t1; s2 = rho; r2 = rho * t2; }
-                                else { u1 = rho * t1; s2 = rho * t2; r2 = rho; }
-                                double s1, r1;
-                                split(u1, t3, sg ? -1 : 1, s1, r1);
-                                out.insert(out.end(), {s1, s2, r1, r2, W * (1 - u1) * rho * rho});
-                            }
-                    } else {  // vertex: 4 pyramids
-                        for (int pyr = 0; pyr < 4; ++pyr) {
-                            double c4[4];
-                            double rest[3] = {rho * t1, rho * t2, rho * t3};
-                            for (int i = 0, j = 0; i < 4; ++i) c4[i] = (i == pyr) ? rho : rest[j++];
-                            out.insert(out.end(), {c4[0], c4[1], c4[2], c4[3], W * rho * rho * rho});
-                        }
+        for (int b = 0; b < n; ++b) {
+            const double rho = gx[a], t = gx[b], W = gw[a] * gw[b];
+            if (cls == 2) {  // identical: 2 x 2 signs x 2 triangles
+                for (int sg = 0; sg < 4; ++sg)
+                    for (int tri = 0; tri < 2; ++tri) {
+                        const double u1 = tri ? rho * t : rho, u2 = tri ? rho : rho * t;
+                        put(split(u1, !(sg & 1)), split(u2, !(sg & 2)), W * (1 - u1) * (1 - u2) * rho);
                     }
-                }
+            } else if (cls == 1) {  // edge: 2 signs x 3 pyramids
+                for (int sg = 0; sg < 2; ++sg)
+                    for (int pyr = 0; pyr < 3; ++pyr) {
+                        const double u1 = pyr == 0 ? rho : rho * t;
+                        const Pair b2 = pyr == 0   ? Pair{rho * t, 0.0, 0.0, rho}
+                                        : pyr == 1 ? Pair{rho, 0.0, 0.0, rho}
+                                                   : Pair{0.0, rho, rho, 0.0};
+                        put(split(u1, !sg), b2, W * (1 - u1) * rho * rho);
+                    }
+            } else {  // vertex: 4 pyramids, (s1, s2, r1, r2) = rho at one coordinate
+                const double W3 = W * rho * rho * rho, q = rho * t;
+                put(Pair{rho, 0.0, 0.0, rho}, Pair{q, 0.0, 0.0, rho}, W3);
+                put(Pair{q, 0.0, 0.0, rho}, Pair{rho, 0.0, 0.0, rho}, W3);
+                put(Pair{0.0, rho, rho, 0.0}, Pair{q, 0.0, 0.0, rho}, W3);
+                put(Pair{0.0, rho, q, 0.0}, Pair{0.0, rho, rho, 0.0}, W3);
+            }
+        }
     return out;
 }
 
 }  // namespace
 
 // orders of the GPU rules (see near_classify for the regular ones)
-constexpr int NSING_IDENT = 7, NSING_EDGE = 8, NSING_VERTEX = 9, MASS_ORDER = 6;
+constexpr int NSING_IDENT = 7, NSING_EDGE = 8, NSING_VERTEX = 9;
 
 template <int P, bool HARD>
 static igb_status near_launch(igb_op op, hipStream_t s) {
@@ -516,10 +721,11 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
                         std::min(NGMAX, NSING_IDENT + raise)};
     NearArgs A{};
     for (int c = 0; c < 3; ++c) {
-        std::vector<double> r = duffy_rule(c, ord[c]);
+        std::vector<double> r = duffy_blocks(c, ord[c]);
         if ((st = upload(d_rules[c], r.data(), r.size(), nullptr))) return st;
         A.rule[c] = d_rules[c].as<double>();
-        A.rule_n[c] = int(r.size() / 5);
+        A.rule_n[c] = int(r.size() / 10);
+        A.rule_ord[c] = ord[c];
     }
     if ((st = upload(op->d_near_ptr, op->near_ptr.data(), op->near_ptr.size(), acct))) return st;
     if ((st = upload(op->d_near_src, op->near_src.data(), op->near_src.size(), acct))) return st;
@@ -545,7 +751,6 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
     A.mix = op->mix;
     A.hmix = op->hmix;
     A.cm = op->cm;
-    A.mass_order = MASS_ORDER;
 
     // chunks of target elements with a bounded staging buffer
     const int64_t max_slots = std::max<int64_t>(int64_t(1) << 22, 1);  // 4M pairs
@@ -556,6 +761,7 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
     const bool hard = op->bc == IGB_HARD;
     int64_t e0 = 0;
     std::vector<int> reg, reg_big, sing;
+    const int geo_deg = *std::max_element(g->pg.begin(), g->pg.end());
     auto points = [](int kind) {
         return std::max(((kind >> 8) & 15) * ((kind >> 12) & 15), ((kind >> 16) & 15) * ((kind >> 20) & 15));
     };
@@ -598,7 +804,11 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
         if (!sing.empty()) {
             A.list = d_list.as<int>() + reg.size() + reg_big.size();
             A.nlist = int64_t(sing.size());
-            hipLaunchKernelGGL((near_singular<P, HARD>), dim3(unsigned(sing.size())), dim3(NEAR_THREADS), 0, s, A);
+            // the nets are read at the largest geometry degree (2 or 3)
+            if (geo_deg <= 2)
+                hipLaunchKernelGGL((near_singular<P, HARD, 2>), dim3(unsigned(sing.size())), dim3(NEAR_THREADS), 0, s, A);
+            else
+                hipLaunchKernelGGL((near_singular<P, HARD, 3>), dim3(unsigned(sing.size())), dim3(NEAR_THREADS), 0, s, A);
             IGB_HIP(hipGetLastError());
         }
         // rows touched by the chunk's target elements

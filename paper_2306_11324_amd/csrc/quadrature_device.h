@@ -22,6 +22,54 @@ __device__ __forceinline__ double2 cfma(double2 a, double2 b, double2 c) {
 }
 __device__ __forceinline__ double2 cscale(double2 a, double s) { return make_double2(a.x * s, a.y * s); }
 
+// 1/x and 1/sqrt(x) for normal x: the hardware estimates (about 2^-24) and one
+// third-order correction; the result is within an ulp or two, at a fraction of
+// the instructions of the correctly rounded division and square root.
+__device__ __forceinline__ double rcp_fast(double x) {
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+__device__ __forceinline__ double rsqrt_fast(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double h = fma(-x * y, y, 1.0);
+    return fma(y * h, fma(h, 0.375, 0.5), y);
+}
+
+// sin(x) and cos(x) to about an ulp of 1 for |x| < 2^50: x reduced by the nearest
+// multiple of pi/2 (read off the low bits of x 2/pi + 1.5 2^52) in two fused
+// steps with pi/2 = A + B to 107 bits, then polynomials on [-pi/4, pi/4]
+// (interpolants of (sin r - r)/r^3 and (cos r - 1 + r^2/2)/r^4 in r^2 at six
+// Chebyshev points; truncation below 1.4e-17).  Without the libm function's
+// branch for huge arguments: beyond 2^50, where the spacing of doubles
+// approaches a radian, the values are only bounded (the reduced argument is
+// clamped).  About 35 instructions.
+__device__ __forceinline__ void sincos_fast(double x, double& sn, double& cs) {
+    const double MAGIC = 6755399441055744.0;   // 1.5 * 2^52
+    const double t = fma(x, 0x1.45f306dc9c883p-1, MAGIC);
+    const double n = t - MAGIC;
+    double r = fma(n, -0x1.921fb54442d18p+0, x);
+    r = fma(n, -0x1.1a62633145c07p-54, r);
+    r = fmin(fmax(r, -0.7863), 0.7863);
+    const double z = r * r;
+    double S = fma(z, 0x1.5e0af186af739p-33, -0x1.ae600a926c89ap-26);
+    S = fma(z, S, 0x1.71de37961e4c6p-19);
+    S = fma(z, S, -0x1.a01a019e8357dp-13);
+    S = fma(z, S, 0x1.1111111110bb1p-7);
+    S = fma(z, S, -0x1.5555555555555p-3);
+    const double s = fma(r * z, S, r);
+    double C = fma(z, -0x1.907d7aebd5e3dp-37, 0x1.1eeb68b109173p-29);
+    C = fma(z, C, -0x1.27e4fa17a41b4p-22);
+    C = fma(z, C, 0x1.a01a019f4e867p-16);
+    C = fma(z, C, -0x1.6c16c16c16966p-10);
+    C = fma(z, C, 0x1.5555555555555p-5);
+    const double c = fma(z * z, C, fma(z, -0.5, 1.0));
+    const int q = __double2loint(t);
+    const double a = (q & 1) ? c : s, b = (q & 1) ? s : c;
+    sn = __hiloint2double(__double2hiint(a) ^ ((q & 2) << 30), __double2loint(a));
+    cs = __hiloint2double(__double2hiint(b) ^ (((q + 1) & 2) << 30), __double2loint(b));
+}
+
 // Bernstein polynomials of degree p <= 3 on [0,1] and their derivatives
 __device__ __forceinline__ void bernstein(int p, double s, double* b, double* db) {
     const double t = 1.0 - s;
