@@ -214,6 +214,9 @@ struct igb_op_s {
     std::vector<std::vector<int>> near_leaf;  // per leaf (local index): sorted inadmissible leaves
     std::vector<int> near_kind;       // per near pair: 0 regular (order in bits 8..), 1 vertex,
                                       // 2 edge, 4 identical; transforms in bits 16.. / 20..
+    std::vector<int2> near_touch;         // touching pairs (near pair, target element) by target element
+    std::vector<int64_t> near_touch_ptr;  // [E+1]
+    int near_points_max = 0;              // most points per element of a regular pair's rules
     // near CSR in the solution space
     std::vector<int64_t> row_ptr;
     std::vector<int> col;

@@ -2173,7 +2173,7 @@ struct QuadGeoArgs {
 // per element: sum_g w_g f(x_g) phi_a(x_g) for each direction, with
 // f a = (rn d_n + rd) u_inc a = (rn i kappa d.n~ + rd a) u_inc
 template <int P>
-__global__ void rhs_elements(QuadGeoArgs A, const double* dirs, int ndir, double kappa, double2 rn, double2 rd,
+__global__ __launch_bounds__(128) void rhs_elements(QuadGeoArgs A, const double* dirs, int ndir, double kappa, double2 rn, double2 rd,
                              double2* loc /* [ndir][E][NL] */) {
     constexpr int NL = (P + 1) * (P + 1);
     const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -2241,7 +2241,7 @@ __global__ void rhs_gather(const double2* loc, int ndir, int64_t nelem, int nel1
 // boundary density and geometry at element quadrature points for far fields:
 // geo[e][g] = (x(3), n~(3), a, w), dens[dir][e][g]
 template <int P>
-__global__ void density_points(QuadGeoArgs A, const double2* coef, int ndir, int64_t n,
+__global__ __launch_bounds__(256) void density_points(QuadGeoArgs A, const double2* coef, int ndir, int64_t n,
                                const int* s2_to_s0, int k, double* geo, double2* dens) {
     constexpr int NL = (P + 1) * (P + 1);
     (void)NL;

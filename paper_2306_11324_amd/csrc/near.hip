@@ -17,18 +17,56 @@ namespace igb {
 constexpr int NEAR_THREADS = 256;
 constexpr int MASS_ORDER = 6;   // Gauss order per direction of the mass matrix on identical pairs
 
+// Staged places of the near pairs' blocks.  A target element's blocks are stored
+// by test function, then source: [a][source][b], the sources ordered by the near
+// leaves of the target's leaf and row-major inside each leaf (so a source's place
+// follows from its leaf's rank in the list).
+struct NearSlots {
+    const int64_t* near_ptr;   // [E + 1] first near pair of each target element
+    const int* list_ptr;       // [leaves + 1]
+    const int* list;           // near leaves of each leaf, sorted
+    int d, L, nel1;            // elements per leaf side 2^d, leaf level
+};
+__device__ __forceinline__ int leaf_index(const NearSlots& S, int patch, int lx, int ly) {
+    return (patch << (2 * S.L)) + (ly << S.L) + lx;
+}
+// position of leaf sl in the near list of leaf tl, -1 if it is not there
+__device__ __forceinline__ int near_leaf_rank(const NearSlots& S, int tl, int sl) {
+    const int a = S.list_ptr[tl], b = S.list_ptr[tl + 1];
+    int lo = a, hi = b;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (S.list[mid] < sl) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo < b && S.list[lo] == sl ? lo - a : -1;
+}
+// first staged entry of target element e's test function a (nl local functions)
+__device__ __forceinline__ int64_t stage_row(const NearSlots& S, int64_t e, int64_t slot0, int nl, int a) {
+    const int64_t k = S.near_ptr[e];
+    return ((k - slot0) * nl + a * (S.near_ptr[e + 1] - k)) * nl;
+}
+// place of source element f among the near sources of an element of leaf tl
+__device__ __forceinline__ int stage_slot(const NearSlots& S, int tl, int f) {
+    const int n2 = S.nel1 * S.nel1, p = f / n2, fy = f % n2 / S.nel1, fx = f % n2 % S.nel1, s1 = (1 << S.d) - 1;
+    return (near_leaf_rank(S, tl, leaf_index(S, p, fx >> S.d, fy >> S.d)) << (2 * S.d)) + ((fy & s1) << S.d) + (fx & s1);
+}
+__device__ __forceinline__ int leaf_of(const NearSlots& S, int64_t e) {
+    const int n2 = S.nel1 * S.nel1, p = int(e / n2), r = int(e % n2);
+    return leaf_index(S, p, r % S.nel1 >> S.d, r / S.nel1 >> S.d);
+}
+
 struct NearArgs {
     const double* bez;
     const int* pg;
     const double* C1;
     const double* gl;        // [NGMAX+1][2][NGMAX]: Gauss nodes / weights on [0,1] per order
-    const int* pair_e;       // near pair -> target element
+    NearSlots slots;
     const int* pair_f;       // near pair -> source element
     const int* pair_kind;
-    const int* list;         // near pairs handled by this launch
-    int64_t nlist;
-    int64_t slot0;           // staging slot = pair - slot0
-    double2* stage;          // [slots][nloc*nloc]
+    const int2* touch;       // touching pairs handled by this launch: (pair, target element)
+    int64_t slot0;           // first staged pair
+    double2* stage;          // [pairs][nloc*nloc], order: NearSlots
     int nel1;
     double kappa, eta;       // eta: coupling of the sound-hard CFIE
     SoftMix mix;             // kernel of the sound-soft family
@@ -116,107 +154,269 @@ __device__ __forceinline__ void point_data(const ElemRef& R, const double* Cu, c
 
 // --------------------------------------------------------------------------
 // Near field: regular element pairs, tensor Gauss rules of orders (nu, nv) on
-// each element (nu * nv <= MAXQ points; the orders may differ between the two
-// elements and between directions).  Kernel values are produced in chunks of
-// CI test points in LDS; thread items (j, a) accumulate
-// T[j][a] = sum_i w phi_a(x_i) k(x_i, y_j); finally B[a][b] = sum_j T[j][a] . w phi_b(y_j).
+// each element (the orders may differ between the two elements and between
+// directions).
+//
+// One wave takes a target element and a segment of its pairs, one rule at a
+// time: the test points once, then batches of source elements with one source
+// point per lane, and then the batch's points 16 at a time.  Lane (g, li)
+// evaluates the kernel at source point li and test points 4 t + g, which is the A
+// operand of the first product T[j][a] = sum_i k(x_i, y_j) w phi_a(x_i) on the
+// fp64 matrix cores; its result, rows 4 r + g in register r, is the B operand of
+// the second product B[b][a] = sum_j w phi_b(y_j) T[j][a] as it stands, so no
+// value passes through LDS between evaluation and the finished block.  Test
+// points are padded to 4 per element and source points to 4 per source (weight
+// 0, so their values do not matter).
+// (Sound-hard: the curl parts c_a . c_b as three more components with the kernel g.)
+// One wave per workgroup, so that no wave waits for another at the many small
+// rules of an element (16-20 of them, most with a few pairs).  Bound by fp64
+// issue: about 75 VALU instructions per point pair, 125 per source element to
+// place its points, and the padded matrix products, which run on the same fp64
+// units.  Level-5 sphere, p = 2, leaf depth 3, 17.6 million pairs: 128 -> 53 ms
+// (before: a workgroup per pair, values and products through LDS); level-5 hard
+// star, 5.3 million pairs: 73 -> 39 ms.
 // --------------------------------------------------------------------------
-template <int P, bool HARD, int MAXQ>
-__global__ __launch_bounds__(NEAR_THREADS) void near_regular(NearArgs A) {
-    constexpr int NL = (P + 1) * (P + 1);
-    constexpr int NV = HARD ? 4 : 1;
-    constexpr int NK = HARD ? 2 : 1;
-    constexpr int CI = 8;
-    constexpr int BUF = (CI * MAXQ * NK > MAXQ * NL) ? CI * MAXQ * NK : MAXQ * NL;
-    constexpr int ITEMS = (MAXQ * NL + NEAR_THREADS - 1) / NEAR_THREADS;
-    __shared__ double xg[MAXQ][7];
-    __shared__ double yg[MAXQ][7];
-    __shared__ double px[MAXQ][NL * NV];
-    __shared__ double py[MAXQ][NL * NV];
-    __shared__ double2 buf[BUF];
+// wavefront-wide ordering of LDS traffic inside one wave
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-    const int64_t item = blockIdx.x;
-    if (item >= A.nlist) return;
-    const int k = A.list[item];
-    const int e = A.pair_e[k], f = A.pair_f[k];
-    const int kind = A.pair_kind[k];
-    const int nxu = (kind >> 8) & 15, nxv = (kind >> 12) & 15, nyu = (kind >> 16) & 15, nyv = (kind >> 20) & 15;
-    const int nx = nxu * nxv, ny = nyu * nyv;
-    const int tid = threadIdx.x;
+// points of the larger of a regular pair's two rules
+__host__ __device__ inline int regular_points(int kind) {
+    const int nx = ((kind >> 8) & 15) * ((kind >> 12) & 15), ny = ((kind >> 16) & 15) * ((kind >> 20) & 15);
+    return nx > ny ? nx : ny;
+}
+constexpr int REG_POINTS_SMALL = 36;   // rules of up to 6 x 6 points take the form with less LDS
+constexpr int REG_SEG = 1024;          // pairs per workgroup
+constexpr int REG_ORDER_MAX = 12;
 
-    if (tid < nx + ny) {
-        const bool isx = tid < nx;
-        const int i = isx ? tid : tid - nx;
-        const int nu = isx ? nxu : nyu, nv = isx ? nxv : nyv;
-        const double* gu = A.gl + nu * 2 * NGMAX;
-        const double* gv = A.gl + nv * 2 * NGMAX;
-        const ElemRef R = elem_ref(A.bez, A.pg, A.nel1, isx ? e : f);
-        point_data<P, HARD>(R, A.C1 + R.ex * (P + 1) * (P + 1), A.C1 + R.ey * (P + 1) * (P + 1), gu[i % nu],
-                            gv[i / nu], gu[NGMAX + i % nu] * gv[NGMAX + i / nu], isx ? xg[i] : yg[i],
-                            isx ? px[i] : py[i]);
+// point data of a regular rule: g[0..6] = x, n~, |n~|; sound-hard also F_s, F_t
+template <bool HARD>
+__device__ __forceinline__ void surface_point(const ElemRef& R, double s, double t, double* g) {
+    GeoPt G;
+    if (R.pu == 2 && R.pv == 2) {
+        // all 9 control points in flight together
+        const double2* H = reinterpret_cast<const double2*>(R.bez);
+        double2 h[3][3][2];
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) h[j][i][c] = H[(j * (PGMAX + 1) + i) * 2 + c];
+        double bu[4], du[4], bv[4], dv[4];
+        bernstein(2, s, bu, du);
+        bernstein(2, t, bv, dv);
+        double p[4], ps[4], pt[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            double v = 0, vs = 0, vt = 0;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                double r = 0, rs = 0;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const double x = c & 1 ? h[j][i][c >> 1].y : h[j][i][c >> 1].x;
+                    r = fma(bu[i], x, r);
+                    rs = fma(du[i], x, rs);
+                }
+                v = fma(bv[j], r, v);
+                vs = fma(bv[j], rs, vs);
+                vt = fma(dv[j], r, vt);
+            }
+            p[c] = v;
+            ps[c] = vs;
+            pt[c] = vt;
+        }
+        const double iw = rcp_fast(p[3]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            G.x[c] = p[c] * iw;
+            G.fs[c] = (ps[c] - G.x[c] * ps[3]) * iw;
+            G.ft[c] = (pt[c] - G.x[c] * pt[3]) * iw;
+        }
+    } else {
+        eval_geo(R.bez, R.pu, R.pv, s, t, G);
     }
-    __syncthreads();
+    double nt[3];
+    cross3(G.fs, G.ft, nt);
+    const double n2 = nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        g[c] = G.x[c];
+        g[3 + c] = nt[c];
+        if (HARD) {
+            g[7 + c] = G.fs[c];
+            g[10 + c] = G.ft[c];
+        }
+    }
+    g[6] = n2 * rsqrt_fast(n2);
+}
 
-    double2 acc[ITEMS][NV];
+template <int P, bool HARD, int MX>
+__global__ __launch_bounds__(64, 2) void near_regular(NearArgs A, int e0) {
+    constexpr int P1 = P + 1, NL = P1 * P1, NV = HARD ? 4 : 1, NG = HARD ? 13 : 7, ND = HARD ? 2 * P1 : P1;
+    constexpr int YC = MX <= 64 ? 64 : MX;   // source points per batch (at least one source)
+    static_assert(MX % 4 == 0 && MX <= REG_POINTS_MAX, "padded points of a rule");
+    __shared__ unsigned short code[REG_SEG], list[REG_SEG];
+    __shared__ double xg[MX][NG], yg[YC][NG];
+    __shared__ double px[HARD ? 1 : MX][NL];              // sound-soft: w phi_a at the test points
+    __shared__ double bx[2 * REG_ORDER_MAX][ND];          // 1-D basis values (then derivatives) at the test points: u, v
+    __shared__ double by[64][ND];                         // the same per source of a batch: [source][u, v]
+    __shared__ int lsrc[16], lslot[16];
+    const int e = e0 + blockIdx.x, lane = threadIdx.x, li = lane & 15, g = lane >> 4;
+    const int lc = min(li, NL - 1), lu = lc % P1, lv = lc / P1;   // basis index of this lane (past NL: not read)
+    const int64_t kb = A.slots.near_ptr[e] + int64_t(blockIdx.y) * REG_SEG;
+    const int np = int(min(int64_t(REG_SEG), A.slots.near_ptr[e + 1] - kb));
+    if (np <= 0) return;
+    const int tl = leaf_of(A.slots, e);
+    const ElemRef Re = elem_ref(A.bez, A.pg, A.nel1, e);
+    constexpr int NONE = 0xffff;   // (orders are at most 12: no rule has this code)
+    int next = NONE;
+    for (int k = lane; k < np; k += 64) {
+        const int kd = A.pair_kind[kb + k];
+        const bool mine = (kd & 15) == 0 && (regular_points(kd) <= REG_POINTS_SMALL) == (MX == REG_POINTS_SMALL);
+        const int c = mine ? (kd >> 8) & 0xffff : NONE;
+        code[k] = (unsigned short)c;
+        next = min(next, c);
+    }
+    // 1-D basis of an element at the nodes of order n along one direction, times the weight
+    auto basis = [&](int n, int r, const double* C, double* o) {
+        const double* gl = A.gl + n * 2 * NGMAX;
+        double b[P1], db[P1];
+        eval_basis1<P>(C, gl[r], b, db);
 #pragma unroll
-    for (int it = 0; it < ITEMS; ++it)
+        for (int a = 0; a < P1; ++a) {
+            o[a] = gl[NGMAX + r] * b[a];
+            if (HARD) o[ND - P1 + a] = gl[NGMAX + r] * db[a];
+        }
+    };
+    // component v of the weighted test functions at a point (u and v factors bu, bv, geometry p):
+    // phi, then the curl d_s phi F_t - d_t phi F_s
+    auto comp = [&](int v, const double* bu, const double* bv, const double* p) {
+        if (v == 0) return bu[lu] * bv[lv];
+        return bu[ND - P1 + lu] * bv[lv] * p[9 + v] - bu[lu] * bv[ND - P1 + lv] * p[6 + v];
+    };
+    for (;;) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) acc[it][v] = make_double2(0, 0);
-    for (int i0 = 0; i0 < nx; i0 += CI) {
-        const int ci = min(CI, nx - i0);
-        for (int idx = tid; idx < ci * ny; idx += NEAR_THREADS) {
-            const int i = i0 + idx / ny, j = idx % ny;
-            const KVal kv = kernel_pair<HARD>(xg[i], xg[i] + 3, xg[i][6], yg[j], yg[j] + 3, yg[j][6], A.kappa, A.mix,
-                                                 A.hmix);
-            buf[idx * NK] = kv.s;
-            if (HARD) buf[idx * NK + 1] = kv.g;
+        for (int o = 32; o >= 1; o >>= 1) next = min(next, __shfl_xor(next, o, 64));
+        const int cur = next;
+        if (cur == NONE) break;
+        const int nxu = cur & 15, nxv = (cur >> 4) & 15, nyu = (cur >> 8) & 15, nyv = cur >> 12;
+        const int nx = nxu * nxv, ny = nyu * nyv, nx4 = (nx + 3) & ~3, ny4 = (ny + 3) & ~3, n1 = nyu + nyv;
+        const double *gxu = A.gl + nxu * 2 * NGMAX, *gxv = A.gl + nxv * 2 * NGMAX;
+        const double *gyu = A.gl + nyu * 2 * NGMAX, *gyv = A.gl + nyv * 2 * NGMAX;
+        __syncthreads();   // the rule before is done with the LDS
+        // the rule's pairs in order, and the next rule
+        int nsrc = 0;
+        next = NONE;
+        for (int k0 = 0; k0 < np; k0 += 64) {
+            const int c = k0 + lane < np ? code[k0 + lane] : NONE;
+            const unsigned long long m = __ballot(c == cur);
+            if (c == cur) list[nsrc + __popcll(m & ((1ull << lane) - 1))] = (unsigned short)(k0 + lane);
+            if (c > cur) next = min(next, c);
+            nsrc += __popcll(m);
+        }
+        for (int i = lane; i < nx4; i += 64) {
+            const int j = i < nx ? i : 0;
+            surface_point<HARD>(Re, gxu[j % nxu], gxv[j / nxu], xg[i]);
+        }
+        for (int r = lane; r < nxu + nxv; r += 64) {
+            const bool u = r < nxu;
+            basis(u ? nxu : nxv, u ? r : r - nxu, A.C1 + (u ? Re.ex : Re.ey) * P1 * P1, bx[r]);
         }
         __syncthreads();
+        if (!HARD)
+            for (int t = lane; t < nx4 * NL; t += 64) {
+                const int i = t / NL, a = t % NL;
+                px[i][a] = i < nx ? bx[i % nxu][a % P1] * bx[nxu + i / nxu][a / P1] : 0.0;
+            }
+        const int nbmax = min(16, YC / ny4);
+        const int invx = (65536 + nxu - 1) / nxu, invy = (65536 + nyu - 1) / nyu;   // i / n = i * inv >> 16 for i < 144
+        for (int s0 = 0; s0 < nsrc; s0 += nbmax) {
+            const int nb = min(nbmax, nsrc - s0), je = nb * ny4;
+            __syncthreads();   // the batch before is read
+            if (lane < nb) {
+                const int f = A.pair_f[kb + list[s0 + lane]];
+                lsrc[lane] = f;
+                lslot[lane] = stage_slot(A.slots, tl, f);
+            }
+            __syncthreads();
+            for (int t = lane; t < je; t += 64) {
+                const int q = t / ny4, j = t - q * ny4, jj = j < ny ? j : 0, jv = jj * invy >> 16;
+                surface_point<HARD>(elem_ref(A.bez, A.pg, A.nel1, lsrc[q]), gyu[jj - jv * nyu], gyv[jv], yg[t]);
+            }
+            for (int t = lane; t < nb * n1; t += 64) {
+                const int q = t / n1, r = t - q * n1;
+                const bool u = r < nyu;
+                const ElemRef Rf = elem_ref(A.bez, A.pg, A.nel1, lsrc[q]);
+                basis(u ? nyu : nyv, u ? r : r - nyu, A.C1 + (u ? Rf.ex : Rf.ey) * P1 * P1, by[t]);
+            }
+            __syncthreads();
+            f64x4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0};
+            int q = 0, qend = ny4;   // current source of the batch, its end
+            auto store = [&]() {
+                double2* o = A.stage + stage_row(A.slots, e, A.slot0, NL, lc) + int64_t(lslot[q]) * NL;
 #pragma unroll
-        for (int it = 0; it < ITEMS; ++it) {
-            const int w = tid + it * NEAR_THREADS;
-            if (w < ny * NL) {
-                const int j = w / NL, a = w % NL;
-                for (int ii = 0; ii < ci; ++ii) {
-                    const double* pxv = &px[i0 + ii][a * NV];
-                    const double2 ks = buf[(ii * ny + j) * NK];
-                    acc[it][0].x = fma(pxv[0], ks.x, acc[it][0].x);
-                    acc[it][0].y = fma(pxv[0], ks.y, acc[it][0].y);
-                    if (HARD) {
-                        const double2 kg = buf[(ii * ny + j) * NK + 1];
+                for (int r = 0; r < 4; ++r)
+                    if (li < NL && g + 4 * r < NL) o[g + 4 * r] = make_double2(cr[r], ci[r]);
+            };
+            for (int jt = 0; jt < je; jt += 16) {
+                const int J = min(jt + li, je - 1);
+                double Y[7];
 #pragma unroll
-                        for (int v = 1; v < NV; ++v) {
-                            acc[it][v].x = fma(pxv[v], kg.x, acc[it][v].x);
-                            acc[it][v].y = fma(pxv[v], kg.y, acc[it][v].y);
+                for (int c = 0; c < 7; ++c) Y[c] = yg[J][c];
+                f64x4 tr[NV], ti[NV];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) tr[v] = ti[v] = f64x4{0, 0, 0, 0};
+                for (int t = 0; t < nx4; t += 4) {
+                    const double* X = xg[t + g];
+                    const KVal kv = kernel_pair<HARD>(X, X + 3, X[6], Y, Y + 3, Y[6], A.kappa, A.mix, A.hmix);
+                    if constexpr (!HARD) {
+                        const double ph = px[t + g][lc];
+                        tr[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(kv.s.x, ph, tr[0], 0, 0, 0);
+                        ti[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(kv.s.y, ph, ti[0], 0, 0, 0);
+                    } else {
+                        const int i = t + g, iv = i * invx >> 16;
+                        const double *pu = bx[i < nx ? i - iv * nxu : 0], *pv = bx[i < nx ? nxu + iv : 0];
+                        const double on = i < nx ? 1.0 : 0.0;
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) {
+                            const double ph = on * comp(v, pu, pv, X);
+                            const double2 k = v == 0 ? kv.s : kv.g;
+                            tr[v] = __builtin_amdgcn_mfma_f64_16x16x4f64(k.x, ph, tr[v], 0, 0, 0);
+                            ti[v] = __builtin_amdgcn_mfma_f64_16x16x4f64(k.y, ph, ti[v], 0, 0, 0);
                         }
                     }
                 }
-            }
-        }
-        __syncthreads();
-    }
-    // one component v at a time: T[j][a] into LDS, then B[a][b] += sum_j T[j][a] py[j][b][v]
-    // (keeps the buffer at MAXQ * NL entries, which the degree-3 hypersingular case needs)
-    const int a = tid / NL, b = tid % NL;
-    double2 sum = make_double2(0, 0);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
+                for (int r = 0; r < 4; ++r) {
+                    const int jk = jt + 4 * r;
+                    if (jk >= je) break;
+                    if (jk == qend) {   // the source before is complete
+                        store();
+                        cr = ci = f64x4{0, 0, 0, 0};
+                        ++q;
+                        qend += ny4;
+                    }
+                    const int j = jk + g - (qend - ny4), jv = j * invy >> 16;
+                    const bool in = j < ny;
+                    const double *pu = by[q * n1 + (in ? j - jv * nyu : 0)], *pv = by[q * n1 + nyu + (in ? jv : 0)];
+                    const double on = in ? 1.0 : 0.0;
 #pragma unroll
-        for (int it = 0; it < ITEMS; ++it) {
-            const int w = tid + it * NEAR_THREADS;
-            if (w < ny * NL) buf[w] = acc[it][v];
-        }
-        __syncthreads();
-        if (tid < NL * NL)
-            for (int j = 0; j < ny; ++j) {
-                const double2 t = buf[j * NL + a];
-                const double y = py[j][b * NV + v];
-                sum.x = fma(t.x, y, sum.x);
-                sum.y = fma(t.y, y, sum.y);
+                    for (int v = 0; v < NV; ++v) {
+                        const double ph = on * comp(v, pu, pv, yg[jk + g]);
+                        cr = __builtin_amdgcn_mfma_f64_16x16x4f64(ph, tr[v][r], cr, 0, 0, 0);
+                        ci = __builtin_amdgcn_mfma_f64_16x16x4f64(ph, ti[v][r], ci, 0, 0, 0);
+                    }
+                }
             }
-        __syncthreads();
+            store();
+        }
     }
-    if (tid < NL * NL) A.stage[(int64_t(k) - A.slot0) * NL * NL + tid] = sum;
 }
 
 // --------------------------------------------------------------------------
@@ -244,14 +444,6 @@ __global__ __launch_bounds__(NEAR_THREADS) void near_regular(NearArgs A) {
 // pairs): 79 -> 17 ms sound-soft, 287 -> 37.5 ms sound-hard (the sound-hard form
 // keeps 72 accumulators and runs one wave per SIMD).
 // --------------------------------------------------------------------------
-// wavefront-wide ordering of LDS traffic inside one wave
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
 // Bernstein polynomials of compile-time degree
 template <int P>
 __device__ __forceinline__ void bern(double s, double* b) {
@@ -269,9 +461,11 @@ __device__ __forceinline__ double elevation(int p, int q, int k, int i) {
 // P: spline degree, G >= the geometry degree of every element (lower degrees are
 // elevated as the net is read)
 template <int P, bool HARD, int G>
-__global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 ? 2 : 1) void near_singular(NearArgs A) {
+__global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 && G == 2 ? 2 : 1) void near_singular(NearArgs A) {
     constexpr int P1 = P + 1, NL = P1 * P1, G1 = G + 1, NW = NEAR_THREADS / 64;
     constexpr int NT = HARD ? 4 : 1;   // factorised terms with their own outer factor
+    // terms summed per walk along a line (degree 3: two walks of two, within the registers)
+    constexpr int TW = HARD && P == 3 ? 2 : NT;
     __shared__ double net[2][G1][G1][4];      // [x, y][dim 1][dim 2][homogeneous]
     __shared__ double ext[2][2][P1][P1];      // [x, y][dim][B-spline][Bernstein]
     __shared__ double2 Tb[NW][64][NL];        // a chunk's inner sums, one term at a time
@@ -282,8 +476,7 @@ __global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 ? 2 : 1) void near_si
     static_assert(sizeof(double2) * NW * NL * NL <= sizeof(Tb), "the waves' sums fit");
 
     const int64_t item = blockIdx.x;
-    if (item >= A.nlist) return;
-    const int kp = A.list[item];
+    const int kp = A.touch[item].x;
     const int kind = A.pair_kind[kp];
     const int cls = kind & 15;
     const int ri = cls == 4 ? 2 : cls == 2 ? 1 : 0;
@@ -293,7 +486,7 @@ __global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 ? 2 : 1) void near_si
     const double* gw = gx + NGMAX;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, g = lane >> 4;
     const int code[2] = {(kind >> 16) & 7, (kind >> 20) & 7};
-    const ElemRef R[2] = {elem_ref(A.bez, A.pg, A.nel1, A.pair_e[kp]), elem_ref(A.bez, A.pg, A.nel1, A.pair_f[kp])};
+    const ElemRef R[2] = {elem_ref(A.bez, A.pg, A.nel1, A.touch[item].y), elem_ref(A.bez, A.pg, A.nel1, A.pair_f[kp])};
 
     // canonical nets and extraction rows (dim 1 = u unless swapped; flips reverse)
     for (int t = tid; t < 2 * G1 * G1 * 4; t += NEAR_THREADS) {
@@ -353,9 +546,10 @@ __global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 ? 2 : 1) void near_si
                     dq[x][i][c] = d;
                 }
         }
-        double2 T[NT][P1][P1];
+        for (int t0 = 0; t0 < NT; t0 += TW) {
+        double2 T[TW][P1][P1];
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+        for (int t = 0; t < TW; ++t)
 #pragma unroll
             for (int i = 0; i < P1; ++i)
 #pragma unroll
@@ -399,37 +593,31 @@ __global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 ? 2 : 1) void near_si
             double bx[4], dbx[4], by[4], dby[4];
             bernstein(P, st[0], bx, dbx);
             bernstein(P, st[1], by, dby);
+            const double2 Gw = HARD ? cscale(kv.g, wa * sxy) : make_double2(0, 0);
+            // T[t][i][k] += K f_i(s1) h_k(r1), f and h Bernstein values or derivatives
+            auto add = [&](double2(&Tt)[P1][P1], double2 K, const double* f, const double* h) {
 #pragma unroll
-            for (int i = 0; i < P1; ++i) {
-                const double2 u = cscale(S, bx[i]);
+                for (int i = 0; i < P1; ++i) {
+                    const double2 u = cscale(K, f[i]);
 #pragma unroll
-                for (int k = 0; k < P1; ++k) {
-                    T[0][i][k].x = fma(u.x, by[k], T[0][i][k].x);
-                    T[0][i][k].y = fma(u.y, by[k], T[0][i][k].y);
+                    for (int k = 0; k < P1; ++k) {
+                        Tt[i][k].x = fma(u.x, h[k], Tt[i][k].x);
+                        Tt[i][k].y = fma(u.y, h[k], Tt[i][k].y);
+                    }
+                }
+            };
+            auto dot = [](const double* a, const double* b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; };
+            if (t0 == 0) {
+                add(T[0], S, bx, by);
+                if constexpr (HARD) {
+                    add(T[0], cscale(Gw, dot(F2[0], F2[1])), dbx, dby);
+                    add(T[1], cscale(Gw, -dot(F2[0], F1[1])), dbx, by);
                 }
             }
             if constexpr (HARD) {
-                const double2 Gw = cscale(kv.g, wa * sxy);
-                const double e22 = F2[0][0] * F2[1][0] + F2[0][1] * F2[1][1] + F2[0][2] * F2[1][2];
-                const double e21 = F2[0][0] * F1[1][0] + F2[0][1] * F1[1][1] + F2[0][2] * F1[1][2];
-                const double e12 = F1[0][0] * F2[1][0] + F1[0][1] * F2[1][1] + F1[0][2] * F2[1][2];
-                const double e11 = F1[0][0] * F1[1][0] + F1[0][1] * F1[1][1] + F1[0][2] * F1[1][2];
-                const double2 g22 = cscale(Gw, e22), g21 = cscale(Gw, -e21), g12 = cscale(Gw, -e12), g11 = cscale(Gw, e11);
-#pragma unroll
-                for (int i = 0; i < P1; ++i) {
-                    const double2 u0 = cscale(g22, dbx[i]), u1 = cscale(g21, dbx[i]), u2 = cscale(g12, bx[i]),
-                                  u3 = cscale(g11, bx[i]);
-#pragma unroll
-                    for (int k = 0; k < P1; ++k) {
-                        T[0][i][k].x = fma(u0.x, dby[k], T[0][i][k].x);
-                        T[0][i][k].y = fma(u0.y, dby[k], T[0][i][k].y);
-                        T[1][i][k].x = fma(u1.x, by[k], T[1][i][k].x);
-                        T[1][i][k].y = fma(u1.y, by[k], T[1][i][k].y);
-                        T[2][i][k].x = fma(u2.x, dby[k], T[2][i][k].x);
-                        T[2][i][k].y = fma(u2.y, dby[k], T[2][i][k].y);
-                        T[3][i][k].x = fma(u3.x, by[k], T[3][i][k].x);
-                        T[3][i][k].y = fma(u3.y, by[k], T[3][i][k].y);
-                    }
+                if (TW == NT || t0 > 0) {
+                    add(T[TW - 2], cscale(Gw, -dot(F1[0], F2[1])), bx, dby);
+                    add(T[TW - 1], cscale(Gw, dot(F1[0], F1[1])), bx, by);
                 }
             }
         }
@@ -438,13 +626,14 @@ __global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 ? 2 : 1) void near_si
         bernstein(P, s2, bx, dbx);
         bernstein(P, r2, by, dby);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
+        for (int tt = 0; tt < TW; ++tt) {
+            const int t = t0 + tt;
             wave_lds_sync();   // the previous term's operands are read
 #pragma unroll
             for (int i = 0; i < P1; ++i)
 #pragma unroll
                 for (int k = 0; k < P1; ++k) {
-                    Tb[wave][lane][i * P1 + k] = T[t][i][k];
+                    Tb[wave][lane][i * P1 + k] = T[tt][i][k];
                     Qb[wave][lane][i * P1 + k] = wl * (t < 2 ? bx[i] : dbx[i]) * (t == 0 || t == 2 ? by[k] : dby[k]);
                 }
             wave_lds_sync();
@@ -458,6 +647,7 @@ __global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 ? 2 : 1) void near_si
                 accr = __builtin_amdgcn_mfma_f64_16x16x4f64(Aq, Bt.x, accr, 0, 0, 0);
                 acci = __builtin_amdgcn_mfma_f64_16x16x4f64(Aq, Bt.y, acci, 0, 0, 0);
             }
+        }
         }
     }
     // the waves' sums meet in wave order
@@ -495,10 +685,31 @@ __global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 ? 2 : 1) void near_si
     if (mass && tid < nm * nm) {
         const double* mx = A.gl + nm * 2 * NGMAX;
         const double ss = mx[tid % nm], tt = mx[tid / nm];
-        GeoPt gp;
-        eval_geo(R[0].bez, R[0].pu, R[0].pv, ss, tt, gp);
-        double nt[3];
-        cross3(gp.fs, gp.ft, nt);
+        // (identical pairs carry no symmetry: the net is in element coordinates)
+        double bu[4], du[4], bv[4], dv[4], p0[4], p1[4], p2[4];
+        bernstein(G, ss, bu, du);
+        bernstein(G, tt, bv, dv);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            p0[c] = p1[c] = p2[c] = 0;
+#pragma unroll
+            for (int i = 0; i < G1; ++i)
+#pragma unroll
+                for (int j = 0; j < G1; ++j) {
+                    const double h = net[0][i][j][c];
+                    p0[c] = fma(bu[i] * bv[j], h, p0[c]);
+                    p1[c] = fma(du[i] * bv[j], h, p1[c]);
+                    p2[c] = fma(bu[i] * dv[j], h, p2[c]);
+                }
+        }
+        const double iw = 1.0 / p0[3];
+        double fs[3], ft[3], nt[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            fs[c] = (p1[c] - p0[c] * iw * p1[3]) * iw;
+            ft[c] = (p2[c] - p0[c] * iw * p2[3]) * iw;
+        }
+        cross3(fs, ft, nt);
         mw[tid] = mx[NGMAX + tid % nm] * mx[NGMAX + tid / nm] * sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
         eval_basis1<P>(A.C1 + R[0].ex * P1 * P1, ss, mb + tid * 2 * P1, nullptr);
         eval_basis1<P>(A.C1 + R[0].ey * P1 * P1, tt, mb + tid * 2 * P1 + P1, nullptr);
@@ -526,21 +737,29 @@ __global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 ? 2 : 1) void near_si
             s.x += A.cm.x * m;
             s.y += A.cm.y * m;
         }
-        A.stage[(int64_t(kp) - A.slot0) * NL * NL + tid] = s;
+        const int e = A.touch[item].y;
+        const int slot = stage_slot(A.slots, leaf_of(A.slots, e), A.pair_f[kp]);
+        A.stage[stage_row(A.slots, e, A.slot0, NL, oa) + int64_t(slot) * NL + ob] = s;
     }
 }
 
 // --------------------------------------------------------------------------
 // Near field: deterministic gather of the staged element blocks into the CSR
 // values of the solution space.  One workgroup per row; each nonzero sums its
-// contributions in a fixed order (representatives, elements, source elements).
+// contributions in a fixed order (representatives, leaves and elements of the
+// row, source elements).  A source element's staged place follows from its
+// leaf's place in the target leaf's near list (stage_slot), so a nonzero searches
+// that list once per target and source leaf instead of the element's pairs once
+// per element pair, and then has the (p+1)^2 loads of a target element in
+// flight together.  Bound by the staged blocks' traffic (16 (p+1)^4 bytes per
+// near pair, written and read once).  Level-5 sphere, leaf depth 3, p = 2 (23 GB
+// of blocks): 39 -> 11 ms.
 // --------------------------------------------------------------------------
 struct CsrArgs {
     const int64_t* row_ptr;
     const int* col;
     double2* val;
-    const int64_t* near_ptr;
-    const int* near_src;
+    NearSlots slots;
     const double2* stage;
     int64_t slot0;
     int64_t e_lo, e_hi;          // target elements whose pairs are staged
@@ -551,11 +770,11 @@ struct CsrArgs {
 };
 
 template <int P>
-__global__ void near_gather_csr(CsrArgs A) {
-    constexpr int NL = (P + 1) * (P + 1);
+__global__ __launch_bounds__(256) void near_gather_csr(CsrArgs A) {
+    constexpr int P1 = P + 1, NL = P1 * P1;
     const int64_t row = A.row0 + blockIdx.x;
     const int64_t beg = A.row_ptr[row], end = A.row_ptr[row + 1];
-    const int64_t kk = int64_t(A.k) * A.k;
+    const int kk = A.k * A.k, d = A.slots.d, s1 = (1 << d) - 1, n1 = A.nel1 - 1;
     const int r0 = A.s0_ptr ? A.s0_ptr[row] : int(row);
     const int r1 = A.s0_ptr ? A.s0_ptr[row + 1] : int(row) + 1;
     for (int64_t idx = beg + threadIdx.x; idx < end; idx += blockDim.x) {
@@ -564,30 +783,48 @@ __global__ void near_gather_csr(CsrArgs A) {
         const int c1 = A.s0_ptr ? A.s0_ptr[colv + 1] : colv + 1;
         double2 acc = make_double2(0, 0);
         for (int ri = r0; ri < r1; ++ri) {
-            const int64_t i = A.s0_ptr ? A.s0_reps[ri] : ri;
-            const int pj = int(i / kk), rem = int(i % kk), iv = rem / A.k, iu = rem % A.k;
-            for (int ey = max(0, iv - P); ey <= min(iv, A.nel1 - 1); ++ey)
-                for (int ex = max(0, iu - P); ex <= min(iu, A.nel1 - 1); ++ex) {
-                    const int64_t e = (int64_t(pj) * A.nel1 + ey) * A.nel1 + ex;
-                    if (e < A.e_lo || e >= A.e_hi) continue;
-                    const int a = (iv - ey) * (P + 1) + (iu - ex);
-                    const int64_t nb = A.near_ptr[e], ne = A.near_ptr[e + 1];
+            const int i = A.s0_ptr ? A.s0_reps[ri] : ri;
+            const int pj = i / kk, iv = i % kk / A.k, iu = i % kk % A.k;
+            const int ey0 = max(0, iv - P), ey1 = min(iv, n1), ex0 = max(0, iu - P), ex1 = min(iu, n1);
+            for (int ly = ey0 >> d; ly <= ey1 >> d; ++ly)
+                for (int lx = ex0 >> d; lx <= ex1 >> d; ++lx) {
+                    const int tl = leaf_index(A.slots, pj, lx, ly);
                     for (int ci = c0; ci < c1; ++ci) {
-                        const int64_t j = A.s0_ptr ? A.s0_reps[ci] : ci;
-                        const int qj = int(j / kk), rj = int(j % kk), jv = rj / A.k, ju = rj % A.k;
-                        for (int fy = max(0, jv - P); fy <= min(jv, A.nel1 - 1); ++fy)
-                            for (int fx = max(0, ju - P); fx <= min(ju, A.nel1 - 1); ++fx) {
-                                const int f = int((int64_t(qj) * A.nel1 + fy) * A.nel1 + fx);
-                                int64_t lo = nb, hi = ne;
-                                while (lo < hi) {
-                                    int64_t mid = (lo + hi) >> 1;
-                                    if (A.near_src[mid] < f) lo = mid + 1;
-                                    else hi = mid;
+                        const int j = A.s0_ptr ? A.s0_reps[ci] : ci;
+                        const int qj = j / kk, jv = j % kk / A.k, ju = j % kk % A.k;
+                        // staged places of the source elements jv - dy, ju - dx relative to the
+                        // target element's blocks (-1: not a near source)
+                        int off[NL], lf[P1], lq[P1];
+#pragma unroll
+                        for (int dx = 0; dx < P1; ++dx) lf[dx] = -1;
+#pragma unroll
+                        for (int dy = 0; dy < P1; ++dy)
+#pragma unroll
+                            for (int dx = 0; dx < P1; ++dx) {
+                                const int fy = jv - dy, fx = ju - dx;
+                                const bool in = fy >= 0 && fy <= n1 && fx >= 0 && fx <= n1;
+                                const int sl = in ? leaf_index(A.slots, qj, fx >> d, fy >> d) : -1;
+                                if (sl != lf[dx]) {
+                                    lf[dx] = sl;
+                                    lq[dx] = dx > 0 && sl == lf[dx - 1] ? lq[dx - 1] : near_leaf_rank(A.slots, tl, sl);
                                 }
-                                if (lo < ne && A.near_src[lo] == f) {
-                                    const int b = (jv - fy) * (P + 1) + (ju - fx);
-                                    acc = cadd(acc, A.stage[(lo - A.slot0) * NL * NL + a * NL + b]);
-                                }
+                                off[dy * P1 + dx] =
+                                    in && lq[dx] >= 0
+                                        ? ((lq[dx] << (2 * d)) + ((fy & s1) << d) + (fx & s1)) * NL + dy * P1 + dx
+                                        : -1;
+                            }
+                        for (int ey = max(ey0, ly << d); ey <= min(ey1, (ly << d) + s1); ++ey)
+                            for (int ex = max(ex0, lx << d); ex <= min(ex1, (lx << d) + s1); ++ex) {
+                                const int64_t e = (int64_t(pj) * A.nel1 + ey) * A.nel1 + ex;
+                                if (e < A.e_lo || e >= A.e_hi) continue;
+                                const int a = (iv - ey) * P1 + (iu - ex);
+                                const double2* blk = A.stage + stage_row(A.slots, e, A.slot0, NL, a);
+                                double2 v[NL];
+#pragma unroll
+                                for (int t = 0; t < NL; ++t)
+                                    v[t] = off[t] >= 0 ? blk[off[t]] : make_double2(0, 0);
+#pragma unroll
+                                for (int t = 0; t < NL; ++t) acc = cadd(acc, v[t]);
                             }
                     }
                 }
@@ -706,13 +943,7 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
     const int64_t npairs = op->near_ptr[E];
     size_t* acct = &op->dev_bytes;
     igb_status st;
-    // pair arrays
-    std::vector<int> pe(npairs);
-    for (int64_t e = 0; e < E; ++e)
-        for (int64_t k = op->near_ptr[e]; k < op->near_ptr[e + 1]; ++k) pe[k] = int(e);
-    DevBuf d_pe, d_pf, d_kind, d_gl, d_rules[3], d_list, d_stage;
-    if ((st = upload(d_pe, pe.data(), pe.size(), nullptr))) return st;
-    if ((st = upload(d_pf, op->near_src.data(), op->near_src.size(), nullptr))) return st;
+    DevBuf d_kind, d_gl, d_rules[3], d_touch, d_stage;
     if ((st = upload(d_kind, op->near_kind.data(), op->near_kind.size(), nullptr))) return st;
     std::vector<double> gl = gauss_table();
     if ((st = upload(d_gl, gl.data(), gl.size(), nullptr))) return st;
@@ -738,12 +969,23 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
     if ((st = alloc(op->d_val, op->nnz * sizeof(double2), acct))) return st;
     IGB_HIP(hipMemsetAsync(op->d_val.ptr, 0, op->nnz * sizeof(double2), s));
 
+    std::vector<int> list_ptr(op->near_leaf.size() + 1, 0), list;
+    for (size_t i = 0; i < op->near_leaf.size(); ++i) {
+        list.insert(list.end(), op->near_leaf[i].begin(), op->near_leaf[i].end());
+        list_ptr[i + 1] = int(list.size());
+    }
+    DevBuf d_list_ptr, d_list;
+    if ((st = upload(d_list_ptr, list_ptr.data(), list_ptr.size(), nullptr)) ||
+        (st = upload(d_list, list.data(), list.size(), nullptr)))
+        return st;
+    const NearSlots slots{op->d_near_ptr.as<int64_t>(), d_list_ptr.as<int>(), d_list.as<int>(), op->d, op->L, g->nel1};
+
     A.bez = g->d_bez.as<double>();
     A.pg = g->d_pg.as<int>();
     A.C1 = g->d_C1.as<double>();
     A.gl = d_gl.as<double>();
-    A.pair_e = d_pe.as<int>();
-    A.pair_f = d_pf.as<int>();
+    A.slots = slots;
+    A.pair_f = op->d_near_src.as<int>();
     A.pair_kind = d_kind.as<int>();
     A.nel1 = g->nel1;
     A.kappa = op->kappa;
@@ -756,15 +998,11 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
     const int64_t max_slots = std::max<int64_t>(int64_t(1) << 22, 1);  // 4M pairs
     if ((st = alloc(d_stage, size_t(std::min(npairs, max_slots)) * NL * NL * sizeof(double2), nullptr)))
         return st;
-    if ((st = alloc(d_list, size_t(std::min(npairs, max_slots)) * sizeof(int), nullptr))) return st;
+    if ((st = upload(d_touch, op->near_touch.data(), op->near_touch.size(), nullptr))) return st;
     A.stage = d_stage.as<double2>();
     const bool hard = op->bc == IGB_HARD;
     int64_t e0 = 0;
-    std::vector<int> reg, reg_big, sing;
     const int geo_deg = *std::max_element(g->pg.begin(), g->pg.end());
-    auto points = [](int kind) {
-        return std::max(((kind >> 8) & 15) * ((kind >> 12) & 15), ((kind >> 16) & 15) * ((kind >> 20) & 15));
-    };
     while (e0 < E) {
         int64_t e1 = e0;
         while (e1 < E && op->near_ptr[e1 + 1] - op->near_ptr[e0] <= max_slots) ++e1;
@@ -772,45 +1010,24 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
             set_error("assemble_nearfield: one element has more near pairs than the staging buffer");
             return IGB_ERR_UNSUPPORTED;
         }
-        const int64_t k0 = op->near_ptr[e0], k1 = op->near_ptr[e1];
-        reg.clear();
-        reg_big.clear();
-        sing.clear();
-        for (int64_t k = k0; k < k1; ++k) {
-            const int kind = op->near_kind[k];
-            ((kind & 15) != 0 ? sing : points(kind) <= 49 ? reg : reg_big).push_back(int(k));
-        }
+        const int64_t k0 = op->near_ptr[e0];
         A.slot0 = k0;
-        // regular pairs with at most 49 points per element, then the larger regular
-        // rules, then the touching pairs
-        std::vector<int> lst(reg);
-        lst.insert(lst.end(), reg_big.begin(), reg_big.end());
-        lst.insert(lst.end(), sing.begin(), sing.end());
-        if (!lst.empty())
-            IGB_HIP(hipMemcpyAsync(d_list.ptr, lst.data(), lst.size() * sizeof(int), hipMemcpyHostToDevice, s));
-        if (!reg.empty()) {
-            A.list = d_list.as<int>();
-            A.nlist = int64_t(reg.size());
-            hipLaunchKernelGGL((near_regular<P, HARD, 49>), dim3(unsigned(reg.size())), dim3(NEAR_THREADS), 0, s, A);
-            IGB_HIP(hipGetLastError());
-        }
-        if (!reg_big.empty()) {
-            A.list = d_list.as<int>() + reg.size();
-            A.nlist = int64_t(reg_big.size());
-            hipLaunchKernelGGL((near_regular<P, HARD, REG_POINTS_MAX>), dim3(unsigned(reg_big.size())),
-                               dim3(NEAR_THREADS), 0, s, A);
-            IGB_HIP(hipGetLastError());
-        }
-        if (!sing.empty()) {
-            A.list = d_list.as<int>() + reg.size() + reg_big.size();
-            A.nlist = int64_t(sing.size());
-            // the nets are read at the largest geometry degree (2 or 3)
-            if (geo_deg <= 2)
-                hipLaunchKernelGGL((near_singular<P, HARD, 2>), dim3(unsigned(sing.size())), dim3(NEAR_THREADS), 0, s, A);
-            else
-                hipLaunchKernelGGL((near_singular<P, HARD, 3>), dim3(unsigned(sing.size())), dim3(NEAR_THREADS), 0, s, A);
-            IGB_HIP(hipGetLastError());
-        }
+        // regular pairs, a workgroup per target element and segment of its pairs
+        int64_t longest = 0;
+        for (int64_t e = e0; e < e1; ++e) longest = std::max(longest, op->near_ptr[e + 1] - op->near_ptr[e]);
+        const dim3 rgrid(unsigned(e1 - e0), unsigned((longest + REG_SEG - 1) / REG_SEG));
+        hipLaunchKernelGGL((near_regular<P, HARD, REG_POINTS_SMALL>), rgrid, dim3(64), 0, s, A, int(e0));
+        if (op->near_points_max > REG_POINTS_SMALL)
+            hipLaunchKernelGGL((near_regular<P, HARD, REG_POINTS_MAX>), rgrid, dim3(64), 0, s, A, int(e0));
+        IGB_HIP(hipGetLastError());
+        // touching pairs (the nets are read at the largest geometry degree, 2 or 3)
+        const int64_t t0 = op->near_touch_ptr[e0], nt = op->near_touch_ptr[e1] - t0;
+        A.touch = d_touch.as<int2>() + t0;
+        if (nt > 0 && geo_deg <= 2)
+            hipLaunchKernelGGL((near_singular<P, HARD, 2>), dim3(unsigned(nt)), dim3(NEAR_THREADS), 0, s, A);
+        else if (nt > 0)
+            hipLaunchKernelGGL((near_singular<P, HARD, 3>), dim3(unsigned(nt)), dim3(NEAR_THREADS), 0, s, A);
+        IGB_HIP(hipGetLastError());
         // rows touched by the chunk's target elements
         int64_t rlo = op->N, rhi = -1;
         for (int64_t e = e0; e < e1; ++e) {
@@ -830,8 +1047,7 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
         C.row_ptr = op->d_rowptr.as<int64_t>();
         C.col = op->d_col.as<int>();
         C.val = op->d_val.as<double2>();
-        C.near_ptr = op->d_near_ptr.as<int64_t>();
-        C.near_src = op->d_near_src.as<int>();
+        C.slots = slots;
         C.stage = d_stage.as<double2>();
         C.slot0 = k0;
         C.e_lo = e0;

@@ -286,6 +286,8 @@ igb_status near_classify(igb_op op) {
         op->aspect_max = std::max(op->aspect_max, std::max(side[2 * e], side[2 * e + 1]) /
                                                       std::max(1e-300, std::min(side[2 * e], side[2 * e + 1])));
     op->near_kind.resize(op->near_src.size());
+    std::vector<std::vector<int2>> touch(E);   // touching pairs of each element
+    std::vector<int> points(E, 0);             // most points of its regular rules
     std::atomic<int> bad_shared{-1};   // first inconsistency found: shared corner count (or 2)
     parallel_for(E, 64, [&](int64_t e) {
         for (int64_t k = op->near_ptr[e]; k < op->near_ptr[e + 1]; ++k) {
@@ -299,6 +301,7 @@ igb_status near_classify(igb_op op) {
                         ++shared;
                     }
             int kind = 0;
+            if (shared > 0) touch[e].push_back(make_int2(int(k), int(e)));
             if (e == f) {
                 kind = 4;
             } else if (shared == 2) {
@@ -335,6 +338,7 @@ igb_status near_classify(igb_op op) {
                     ord[2 * x + 1] = nv;
                 }
                 kind = (ord[0] << 8) | (ord[1] << 12) | (ord[2] << 16) | (ord[3] << 20);
+                points[e] = std::max(points[e], std::max(ord[0] * ord[1], ord[2] * ord[3]));
             } else {
                 int expect = -1;
                 bad_shared.compare_exchange_strong(expect, shared);
@@ -350,6 +354,11 @@ igb_status near_classify(igb_op op) {
         set_error("assemble_nearfield: elements share %d corners", bad_shared.load());
         return IGB_ERR_GEOMETRY;
     }
+    op->near_points_max = *std::max_element(points.begin(), points.end());
+    op->near_touch_ptr.assign(E + 1, 0);
+    for (int64_t e = 0; e < E; ++e) op->near_touch_ptr[e + 1] = op->near_touch_ptr[e] + int64_t(touch[e].size());
+    op->near_touch.reserve(op->near_touch_ptr[E]);
+    for (const std::vector<int2>& v : touch) op->near_touch.insert(op->near_touch.end(), v.begin(), v.end());
     return IGB_OK;
 }
 
