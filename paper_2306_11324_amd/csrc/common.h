@@ -266,7 +266,7 @@ struct igb_op_s {
     igb::DevBuf d_hx, d_hy;
     // right-hand side and far-field buffers (kept between calls): Gauss table,
     // directions, element contributions, observation directions, quadrature
-    // points and densities
+    // points and densities (d_q_loc also holds the far field's partial sums)
     igb::DevBuf d_gauss, d_q_dirs, d_q_loc, d_q_obs, d_q_geo, d_q_dens;
     // false for a single boundary integral operator (no right-hand side or representation)
     bool system = true;

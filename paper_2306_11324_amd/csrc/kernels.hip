@@ -2282,47 +2282,15 @@ __global__ __launch_bounds__(256) void density_points(QuadGeoArgs A, const doubl
     }
 }
 
-__global__ __launch_bounds__(256) void farfield_sum(const double* geo, const double2* dens,
-                                                    int64_t npts, const double* obs, int nobs,
-                                                    double kappa, int hard, double2* uinf) {
-    __shared__ double2 red[256];
-    const int o = blockIdx.x, dir = blockIdx.y;
-    const double* xh = obs + 3 * o;
-    const double2* D = dens + int64_t(dir) * npts;
-    double2 acc = make_double2(0, 0);
-    for (int64_t i = threadIdx.x; i < npts; i += 256) {
-        const double* g = geo + i * 8;
-        const double ph = -kappa * (xh[0] * g[0] + xh[1] * g[1] + xh[2] * g[2]);
-        double sn, cs;
-        sincos(ph, &sn, &cs);
-        const double wt = g[7] * (hard ? (xh[0] * g[3] + xh[1] * g[4] + xh[2] * g[5]) : g[6]);
-        const double2 z = cmul(make_double2(cs * wt, sn * wt), D[i]);
-        acc = cadd(acc, z);
-    }
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] = cadd(red[threadIdx.x], red[threadIdx.x + s]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const double c = 1.0 / (4.0 * M_PI);
-        double2 r = red[0];
-        // soft: -(1/4pi) S ; hard: -(i kappa / 4pi) S
-        uinf[int64_t(dir) * nobs + o] = hard ? make_double2(c * kappa * r.y, -c * kappa * r.x)
-                                             : make_double2(-c * r.x, -c * r.y);
-    }
-}
-
-// kernel of the representation at one point pair, surface data g = (y, n~, a, w):
+// Kernel of the representation at one point pair, surface data g = (y, n~, a, w):
 // soft -G a w, hard G (i kappa r - 1)/r^2 ((y - x).n~) w (used by both potential evaluations)
 __device__ __forceinline__ double2 repr_kernel(const double* x, const double* g, double kappa, int hard) {
     const double d0 = g[0] - x[0], d1 = g[1] - x[1], d2 = g[2] - x[2];   // y - x
-    const double r = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-    const double ir = 1.0 / r, kr = kappa * r;
+    const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+    const double ir = rsqrt_fast(r2), kr = kappa * (r2 * ir);
     double sn, cs;
-    sincos(kr, &sn, &cs);
-    const double c4 = 0.07957747154594767 * ir;
+    sincos_fast(kr, sn, cs);
+    const double c4 = 0.07957747154594767 * ir;   // 1/(4 pi r)
     if (hard) {
         const double dn = (d0 * g[3] + d1 * g[4] + d2 * g[5]) * ir * ir * g[7];
         return make_double2(c4 * dn * (-cs - sn * kr), c4 * dn * (cs * kr - sn));
@@ -2331,25 +2299,172 @@ __device__ __forceinline__ double2 repr_kernel(const double* x, const double* g,
     return make_double2(wa * cs, wa * sn);
 }
 
-// scattered field at points off the boundary: soft u = -sum G a w dens,
-// hard u = sum G (i kappa r - 1)/r^2 ((y - x).n~) w dens; one workgroup per
-// (point, direction), fixed-order tree reduction
-__global__ __launch_bounds__(256) void potential_sum(const double* geo, const double2* dens, int64_t npts,
-                                                     const double* pts, int npt, double kappa, int hard,
-                                                     double2* u) {
+// Sums over all surface quadrature points, for every target and density column:
+//   SUM_FAR_SOFT / _HARD: far field, targets = unit directions x,
+//       -(1/4pi) sum e^{-i kappa x.y} a w dens,  -(i kappa/4pi) sum (x.n~) e^{-i kappa x.y} w dens
+//   SUM_POT_SOFT / _HARD: scattered field at the points x, sum repr_kernel dens
+enum { SUM_FAR_SOFT, SUM_FAR_HARD, SUM_POT_SOFT, SUM_POT_HARD };
+template <int KIND>
+__device__ __forceinline__ double2 sum_kernel(const double* x, const double* g, double kappa) {
+    if (KIND == SUM_POT_SOFT || KIND == SUM_POT_HARD) return repr_kernel(x, g, kappa, KIND == SUM_POT_HARD);
+    double sn, cs;
+    sincos_fast(-kappa * (x[0] * g[0] + x[1] * g[1] + x[2] * g[2]), sn, cs);
+    const double c = 0.07957747154594767 * g[7];
+    if (KIND == SUM_FAR_SOFT) {
+        const double wt = -c * g[6];
+        return make_double2(cs * wt, sn * wt);
+    }
+    const double wt = c * kappa * (x[0] * g[3] + x[1] * g[4] + x[2] * g[5]);   // -i (cs + i sn) = sn - i cs
+    return make_double2(sn * wt, -cs * wt);
+}
+
+// A workgroup takes 64 targets, a segment of the surface points and CB columns;
+// its waves take consecutive parts of the segment.  A lane keeps one target and
+// CB sums; the points' data and densities, the same for all lanes, are staged a
+// few at a time in the wave's own LDS (the next ones loading meanwhile) and read
+// as broadcasts, so that a kernel value costs no global access and serves CB
+// columns.  The waves' sums are added in order, then the segments'
+// (layer_sum_reduce); both numbers are fixed by the targets and points alone,
+// so a column's result does not depend on the other columns.
+// Bound by fp64 VALU issue (about 50 instructions per kernel value and 4 per
+// column), at 16 columns by the LDS broadcasts.  (A workgroup per target and
+// column, lanes over the points, with libm's sine and cosine per column
+// before: far field of 16 columns at 1000 directions on the level-5 star
+// 24.2 -> 1.1 ms; potential of 3 columns at 5000 points on the level-4 star,
+// sound-hard, 7.4 -> 1.5 ms.  Reading the points through the scalar cache
+// instead: 5.3 and 10.6 ms, its latency exposed at every point.)
+constexpr int LAYER_WAVES = 16;          // waves per workgroup
+constexpr int LAYER_GROUPS = 256;        // workgroups aimed at per column block
+constexpr int LAYER_TILE = 8;            // points staged at a time by a wave
+constexpr int LAYER_MIN_TARGETS = 24;    // fewer targets: lanes over the points (layer_sum_few)
+// segments of npts points for ntgt targets, with sums of at most `room` entries per
+// column (one: written in place)
+static inline int layer_segments(int64_t npts, int64_t ntgt, int64_t room) {
+    if (ntgt < LAYER_MIN_TARGETS) return 1;
+    const int64_t groups = (ntgt + 63) / 64;
+    return int(std::max<int64_t>(1, std::min(std::min(LAYER_GROUPS / groups, npts / (16 * LAYER_WAVES)), room / ntgt)));
+}
+template <int KIND, int CB>
+__global__ __launch_bounds__(64 * LAYER_WAVES) void layer_sum(const double* __restrict__ geo,
+                                                              const double2* __restrict__ dens, int64_t npts,
+                                                              const double* __restrict__ tgt, int ntgt, double kappa,
+                                                              int ncol, int nseg, double2* __restrict__ part) {
+    constexpr int NW = LAYER_WAVES, TP = LAYER_TILE, DL = (TP * CB + 63) / 64;
+    static_assert(TP * 8 == 64, "one geometry value per lane");
+    __shared__ double gs[NW][TP][8];
+    __shared__ double2 ds[NW][TP][CB];
+    __shared__ double2 red[NW][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int o = blockIdx.x * 64 + lane, oc = min(o, ntgt - 1), sg = blockIdx.y, c0 = blockIdx.z * CB;
+    const double x[3] = {tgt[3 * oc], tgt[3 * oc + 1], tgt[3 * oc + 2]};
+    // this wave's points (parts of at most one point's difference)
+    const int64_t np = int64_t(nseg) * NW, w = int64_t(sg) * NW + wave;
+    const int64_t i0 = npts * w / np, i1 = npts * (w + 1) / np;
+    double2 acc[CB];
+#pragma unroll
+    for (int c = 0; c < CB; ++c) acc[c] = make_double2(0, 0);
+    // points past the end repeat the last with density 0
+    double gr;
+    double2 dr[DL];
+    auto load = [&](int64_t i) {
+        gr = geo[min(i * 8 + lane, i1 * 8 - 8 + (lane & 7))];
+#pragma unroll
+        for (int q = 0; q < DL; ++q) {
+            const int t = q * 64 + lane, p = t % TP, c = t / TP;
+            dr[q] = c < CB && c0 + c < ncol && i + p < i1 ? dens[int64_t(c0 + c) * npts + i + p] : make_double2(0, 0);
+        }
+    };
+    if (i0 < i1) load(i0);
+    for (int64_t i = i0; i < i1; i += TP) {
+        wave_lds_sync();   // the tile before is read
+        (&gs[wave][0][0])[lane] = gr;
+#pragma unroll
+        for (int q = 0; q < DL; ++q) {
+            const int t = q * 64 + lane, p = t % TP, c = t / TP;
+            if (c < CB) ds[wave][p][c] = dr[q];
+        }
+        wave_lds_sync();
+        if (i + TP < i1) load(i + TP);
+#pragma unroll 2
+        for (int p = 0; p < TP; ++p) {
+            const double2 z = sum_kernel<KIND>(x, gs[wave][p], kappa);
+#pragma unroll
+            for (int c = 0; c < CB; ++c) acc[c] = cfma(z, ds[wave][p][c], acc[c]);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+        __syncthreads();
+        red[wave][lane] = acc[c];
+        __syncthreads();
+        if (wave == 0 && o < ntgt && c0 + c < ncol) {
+            double2 s = red[0][lane];
+#pragma unroll
+            for (int v = 1; v < NW; ++v) s = cadd(s, red[v][lane]);
+            part[(int64_t(sg) * ncol + c0 + c) * ntgt + o] = s;
+        }
+    }
+}
+
+// out[col][target] = sum of the segments' sums: 16 targets per workgroup, 16 strided
+// partial sums each, added in order
+__global__ __launch_bounds__(256) void layer_sum_reduce(const double2* __restrict__ part, int nseg, int ntgt, int ncol,
+                                                        double2* __restrict__ out) {
+    __shared__ double2 red[16][16];
+    const int t = threadIdx.x >> 4, l = threadIdx.x & 15, o = blockIdx.x * 16 + l, c = blockIdx.y;
+    double2 s = make_double2(0, 0);
+    if (o < ntgt)
+        for (int k = t; k < nseg; k += 16) s = cadd(s, part[(int64_t(k) * ncol + c) * ntgt + o]);
+    red[t][l] = s;
+    __syncthreads();
+    if (t == 0 && o < ntgt) {
+#pragma unroll
+        for (int k = 1; k < 16; ++k) s = cadd(s, red[k][l]);
+        out[int64_t(c) * ntgt + o] = s;
+    }
+}
+
+// the same for few targets: a workgroup per (target, column), lanes over the points
+template <int KIND>
+__global__ __launch_bounds__(256) void layer_sum_few(const double* __restrict__ geo, const double2* __restrict__ dens,
+                                                     int64_t npts, const double* __restrict__ tgt, int ntgt,
+                                                     double kappa, double2* __restrict__ out) {
     __shared__ double2 red[256];
-    const int o = blockIdx.x, dir = blockIdx.y;
-    const double* x = pts + 3 * o;
-    const double2* D = dens + int64_t(dir) * npts;
+    const int o = blockIdx.x, col = blockIdx.y;
+    const double2* D = dens + int64_t(col) * npts;
     double2 acc = make_double2(0, 0);
-    for (int64_t i = threadIdx.x; i < npts; i += 256) acc = cfma(repr_kernel(x, geo + i * 8, kappa, hard), D[i], acc);
+    for (int64_t i = threadIdx.x; i < npts; i += 256)
+        acc = cfma(sum_kernel<KIND>(tgt + 3 * o, geo + i * 8, kappa), D[i], acc);
     red[threadIdx.x] = acc;
     __syncthreads();
     for (int st = 128; st > 0; st >>= 1) {
         if (threadIdx.x < st) red[threadIdx.x] = cadd(red[threadIdx.x], red[threadIdx.x + st]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) u[int64_t(dir) * npt + o] = red[0];
+    if (threadIdx.x == 0) out[int64_t(col) * ntgt + o] = red[0];
+}
+
+template <int KIND>
+static void launch_layer_sum(const double* geo, const double2* dens, int64_t npts, const double* tgt, int ntgt,
+                             double kappa, int ncol, int nseg, double2* part, double2* out, hipStream_t s) {
+    if (ntgt < LAYER_MIN_TARGETS) {
+        hipLaunchKernelGGL((layer_sum_few<KIND>), dim3(unsigned(ntgt), unsigned(ncol)), dim3(256), 0, s, geo, dens, npts,
+                           tgt, ntgt, kappa, out);
+        return;
+    }
+    if (nseg == 1) part = out;
+    // columns per wave: the smallest of 1, 4, 16 that holds them all (16 beyond)
+    const int cb = ncol == 1 ? 1 : ncol <= 4 ? 4 : 16;
+    const dim3 grid(unsigned((ntgt + 63) / 64), unsigned(nseg), unsigned((ncol + cb - 1) / cb)), block(64 * LAYER_WAVES);
+    if (cb == 1)
+        hipLaunchKernelGGL((layer_sum<KIND, 1>), grid, block, 0, s, geo, dens, npts, tgt, ntgt, kappa, ncol, nseg, part);
+    else if (cb == 4)
+        hipLaunchKernelGGL((layer_sum<KIND, 4>), grid, block, 0, s, geo, dens, npts, tgt, ntgt, kappa, ncol, nseg, part);
+    else
+        hipLaunchKernelGGL((layer_sum<KIND, 16>), grid, block, 0, s, geo, dens, npts, tgt, ntgt, kappa, ncol, nseg, part);
+    if (nseg > 1)
+        hipLaunchKernelGGL(layer_sum_reduce, dim3(unsigned((ntgt + 15) / 16), unsigned(ncol)), dim3(256), 0, s, part, nseg,
+                       ntgt, ncol, out);
 }
 
 // H^2 potential, sources: moments of the finest source clusters (s x s
@@ -2508,21 +2623,53 @@ __device__ double2 pot_l2p(const double* x, const double* lo, const double* hi, 
 // few points gives each point a group of lanes (a power of two) that split
 // every tile and add their partial sums in a fixed order, so a column's result
 // does not depend on the others.
+// (A staged source holds its position and the density with every factor that does
+// not depend on the point: 5 doubles sound-soft, 8 with the normal sound-hard.
+// Bound by fp64 VALU issue, about 55 instructions per kernel value; 200,000
+// points around the level-5 sphere, kappa 8, q 6: 36.8 -> 19.1 ms with the short
+// reciprocal square root and sine / cosine.)
 constexpr int POT_TILE = 256;   // source points per LDS tile
+template <bool HARD>
 __global__ __launch_bounds__(POT_LEAF_POINTS) void pot_l2p_near(
     const double* __restrict__ pts, const int* __restrict__ perm, const int* __restrict__ box_ptr,
     const double* __restrict__ box_lo, const double* __restrict__ box_hi, const double* __restrict__ tch, int q,
     const double2* __restrict__ lbox, int ncol, const int* __restrict__ m2p_ptr, const int* __restrict__ m2p_src,
     const double* __restrict__ nodes, const double2* __restrict__ xh, const int* __restrict__ near_ptr,
     const int* __restrict__ near_leaf, int d, int L, int nel1, int nqp, const double* __restrict__ geo,
-    const double2* __restrict__ dens, int64_t nqtot, double kappa, int hard, int npt, double2* __restrict__ u) {
+    const double2* __restrict__ dens, int64_t nqtot, double kappa, int npt, double2* __restrict__ u) {
     // the box expansion, the source tiles and the partial sums share the LDS (one after the other)
-    constexpr int LX = (QMAX + 1) * (QMAX + 1) * (QMAX + 1), TL = POT_TILE * 5;
+    constexpr int W = HARD ? 8 : 6;   // doubles per staged source (sound-soft: one unused)
+    constexpr int LX = (QMAX + 1) * (QMAX + 1) * (QMAX + 1), TL = POT_TILE * W / 2;
     static_assert(TL >= POT_LEAF_POINTS, "partial sums fit the tile space");
     __shared__ double2 smem[LX > TL ? LX : TL];
     double2* lx = smem;
-    double(*tg)[8] = reinterpret_cast<double(*)[8]>(smem);     // [POT_TILE][8]
-    double2* td = smem + POT_TILE * 4;                           // [POT_TILE]
+    double(*tg)[W] = reinterpret_cast<double(*)[W]>(smem);   // [POT_TILE]: y, (n~,) scaled density
+    // g = (y, n~, a), weight w, density d: -G a w d (sound-soft), G (i kappa r - 1)/r^2 ((y - x).n~) w d
+    auto put = [&](int k, const double* g, double w, double2 d) {
+        const double f = 0.07957747154594767 * (HARD ? w : -w * g[6]);   // 1/(4 pi)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            tg[k][c] = g[c];
+            if (HARD) tg[k][3 + c] = g[3 + c];
+        }
+        tg[k][W - 2] = f * d.x;
+        tg[k][W - 1] = f * d.y;
+    };
+    auto term = [&](const double* x, const double* t, double2 acc) {
+        const double d0 = t[0] - x[0], d1 = t[1] - x[1], d2 = t[2] - x[2];
+        const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+        const double ir = rsqrt_fast(r2), kr = kappa * (r2 * ir);
+        double sn, cs;
+        sincos_fast(kr, sn, cs);
+        double2 z;
+        if (HARD) {
+            const double h = (d0 * t[3] + d1 * t[4] + d2 * t[5]) * (ir * ir * ir);
+            z = make_double2(h * (-cs - sn * kr), h * (cs * kr - sn));
+        } else {
+            z = make_double2(cs * ir, sn * ir);
+        }
+        return cfma(z, make_double2(t[W - 2], t[W - 1]), acc);
+    };
     const int b = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
     const int q1 = q + 1, nq = q1 * q1, n3 = nq * q1;
     const bool has_far = lbox != nullptr;
@@ -2554,14 +2701,11 @@ __global__ __launch_bounds__(POT_LEAF_POINTS) void pot_l2p_near(
             for (int k = tid; k < cnt; k += POT_LEAF_POINTS) {
                 const int64_t sc = m2p_src[f0 + (t0 + k) / nq];
                 const int64_t ni = sc * nq + (t0 + k) % nq;
-#pragma unroll
-                for (int c = 0; c < 7; ++c) tg[k][c] = nodes[ni * 16 + c];
-                tg[k][7] = 1.0;
-                td[k] = xh[ni * ncol + r];
+                put(k, nodes + ni * 16, 1.0, xh[ni * ncol + r]);
             }
             __syncthreads();
             if (mine)
-                for (int k = lane; k < cnt; k += gs) acc = cfma(repr_kernel(x, tg[k], kappa, hard), td[k], acc);
+                for (int k = lane; k < cnt; k += gs) acc = term(x, tg[k], acc);
             __syncthreads();
         }
         for (int f = near_ptr[b]; f < near_ptr[b + 1]; ++f) {
@@ -2574,13 +2718,11 @@ __global__ __launch_bounds__(POT_LEAF_POINTS) void pot_l2p_near(
                     const int li = t0 + k, el = li / nqp, g = li % nqp;
                     const int64_t e = (patch * nel1 + cy * s + el / s) * nel1 + cx * s + el % s;
                     const int64_t gi = e * nqp + g;
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) tg[k][c] = geo[gi * 8 + c];
-                    td[k] = D[gi];
+                    put(k, geo + gi * 8, geo[gi * 8 + 7], D[gi]);
                 }
                 __syncthreads();
                 if (mine)
-                    for (int k = lane; k < cnt; k += gs) acc = cfma(repr_kernel(x, tg[k], kappa, hard), td[k], acc);
+                    for (int k = lane; k < cnt; k += gs) acc = term(x, tg[k], acc);
                 __syncthreads();
             }
         }
@@ -3557,6 +3699,10 @@ igb_status farfield_device(igb_op op, const double* coeffs, int ndir, const doub
         (st = op_reserve(op, op->d_q_geo, size_t(npts) * 8 * sizeof(double), "farfield")) ||
         (st = op_reserve(op, op->d_q_dens, size_t(ndir) * npts * sizeof(double2), "farfield")))
         return st;
+    // the segments' sums go where the right-hand side's element contributions do
+    const int64_t room = g->nelem * (g->p + 1) * (g->p + 1);
+    const int nseg = layer_segments(npts, nobs, room);
+    if (nseg > 1 && (st = op_reserve(op, op->d_q_loc, size_t(ndir) * room * sizeof(double2), "farfield"))) return st;
     IGB_HIP(hipStreamSynchronize(s));   // earlier work on s may still read these buffers
     IGB_HIP(hipMemcpy(op->d_q_obs.ptr, on.data(), on.size() * sizeof(double), hipMemcpyHostToDevice));
     const DevBuf& d_obs = op->d_q_obs;
@@ -3575,9 +3721,9 @@ igb_status farfield_device(igb_op op, const double* coeffs, int ndir, const doub
              return IGB_OK;
          })))
         return st;
-    hipLaunchKernelGGL(farfield_sum, dim3(unsigned(nobs), unsigned(ndir)), dim3(256), 0, s, d_geo.as<double>(),
-                       d_dens.as<double2>(), npts, d_obs.as<double>(), nobs, op->kappa, hard ? 1 : 0,
-                       reinterpret_cast<double2*>(uinf));
+    auto sum = hard ? launch_layer_sum<SUM_FAR_HARD> : launch_layer_sum<SUM_FAR_SOFT>;
+    sum(d_geo.as<double>(), d_dens.as<double2>(), npts, d_obs.as<double>(), nobs, op->kappa, ndir,
+        nseg, op->d_q_loc.as<double2>(), reinterpret_cast<double2*>(uinf), s);
     IGB_HIP(hipGetLastError());
     IGB_HIP(hipStreamSynchronize(s));
     return IGB_OK;
@@ -3594,7 +3740,7 @@ igb_status potential_device(igb_op op, const double* coeffs, int ndir, const dou
     igb_status st;
     const int nqd = smooth_order(op, 8);
     const int64_t npts = g->nelem * nqd * nqd;
-    DevBuf d_pts, d_gl, d_geo, d_dens;
+    DevBuf d_pts, d_gl, d_geo, d_dens, d_part;
     std::vector<double> gl = gauss_table();
     if ((st = upload(d_pts, points, size_t(3) * npt, nullptr))) return st;
     if ((st = upload(d_gl, gl.data(), gl.size(), nullptr))) return st;
@@ -3613,9 +3759,12 @@ igb_status potential_device(igb_op op, const double* coeffs, int ndir, const dou
              return IGB_OK;
          })))
         return st;
-    hipLaunchKernelGGL(potential_sum, dim3(unsigned(npt), unsigned(ndir)), dim3(256), 0, s, d_geo.as<double>(),
-                       d_dens.as<double2>(), npts, d_pts.as<double>(), npt, op->kappa, hard ? 1 : 0,
-                       reinterpret_cast<double2*>(u));
+    // segments' sums, small beside the densities; without room for them one segment
+    int nseg = layer_segments(npts, npt, npts / 4);
+    if (nseg > 1 && alloc(d_part, size_t(nseg) * ndir * npt * sizeof(double2), nullptr)) nseg = 1;
+    auto sum = hard ? launch_layer_sum<SUM_POT_HARD> : launch_layer_sum<SUM_POT_SOFT>;
+    sum(d_geo.as<double>(), d_dens.as<double2>(), npts, d_pts.as<double>(), npt, op->kappa, ndir, nseg,
+        d_part.as<double2>(), reinterpret_cast<double2*>(u), s);
     IGB_HIP(hipGetLastError());
     IGB_HIP(hipStreamSynchronize(s));
     return IGB_OK;
@@ -3696,12 +3845,12 @@ igb_status potential_h2_device(igb_op op, const double* coeffs, int ndir, const 
                            d_fsrc.as<int>(), ndir, op->kappa, hard ? 1 : 0, d_lbox.as<double2>());
         IGB_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(pot_l2p_near, dim3(unsigned(nbox), unsigned(ndir)), dim3(POT_LEAF_POINTS), 0, s,
+    hipLaunchKernelGGL(hard ? pot_l2p_near<true> : pot_l2p_near<false>, dim3(unsigned(nbox), unsigned(ndir)), dim3(POT_LEAF_POINTS), 0, s,
                        d_pts.as<double>(), d_perm.as<int>(), d_bptr.as<int>(), d_blo.as<double>(), d_bhi.as<double>(),
                        d_tch.as<double>(), q, any_far ? d_lbox.as<double2>() : nullptr, ndir, d_mptr.as<int>(),
                        d_msrc.as<int>(), d_nodes.as<double>(), mom, d_nptr.as<int>(), d_nleaf.as<int>(),
                        g->m - lmax, lmax, g->nel1, nqd * nqd, d_geo.as<double>(), d_dens.as<double2>(), nqtot,
-                       op->kappa, hard ? 1 : 0, npt, reinterpret_cast<double2*>(u));
+                       op->kappa, npt, reinterpret_cast<double2*>(u));
     IGB_HIP(hipGetLastError());
     IGB_HIP(hipStreamSynchronize(s));   // temporaries are freed on return
     return IGB_OK;

@@ -176,12 +176,6 @@ __device__ __forceinline__ void point_data(const ElemRef& R, const double* Cu, c
 // (before: a workgroup per pair, values and products through LDS); level-5 hard
 // star, 5.3 million pairs: 73 -> 39 ms.
 // --------------------------------------------------------------------------
-// wavefront-wide ordering of LDS traffic inside one wave
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // points of the larger of a regular pair's two rules

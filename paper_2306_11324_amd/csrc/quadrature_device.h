@@ -22,6 +22,13 @@ __device__ __forceinline__ double2 cfma(double2 a, double2 b, double2 c) {
 }
 __device__ __forceinline__ double2 cscale(double2 a, double s) { return make_double2(a.x * s, a.y * s); }
 
+// wavefront-wide ordering of LDS traffic inside one wave
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // 1/x and 1/sqrt(x) for normal x: the hardware estimates (about 2^-24) and one
 // third-order correction; the result is within an ulp or two, at a fraction of
 // the instructions of the correctly rounded division and square root.
