@@ -125,7 +125,10 @@ constexpr int LM_W = 20;
 __global__ __launch_bounds__(64) void leaf_moments_wg(const double2* __restrict__ x, int64_t xstride,
                                                       const double* __restrict__ m1, int q, int d, int p, int L,
                                                       int k, int64_t leaf_off, double2* __restrict__ xh,
-                                                      int deriv_u, int deriv_v, int64_t m1_stride_kind, int ncol) {
+                                                      int64_t kind_stride, int64_t m1_stride_kind, int ncol) {
+    // moment kinds (blockIdx.z): values, then (sound-hard) the u and the v derivative
+    const int deriv_u = blockIdx.z == 1, deriv_v = blockIdx.z == 2;
+    xh += blockIdx.z * kind_stride;
     __shared__ double2 X[LM_W * LM_W];
     __shared__ double2 tmp[LM_W * (QMAX + 1)];
     __shared__ double mu[(QMAX + 1) * LM_W], mv[(QMAX + 1) * LM_W];
@@ -167,8 +170,10 @@ __global__ __launch_bounds__(64) void leaf_moments_wg(const double2* __restrict_
 }
 
 __global__ void leaf_moments(const double2* x, int64_t xstride, const double* m1, int q, int d, int p, int L,
-                             int k, int64_t leaf_off, int64_t nleaf, double2* xh, int deriv_u, int deriv_v,
+                             int k, int64_t leaf_off, int64_t nleaf, double2* xh, int64_t kind_stride,
                              int64_t m1_stride_kind, int ncol) {
+    const int deriv_u = blockIdx.z == 1, deriv_v = blockIdx.z == 2;   // moment kind, as in leaf_moments_wg
+    xh += blockIdx.z * kind_stride;
     const int nq = (q + 1) * (q + 1);
     const int64_t gid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (gid >= nleaf * nq * ncol) return;
@@ -208,7 +213,8 @@ constexpr int TNQ = TQ1 * TQ1;
 // 4 (q+1)^2 cb each, columns fastest; each column's operations and their order
 // do not depend on cb)
 __global__ __launch_bounds__(256) void m2m_wg(const double* __restrict__ T1, int q, int l, int64_t off_l,
-                                              int64_t off_l1, double2* xh, int ncol, int cb) {
+                                              int64_t off_l1, double2* xh, int64_t kind_stride, int ncol, int cb) {
+    xh += blockIdx.z * kind_stride;   // moment kind
     extern __shared__ double2 dyn[];
     __shared__ double T[2 * TQ1 * TQ1];
     const int q1 = q + 1, nq = q1 * q1, tid = threadIdx.x, nt = blockDim.x;
@@ -262,15 +268,16 @@ __global__ __launch_bounds__(256) void m2m_wg(const double* __restrict__ T1, int
 // workgroup within 48 KB of dynamic LDS
 // levels L-1 down to lmin (the coarser ones are not needed)
 static void launch_m2m_levels(const double* T1, int q, int L, int npatch, const std::vector<int64_t>& clu_off,
-                              double2* xh, int ncol, hipStream_t s, int lmin = 0) {
+                              double2* xh, int ncol, hipStream_t s, int lmin = 0, int kinds = 1,
+                              int64_t kind_stride = 0) {
     const int nq = (q + 1) * (q + 1);
     int cb = std::min(ncol, 8);
     while (cb > 2 && size_t(8) * nq * cb * sizeof(double2) > 48 * 1024) cb /= 2;
     const size_t lds = size_t(8) * nq * cb * sizeof(double2);
     const unsigned cblk = unsigned((ncol + cb - 1) / cb);
     for (int l = L - 1; l >= std::max(lmin, 0); --l)
-        hipLaunchKernelGGL(m2m_wg, dim3(unsigned(clusters_on_level(npatch, l)), cblk), dim3(cb >= 4 ? 256 : TREE_THREADS),
-                           lds, s, T1, q, l, clu_off[l], clu_off[l + 1], xh, ncol, cb);
+        hipLaunchKernelGGL(m2m_wg, dim3(unsigned(clusters_on_level(npatch, l)), cblk, unsigned(kinds)), dim3(cb >= 4 ? 256 : TREE_THREADS),
+                           lds, s, T1, q, l, clu_off[l], clu_off[l + 1], xh, kind_stride, ncol, cb);
 }
 
 // The far part of the product at S^2 index i and column r, gathered from the
@@ -342,9 +349,13 @@ __global__ __launch_bounds__(256) void down_project_leaf(const double2* __restri
                                                          const double* __restrict__ Tc,
                                                          const int64_t* __restrict__ clu_off,
                                                          const double* __restrict__ m1, int q, int w, int L,
-                                                         int lmin, int deriv_u, int deriv_v,
+                                                         int lmin, int64_t kind_stride,
                                                          int64_t m1_stride_kind, int ncol, int cb,
                                                          double2* __restrict__ leafbuf) {
+    // moment kinds (blockIdx.z): values, then (sound-hard) the u and the v derivative
+    const int deriv_u = blockIdx.z == 1, deriv_v = blockIdx.z == 2;
+    yh += blockIdx.z * kind_stride;
+    leafbuf += int64_t(blockIdx.z) * gridDim.x * ncol * w * w;
     extern __shared__ double2 dyn[];
     __shared__ double Mu[TQ1 * TQ1], Mv[TQ1 * TQ1];
     const int q1 = q + 1, nq = q1 * q1, tid = threadIdx.x, nt = blockDim.x;
@@ -1611,37 +1622,53 @@ __global__ __launch_bounds__(64 * NW) void m2l_chunks_lowrank(const double2* __r
     if (a < nq) part[ch * nq + a] = acc;
 }
 
-// coupling, sound-hard: per source the 7 node-scaled moment vectors
-//   n~_c xp (c = 0..2), (y.n~) xp, v_c = F_v,c xu - F_u,c xv
-// are formed in LDS; H acts on {(y.n~) xp, n~_c xp}, G on {n~_c xp, v_c}:
-// 10 partial vectors per chunk and column.
-template <int NT, class CT, int RB>
-__global__ __launch_bounds__(NT) void m2l_hard_chunks(const CT* __restrict__ coup, const double2* __restrict__ xh,
-                                                      int64_t kind_stride, const double* __restrict__ nodes,
-                                                      const int* __restrict__ far_src_g,
-                                                      const int64_t* __restrict__ chunk_pair,
-                                                      const int* __restrict__ chunk_len, int64_t nchunk, int nq,
-                                                      int ncol, double2* __restrict__ part) {
-    __shared__ double2 sv[7][NT * RB];
+// coupling, sound-hard, blocks of up to 15 columns: with the target nodes (x, n~)
+// at hand as well as the source nodes (y, n~), the tiles H and G act on
+//   R = sum_b H ((x - y).n~_y) xp,  S = sum_b G (n~_x.n~_y) xp,
+//   T_c = sum_b G v_c,  v_c = F_v,c xu - F_u,c xv  (c = 0..2):
+// 5 partial vectors per chunk and column (the matrix cores, whose operands
+// cannot carry node-pair factors, need 10 products with node-scaled sources).
+// One workgroup per (chunk, RB columns): thread (g, a) sums target node a over
+// the source nodes b = g mod NG, NG = 256 / nq groups, so that the lanes are full
+// at every degree (243 of 256 at q = 8, where one thread per node left 81 of
+// 128); the groups' sums meet in LDS in order.  A column's sums do not depend
+// on RB.
+// Bound by the tiles' HBM traffic (32 nq^2 bytes per pair) for a few columns.
+// Level-4 hard star, q = 8 (1.01 GB): one column 476 -> 224 us, 4 columns 642 ->
+// 500 us, 8 columns 1168 -> 778 us (before: one thread per node, 10 vectors).
+constexpr int HARD_VECS = 5;
+template <int RB>
+__global__ __launch_bounds__(256) void m2l_hard_chunks(const double2* __restrict__ coup, const double2* __restrict__ xh,
+                                                       int64_t kind_stride, const double* __restrict__ nodes,
+                                                       const int* __restrict__ far_src_g,
+                                                       const int* __restrict__ chunk_tgt,
+                                                       const int64_t* __restrict__ chunk_pair,
+                                                       const int* __restrict__ chunk_len, int nq, int ncol, int col0,
+                                                       double2* __restrict__ part) {
+    // source vectors xp, v_c [4][nq][RB] and nodes [nq][3]; afterwards the groups' sums [NG][nq][RB]
+    extern __shared__ double2 sv[];
     const int64_t ch = blockIdx.x;
-    if (ch >= nchunk) return;
-    const int c0 = blockIdx.y * RB;
-    const int a = threadIdx.x;
+    const int c0 = col0 + blockIdx.y * RB, tid = threadIdx.x, NG = 256 / nq;
+    const int g = min(tid / nq, NG - 1), a = min(tid - g * nq, nq - 1);   // (idle threads repeat a node)
     const int64_t p0 = chunk_pair[ch];
-    const int len = chunk_len[ch];
-    double2 rh[4][RB], rg[6][RB];
+    const int len = chunk_len[ch], vs = nq * RB;
+    double2* sn = sv + 4 * vs;
+    double X[6];
+    {
+        const double* T = nodes + (int64_t(chunk_tgt[ch]) * nq + a) * 16;
 #pragma unroll
-    for (int cb = 0; cb < RB; ++cb) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) rh[v][cb] = make_double2(0, 0);
-#pragma unroll
-        for (int v = 0; v < 6; ++v) rg[v][cb] = make_double2(0, 0);
+        for (int c = 0; c < 6; ++c) X[c] = T[c];
     }
+    double2 acc[HARD_VECS][RB];
+#pragma unroll
+    for (int v = 0; v < HARD_VECS; ++v)
+#pragma unroll
+        for (int cb = 0; cb < RB; ++cb) acc[v][cb] = make_double2(0, 0);
     for (int i = 0; i < len; ++i) {
         const int64_t pr = p0 + i;
         const int64_t src = far_src_g[pr];
         __syncthreads();
-        for (int idx = a; idx < nq * RB; idx += NT) {
+        for (int idx = tid; idx < vs; idx += 256) {
             const int cb = idx % RB, b = idx / RB;
             const double* Y = nodes + (src * nq + b) * 16;
             double2 xp = make_double2(0, 0), xu = xp, xv = xp;
@@ -1651,50 +1678,58 @@ __global__ __launch_bounds__(NT) void m2l_hard_chunks(const CT* __restrict__ cou
                 xu = xh[kind_stride + o];
                 xv = xh[2 * kind_stride + o];
             }
-            const double yn = Y[0] * Y[3] + Y[1] * Y[4] + Y[2] * Y[5];
+            sv[idx] = xp;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                sv[c][idx] = cscale(xp, Y[3 + c]);
-                sv[4 + c][idx] = make_double2(Y[11 + c] * xu.x - Y[8 + c] * xv.x, Y[11 + c] * xu.y - Y[8 + c] * xv.y);
-            }
-            sv[3][idx] = cscale(xp, yn);
+            for (int c = 0; c < 3; ++c)
+                sv[(1 + c) * vs + idx] =
+                    make_double2(Y[11 + c] * xu.x - Y[8 + c] * xv.x, Y[11 + c] * xu.y - Y[8 + c] * xv.y);
+            if (cb == 0)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) sn[b * 3 + c] = make_double2(Y[2 * c], Y[2 * c + 1]);
         }
         __syncthreads();
-        if (a < nq) {
-            const CT* K = coup + pr * nq * nq * 2 + a;
-            for (int b = 0; b < nq; ++b) {
-                const double2 G = to_d2(K[int64_t(b) * nq]), H = to_d2(K[int64_t(nq + b) * nq]);
+        const double2* K = coup + pr * nq * nq * 2 + a;
+#pragma unroll RB == 1 ? 4 : 2
+        for (int b = g; b < nq; b += NG) {
+            const double2 G = K[int64_t(b) * nq], H = K[int64_t(nq + b) * nq];
+            const double2 y0 = sn[b * 3], y1 = sn[b * 3 + 1], y2 = sn[b * 3 + 2];   // (y0 y1)(y2 n0)(n1 n2)
+            const double dn = (X[0] - y0.x) * y1.y + (X[1] - y0.y) * y2.x + (X[2] - y1.x) * y2.y;
+            const double nn = X[3] * y1.y + X[4] * y2.x + X[5] * y2.y;
+            const double2 Hd = cscale(H, dn), Gn = cscale(G, nn);
 #pragma unroll
-                for (int cb = 0; cb < RB; ++cb) {
-                    const int o = b * RB + cb;
-                    rh[0][cb] = cfma(H, sv[3][o], rh[0][cb]);
+            for (int cb = 0; cb < RB; ++cb) {
+                const double2* s = sv + b * RB + cb;
+                acc[0][cb] = cfma(Hd, s[0], acc[0][cb]);
+                acc[1][cb] = cfma(Gn, s[0], acc[1][cb]);
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        rh[1 + c][cb] = cfma(H, sv[c][o], rh[1 + c][cb]);
-                        rg[c][cb] = cfma(G, sv[c][o], rg[c][cb]);
-                        rg[3 + c][cb] = cfma(G, sv[4 + c][o], rg[3 + c][cb]);
-                    }
-                }
+                for (int c = 0; c < 3; ++c) acc[2 + c][cb] = cfma(G, s[(1 + c) * vs], acc[2 + c][cb]);
             }
         }
     }
-    if (a < nq)
 #pragma unroll
-        for (int cb = 0; cb < RB; ++cb) {
-            if (c0 + cb >= ncol) continue;
+    for (int v = 0; v < HARD_VECS; ++v) {
+        __syncthreads();
+        if (tid < NG * nq)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) part[((ch * 10 + v) * nq + a) * ncol + c0 + cb] = rh[v][cb];
-#pragma unroll
-            for (int v = 0; v < 6; ++v) part[((ch * 10 + 4 + v) * nq + a) * ncol + c0 + cb] = rg[v][cb];
+            for (int cb = 0; cb < RB; ++cb) sv[(g * nq + a) * RB + cb] = acc[v][cb];
+        __syncthreads();
+        for (int idx = tid; idx < vs; idx += 256) {
+            const int cb = idx % RB, b = idx / RB;
+            double2 s = sv[idx];
+            for (int h = 1; h < NG; ++h) s = cadd(s, sv[h * vs + idx]);
+            if (c0 + cb < ncol) part[((ch * HARD_VECS + v) * nq + b) * ncol + c0 + cb] = s;
         }
+    }
 }
 
 // target-side factors of the sound-hard coupling:
 //   y_p = -a R0 + a sum_c x_c R_c + i eta kappa^2 sum_c n~_c S_c
 //   y_u = -i eta sum_c F_v,c T_c,   y_v = +i eta sum_c F_u,c T_c
-// from raw[cluster][10][nq][C] = (R0, R_0..2, S_0..2, T_0..2)
-__global__ void m2l_finalize_hard(const double2* raw, const double* nodes, int64_t nclusters, int nq, double kappa,
-                                  HardMix hmix, int64_t kind_stride, int ncol, double2* yh) {
+// from raw[cluster][10][nq][C] = (R0, R_0..2, S_0..2, T_0..2), or (nvec = HARD_VECS)
+// from raw[cluster][5][nq][C] = (R, S, T_0..2) with R and S already carrying the
+// target's factors
+__global__ void m2l_finalize_hard(const double2* raw, int nvec, const double* nodes, int64_t nclusters, int nq,
+                                  double kappa, HardMix hmix, int64_t kind_stride, int ncol, double2* yh) {
     const int64_t gid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (gid >= nclusters * nq * ncol) return;
     const int r = int(gid % ncol);
@@ -1702,15 +1737,24 @@ __global__ void m2l_finalize_hard(const double2* raw, const double* nodes, int64
     const int64_t c = t / nq;
     const int a = int(t % nq);
     const double* X = nodes + t * 16;
-    const double2* rw = raw + (c * 10 * nq + a) * ncol + r;
+    const double2* rw = raw + (c * nvec * nq + a) * ncol + r;
     const int64_t vs = int64_t(nq) * ncol;
-    double2 yp = cscale(rw[0], -X[6]);
-    double2 su = make_double2(0, 0), sv = make_double2(0, 0), sn = make_double2(0, 0);
+    double2 yp, sn = make_double2(0, 0);
+    if (nvec == HARD_VECS) {
+        yp = cscale(rw[0], X[6]);
+        sn = rw[vs];
+    } else {
+        yp = cscale(rw[0], -X[6]);
+        for (int cc = 0; cc < 3; ++cc) {
+            yp = cadd(yp, cscale(rw[(1 + cc) * vs], X[6] * X[cc]));
+            sn = cadd(sn, cscale(rw[(4 + cc) * vs], X[3 + cc]));
+        }
+    }
+    double2 su = make_double2(0, 0), sv = make_double2(0, 0);
     for (int cc = 0; cc < 3; ++cc) {
-        yp = cadd(yp, cscale(rw[(1 + cc) * vs], X[6] * X[cc]));
-        sn = cadd(sn, cscale(rw[(4 + cc) * vs], X[3 + cc]));
-        su = cadd(su, cscale(rw[(7 + cc) * vs], X[11 + cc]));
-        sv = cadd(sv, cscale(rw[(7 + cc) * vs], X[8 + cc]));
+        const double2 t = rw[(nvec - 3 + cc) * vs];
+        su = cadd(su, cscale(t, X[11 + cc]));
+        sv = cadd(sv, cscale(t, X[8 + cc]));
     }
     // yp is the -K part: ck K = -ck yp; W: -kappa^2 sn (normal part), su - sv (curl part)
     const double2 mck = make_double2(-hmix.ck.x, -hmix.ck.y);
@@ -3139,10 +3183,19 @@ static void launch_m2l_fp64(igb_op op, const MatvecWork& W, double2* xh, int64_t
         return;
     }
     if (op->bc == IGB_HARD) {
-        constexpr int RB = 2;
-        hipLaunchKernelGGL((m2l_hard_chunks<NT, double2, RB>), dim3(unsigned(nchunk), unsigned((ncol + RB - 1) / RB)),
-                           dim3(NT), 0, s, coup, xh, ks, op->d_nodes.as<double>(), op->d_far_src.as<int>(),
-                           C.d_pair.as<int64_t>(), C.d_len.as<int>(), nchunk, op->nq, ncol, W.part);
+        // blocks of 4 columns, the last with one column idle rather than a block of 2 and one of 1
+        // (level-4 star, q = 6, 7 columns: 412 against 500 us), then a block of 2 or 1 (2 columns:
+        // 147 us, as a block of 4: 265 us)
+        for (int c0 = 0; c0 < ncol;) {
+            const int left = ncol - c0, rb = left >= 3 ? 4 : left, nb = rb == 4 ? (left + 1) / 4 : 1;
+            const size_t lds =
+                std::max<size_t>(size_t(4 * rb + 3), size_t(256 / op->nq) * rb) * op->nq * sizeof(double2);
+            auto kern = rb == 1 ? m2l_hard_chunks<1> : rb == 2 ? m2l_hard_chunks<2> : m2l_hard_chunks<4>;
+            hipLaunchKernelGGL(kern, dim3(unsigned(nchunk), unsigned(nb)), dim3(256), lds, s, coup, xh, ks,
+                               op->d_nodes.as<double>(), op->d_far_src.as<int>(), C.d_tgt.as<int>(),
+                               C.d_pair.as<int64_t>(), C.d_len.as<int>(), op->nq, ncol, c0, W.part);
+            c0 += nb * rb;
+        }
     } else if (ncol == 1 && op->d_lr.ptr) {
         hipLaunchKernelGGL(m2l_chunks_lowrank<LR_WAVES>, dim3(unsigned(nchunk)), dim3(64 * LR_WAVES), 0, s,
                            op->d_lr.as<double2>(),
@@ -3288,20 +3341,21 @@ static igb_status matvec_launches(igb_op op, const MatvecWork& W, const double* 
 // y = A x: the launch sequence is captured once per (x, y, columns, parts,
 // stream) into a HIP graph and replayed; it holds kernel launches only (no
 // memsets, no allocation).  Kernel timing (profile mode) launches directly.
-// leaf moments of one kind (derivative flags du, dv) of ncol columns into xh
-static void launch_leaf_moments(igb_op op, const double2* x2, double2* xh, int du, int dv, int ncol, hipStream_t s) {
+// leaf moments of ncol columns into xh, one kind (values) or three (kind_stride apart)
+static void launch_leaf_moments(igb_op op, const double2* x2, double2* xh, int kinds, int64_t ks, int ncol,
+                                hipStream_t s) {
     igb_geom g = op->geom;
     const int q = op->q, L = op->L, nq = op->nq;
     const int64_t nleaf = clusters_on_level(g->npatch, L);
     const int w = (1 << op->d) + g->p;
     const int64_t stride_kind = int64_t(1 << L) * (q + 1) * w;
     if (w <= LM_W)
-        hipLaunchKernelGGL(leaf_moments_wg, dim3(unsigned(nleaf), unsigned(ncol)), dim3(64), 0, s, x2, g->n2,
-                           op->d_m1.as<double>(), q, op->d, g->p, L, g->k, op->clu_off[L], xh, du, dv, stride_kind,
+        hipLaunchKernelGGL(leaf_moments_wg, dim3(unsigned(nleaf), unsigned(ncol), unsigned(kinds)), dim3(64), 0, s, x2,
+                           g->n2, op->d_m1.as<double>(), q, op->d, g->p, L, g->k, op->clu_off[L], xh, ks, stride_kind,
                            ncol);
     else
-        hipLaunchKernelGGL(leaf_moments, dim3(blocks_for(nleaf * nq * ncol, 256)), dim3(256), 0, s, x2, g->n2,
-                           op->d_m1.as<double>(), q, op->d, g->p, L, g->k, op->clu_off[L], nleaf, xh, du, dv,
+        hipLaunchKernelGGL(leaf_moments, dim3(blocks_for(nleaf * nq * ncol, 256), 1, unsigned(kinds)), dim3(256), 0, s,
+                           x2, g->n2, op->d_m1.as<double>(), q, op->d, g->p, L, g->k, op->clu_off[L], nleaf, xh, ks,
                            stride_kind, ncol);
 }
 
@@ -3479,20 +3533,17 @@ static igb_status matvec_launches(igb_op op, const MatvecWork& W, const double* 
         }
         const int kinds = hard ? 3 : 1;
         const int64_t ks = op->nclusters * nq * ncol;  // stride between moment kinds
-        const int du[3] = {0, 1, 0}, dv[3] = {0, 0, 1};
         const int64_t nleaf = clusters_on_level(g->npatch, L);
         const int64_t stride_kind = int64_t(1 << L) * (q + 1) * ((1 << op->d) + g->p);
         if ((st = timer_mark(op, 2, s))) return st;
-        for (int kd = 0; kd < kinds; ++kd) {
-            launch_leaf_moments(op, x2, xh + kd * ks, du[kd], dv[kd], ncol, s);
-            launch_m2m_levels(op->d_T.as<double>(), q, L, g->npatch, op->clu_off, xh + kd * ks, ncol, s,
-                              op->far_lmin);
-        }
+        launch_leaf_moments(op, x2, xh, kinds, ks, ncol, s);
+        launch_m2m_levels(op->d_T.as<double>(), q, L, g->npatch, op->clu_off, xh, ncol, s, op->far_lmin, kinds, ks);
         if ((st = timer_mark(op, 2, s))) return st;
         int pkind = 0;
         if ((st = launch_m2l(op, W, xh, ks, low, ncol, s, pkind))) return st;
         if ((st = timer_mark(op, 3, s))) return st;
-        const int nvec = hard ? 10 : 1;
+        // (the stored fp64 tiles' products of blocks below 16 columns carry the target factors)
+        const int nvec = !hard ? 1 : pkind == 0 && !op->prm.far_on_the_fly ? HARD_VECS : 10;
         double2* red_out = W.yraw;
         const int64_t per = int64_t(nvec) * nq * ncol;
         if (!hard) {
@@ -3510,33 +3561,32 @@ static igb_status matvec_launches(igb_op op, const MatvecWork& W, const double* 
                                W.part, op->chunks.d_tgt_ptr.as<int>(), op->nclusters, per, red_out);
         if (hard)
             hipLaunchKernelGGL(m2l_finalize_hard, dim3(blocks_for(op->nclusters * nq * ncol, 256)), dim3(256), 0, s,
-                               W.yraw, op->d_nodes.as<double>(), op->nclusters, nq, op->kappa,
+                               W.yraw, nvec, op->d_nodes.as<double>(), op->nclusters, nq, op->kappa,
                                op->hmix, ks, ncol, yh);
         const int w = (1 << op->d) + g->p;
         size_t dlds = 0;
         const int dcb = down_cols(ncol, q + 1, w, dlds);
-        const dim3 dgrid(unsigned(nleaf), unsigned((ncol + dcb - 1) / dcb)), dblock(dcb >= 4 ? 256 : TREE_THREADS);
+        const dim3 dgrid(unsigned(nleaf), unsigned((ncol + dcb - 1) / dcb), unsigned(kinds)),
+            dblock(dcb >= 4 ? 256 : TREE_THREADS);
         const double* Tc = op->d_Tc.as<double>();
         const int64_t* cof = op->d_cluoff.as<int64_t>();
         const double* m1 = op->d_m1.as<double>();
         double2* lb = W.leafbuf;
         const int lmin = op->far_lmin;
         if (hard) {
-            for (int kd = 0; kd < kinds; ++kd)
-                hipLaunchKernelGGL(down_project_leaf<double2>, dgrid, dblock, dlds, s, yh + kd * ks,
-                                   static_cast<const double2*>(nullptr), static_cast<const int*>(nullptr), Tc, cof, m1,
-                                   q, w, L, lmin, du[kd], dv[kd], stride_kind, ncol, dcb,
-                                   lb + kd * nleaf * ncol * w * w);
+            hipLaunchKernelGGL(down_project_leaf<double2>, dgrid, dblock, dlds, s, yh,
+                               static_cast<const double2*>(nullptr), static_cast<const int*>(nullptr), Tc, cof, m1, q, w,
+                               L, lmin, ks, stride_kind, ncol, dcb, lb);
         } else if (pkind == 1) {
             hipLaunchKernelGGL(down_project_leaf<float2>, dgrid, dblock, dlds, s, yh, static_cast<float2*>(W.part_lo),
-                               op->chunks_mfma.d_tgt_ptr.as<int>(), Tc, cof, m1, q, w, L, lmin, 0, 0, stride_kind,
+                               op->chunks_mfma.d_tgt_ptr.as<int>(), Tc, cof, m1, q, w, L, lmin, ks, stride_kind,
                                ncol, dcb, lb);
         } else {
             const bool lo = pkind == 2;
             hipLaunchKernelGGL(down_project_leaf<double2>, dgrid, dblock, dlds, s, yh,
                                lo ? static_cast<double2*>(W.part_lo) : W.part,
                                (lo ? op->chunks_mfma : op->chunks).d_tgt_ptr.as<int>(), Tc, cof, m1, q, w, L, lmin,
-                               0, 0, stride_kind, ncol, dcb, lb);
+                               ks, stride_kind, ncol, dcb, lb);
         }
         if ((st = timer_mark(op, 3, s))) return st;
     }
