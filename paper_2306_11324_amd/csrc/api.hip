@@ -5,7 +5,10 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <new>
+#include <system_error>
+#include <thread>
 
 #include "common.h"
 
@@ -25,6 +28,85 @@ bool charge(igb_ctx_s* c, size_t bytes) {
     return true;
 }
 
+// Device memory of released buffers, kept for the next allocations of the same
+// size: assembling and destroying level-5 sound-hard operators (18 GB each) in
+// turn is 0.105 s an operator, but 0.1-3 s where their memory goes back to the
+// driver each time (it stalls at some 100 GB/s of allocations and frees; slower
+// assembly, 0.45 s an operator, did not meet it).  Contexts without a budget
+// only; blocks of POOL_MIN bytes and more, POOL_BLOCKS of them and an eighth of
+// the device's memory at most (the longest kept go first), and none while less
+// than half of the device's memory is free.  Everything kept is freed when an
+// allocation fails and with the device's last context.  A buffer is kept after a
+// device synchronisation (hipFree implies one too), so a kept block is idle
+// whatever stream its last user or its next one runs on.
+namespace {
+constexpr size_t POOL_MIN = size_t(1) << 20, POOL_STEP = size_t(2) << 20;
+constexpr int POOL_BLOCKS = 64;
+struct DevPool {
+    struct Block {
+        void* ptr;
+        size_t bytes;
+    };
+    std::mutex mu;
+    Block blocks[POOL_BLOCKS];   // in order of release
+    int n = 0, contexts = 0;
+    size_t held = 0;
+    Block out(int i) {
+        const Block b = blocks[i];
+        held -= b.bytes;
+        for (--n; i < n; ++i) blocks[i] = blocks[i + 1];
+        return b;
+    }
+    void clear() {
+        while (n > 0) (void)hipFree(out(n - 1).ptr);
+    }
+};
+DevPool pools[SCRATCH_MAX_DEVICES];
+DevPool* pool_of(int device) { return device >= 0 && device < SCRATCH_MAX_DEVICES ? &pools[device] : nullptr; }
+}  // namespace
+
+void pool_enter(int device) {
+    if (DevPool* p = pool_of(device)) {
+        std::lock_guard<std::mutex> lk(p->mu);
+        ++p->contexts;
+    }
+}
+
+void pool_leave(int device) {
+    if (DevPool* p = pool_of(device)) {
+        std::lock_guard<std::mutex> lk(p->mu);
+        if (--p->contexts == 0) p->clear();
+    }
+}
+
+// keeps an idle block, or returns false
+static bool pool_put(int device, void* ptr, size_t bytes) {
+    int cur = -1;
+    size_t avail = 0, total = 0;
+    if (hipGetDevice(&cur) != hipSuccess || (cur != device && hipSetDevice(device) != hipSuccess)) return false;
+    const bool idle = hipDeviceSynchronize() == hipSuccess && hipMemGetInfo(&avail, &total) == hipSuccess;
+    if (cur != device) (void)hipSetDevice(cur);
+    DevPool* p = pool_of(device);
+    std::lock_guard<std::mutex> lk(p->mu);
+    if (!idle || p->contexts == 0 || bytes > total / 8) return false;
+    if (avail < total / 2) {
+        p->clear();
+        return false;
+    }
+    while (p->n == POOL_BLOCKS || p->held + bytes > total / 8) (void)hipFree(p->out(0).ptr);
+    p->blocks[p->n++] = DevPool::Block{ptr, bytes};
+    p->held += bytes;
+    return true;
+}
+
+void DevBuf::release() {
+    if (ptr && !(kept && pool_put(ctx->device, ptr, kept))) (void)hipFree(ptr);
+    if (ctx) uncharge(ctx, bytes);
+    ptr = nullptr;
+    bytes = kept = 0;
+    ctx = nullptr;
+}
+
 igb_status dev_malloc(DevBuf& b, size_t bytes, const char* who) {
     b.release();
     if (bytes == 0) return IGB_OK;
@@ -33,14 +115,38 @@ igb_status dev_malloc(DevBuf& b, size_t bytes, const char* who) {
         set_error("%s: HBM budget exceeded (%zu held + %zu > %zu bytes)", who, c->used.load(), bytes, c->budget);
         return IGB_ERR_BUDGET;
     }
-    const hipError_t e = hipMalloc(&b.ptr, bytes);
+    DevPool* p = c ? pool_of(c->device) : nullptr;
+    // (whole steps, which the driver takes anyway: equal sizes are what repeats)
+    const size_t size = p && c->budget == 0 && bytes >= POOL_MIN ? (bytes + POOL_STEP - 1) / POOL_STEP * POOL_STEP : 0;
+    if (size) {
+        std::lock_guard<std::mutex> lk(p->mu);
+        for (int i = p->n - 1; i >= 0 && !b.ptr; --i)
+            if (p->blocks[i].bytes == size) b.ptr = p->out(i).ptr;
+    }
+    hipError_t e = hipSuccess;
+    if (!b.ptr) {
+        e = hipMalloc(&b.ptr, size ? size : bytes);
+        if (e != hipSuccess && p) {
+            std::lock_guard<std::mutex> lk(p->mu);
+            if (p->n > 0) {   // once more without the kept blocks
+                (void)hipGetLastError();
+                p->clear();
+                e = hipMalloc(&b.ptr, size ? size : bytes);
+            }
+        }
+    }
     if (e != hipSuccess) {
         if (c) uncharge(c, bytes);
         b.ptr = nullptr;
         set_error("%s: hipMalloc of %zu bytes: %s", who, bytes, hipGetErrorString(e));
         return IGB_ERR_HIP;
     }
+#ifdef IGB_POISON
+    (void)hipMemset(b.ptr, 0xff, size ? size : bytes);
+    (void)hipDeviceSynchronize();
+#endif
     b.bytes = bytes;
+    b.kept = size;
     b.ctx = c;
     return IGB_OK;
 }
@@ -139,6 +245,7 @@ igb_status igb_ctx_create(int device, size_t hbm_budget_bytes, igb_ctx* out) {
         set_error("igb_ctx_create: %s", hipGetErrorString(e));
         return IGB_ERR_HIP;
     }
+    pool_enter(device);
     *out = c;
     return IGB_OK;
 }
@@ -148,6 +255,7 @@ igb_status igb_ctx_create(int device, size_t hbm_budget_bytes, igb_ctx* out) {
 void ctx_release(igb_ctx ctx) {
     if (!ctx || --ctx->refs > 0) return;
     if (ctx->stream) (void)hipStreamDestroy(ctx->stream);
+    if (!host_only(ctx)) pool_leave(ctx->device);
     delete ctx;
 }
 
@@ -289,7 +397,21 @@ static igb_status build_one(igb_ctx ctx, igb_geom g, const igb_op_params* prm, c
     op->nq = (prm->q + 1) * (prm->q + 1);
     op->N = op->bc == IGB_SOFT ? g->n2 : g->n0;
     igb_status st;
-    if ((st = tree_build(op)) || (st = near_classify(op)) || (st = near_pattern(op))) {
+    st = tree_build(op);
+    if (!st) {
+        // the pattern and the quadrature classes need the tree alone: side by side
+        igb_status sp = IGB_OK;
+        std::thread pattern;
+        try {
+            pattern = std::thread([&] { sp = near_pattern(op); });
+        } catch (const std::system_error&) {   // no thread to be had: one after the other
+            sp = near_pattern(op);
+        }
+        st = near_classify(op);
+        if (pattern.joinable()) pattern.join();
+        if (!st) st = sp;
+    }
+    if (st) {
         delete op;
         return st;
     }
@@ -298,13 +420,15 @@ static igb_status build_one(igb_ctx ctx, igb_geom g, const igb_op_params* prm, c
     const int ntile = op->bc == IGB_HARD ? 2 : 1;
     const size_t fp64_tiles =
         prm->far_on_the_fly ? 0 : size_t(op->nfar) * op->nq * op->nq * 16 * ntile + size_t(3) * op->nq * 16 + 256;
-    size_t need = fp64_tiles + size_t(op->nnz) * 20 + size_t(op->N + 1) * 8 + op->near_dcol.size() * 4 +
+    size_t need = fp64_tiles + size_t(op->nnz) * 16 + size_t(op->N + 1) * 8 + op->near_dcol.size() * 4 +
                   op->row_coff.size() * 8 + op->near_wgs.size() * sizeof(NearGroupWG) +
                   op->near_grp_rows.size() * 4 +
-                  size_t(op->nclusters) * op->nq * (16 * 8 + 32) + op->near_src.size() * 4;
+                  size_t(op->nclusters) * op->nq * (16 * 8 + 32);
     // held during assembly only: the staged element blocks and the near pair lists
-    const size_t transient = std::min<size_t>(op->near_src.size(), size_t(1) << 22) * nl * nl * 16 +
-                             op->near_src.size() * 12 + (size_t(1) << 20);
+    const size_t npairs = size_t(op->near_ptr[g->nelem]);
+    const size_t transient = std::min<size_t>(npairs, size_t(1) << 22) * nl * nl * 16 + npairs * 2 +
+                             op->leaf_src.size() * 4 + op->near_touch.size() * sizeof(NearTouch) +
+                             op->leaf_src.size() * 4 + (size_t(1) << 20);
     // the near field in tiles: fp32 values (bf16 operators), fp64 values (fp64 and fp32 operators)
     if (op->nnz > 0)
         need += size_t(op->near_tile_vals) * (prm->precision == IGB_MIX_BF16 ? 8 : 16) +
@@ -493,7 +617,7 @@ igb_status igb_op_get_info(igb_op op, igb_op_info* info) {
     info->nq = op->nq;
     info->far_pairs = op->nfar;
     for (int l = 0; l <= op->L && l < 16; ++l) info->far_per_level[l] = int64_t(op->far[l].src.size());
-    info->near_elem_pairs = int64_t(op->near_src.size());
+    info->near_elem_pairs = op->near_ptr.back();
     info->nnz = op->nnz;
     info->device_bytes = int64_t(op->dev_bytes);
     info->estimated_bytes = int64_t(op->estimated_bytes);
@@ -530,7 +654,9 @@ igb_status igb_op_near_csr(igb_op op, int64_t* row_ptr, int32_t* col, double* va
     if (st) return st;
     IGB_HIP(hipSetDevice(op->geom->ctx->device));
     std::memcpy(row_ptr, op->row_ptr.data(), op->row_ptr.size() * sizeof(int64_t));
-    std::memcpy(col, op->col.data(), op->col.size() * sizeof(int32_t));
+    for (int64_t r = 0; r < op->N; ++r)
+        std::memcpy(col + op->row_ptr[r], op->near_dcol.data() + op->row_coff[r],
+                    size_t(op->row_ptr[r + 1] - op->row_ptr[r]) * sizeof(int32_t));
     IGB_HIP(hipMemcpy(val, op->d_val.ptr, op->nnz * sizeof(double2), hipMemcpyDeviceToHost));
     return IGB_OK;
 }
@@ -588,8 +714,11 @@ igb_status igb_op_near_pairs(igb_op op, int64_t* ptr, int32_t* src, int32_t* kin
     }
     if (igb_status st0 = need_single_matrix(op, "igb_op_near_pairs")) return st0;
     std::memcpy(ptr, op->near_ptr.data(), op->near_ptr.size() * sizeof(int64_t));
-    std::memcpy(src, op->near_src.data(), op->near_src.size() * sizeof(int32_t));
-    std::memcpy(kind, op->near_kind.data(), op->near_kind.size() * sizeof(int32_t));
+    for (int64_t e = 0; e < op->geom->nelem; ++e)
+        std::memcpy(src + op->near_ptr[e], op->leaf_src.data() + op->leaf_src_ptr[leaf_of_element(op, e)],
+                    size_t(op->near_ptr[e + 1] - op->near_ptr[e]) * sizeof(int32_t));
+    for (int64_t k = 0; k < op->near_ptr.back(); ++k) kind[k] = int32_t(op->near_code[k]) << 8;
+    for (const NearTouch& t : op->near_touch) kind[t.k] = t.kind;
     return IGB_OK;
 }
 

@@ -81,23 +81,18 @@ bool charge(igb_ctx_s* c, size_t bytes);
 inline void uncharge(igb_ctx_s* c, size_t bytes) { c->used.fetch_sub(bytes); }
 
 // ----------------------------------------------------------------------------
-// device memory owned by a handle; freed in the destructor
+// device memory owned by a handle; released in the destructor
 // ----------------------------------------------------------------------------
 struct DevBuf {
     void* ptr = nullptr;
     size_t bytes = 0;
     igb_ctx_s* ctx = nullptr;   // context charged for the bytes
+    size_t kept = 0;            // size of the block, if it may be kept when released (else 0)
     DevBuf() = default;
     DevBuf(const DevBuf&) = delete;
     DevBuf& operator=(const DevBuf&) = delete;
     ~DevBuf() { release(); }
-    void release() {
-        if (ptr) (void)hipFree(ptr);
-        if (ctx) uncharge(ctx, bytes);
-        ptr = nullptr;
-        bytes = 0;
-        ctx = nullptr;
-    }
+    void release();
     template <class T> T* as() const { return static_cast<T*>(ptr); }
 };
 
@@ -105,11 +100,36 @@ struct DevBuf {
 // (message naming `who`) if that context's budget would be exceeded,
 // IGB_ERR_HIP if hipMalloc fails; b is empty after either.
 igb_status dev_malloc(DevBuf& b, size_t bytes, const char* who);
+// a context of the device begins, ends (what is kept of released buffers goes with the last)
+void pool_enter(int device);
+void pool_leave(int device);
 // As dev_malloc, but keeps b when it already holds at least `bytes`.
 inline igb_status dev_reserve(DevBuf& b, size_t bytes, const char* who) {
     return b.bytes >= bytes && b.ptr ? IGB_OK : dev_malloc(b, bytes, who);
 }
 
+}  // namespace igb
+
+namespace igb {
+// allocator whose resize leaves the elements uninitialised (for lists filled right after)
+template <class T>
+struct UninitAlloc : std::allocator<T> {
+    template <class U>
+    struct rebind {
+        using other = UninitAlloc<U>;
+    };
+    UninitAlloc() = default;
+    template <class U>
+    UninitAlloc(const UninitAlloc<U>&) {}
+    template <class U>
+    void construct(U* p) noexcept {
+        ::new (static_cast<void*>(p)) U;
+    }
+    template <class U, class... A>
+    void construct(U* p, A&&... a) {
+        ::new (static_cast<void*>(p)) U(std::forward<A>(a)...);
+    }
+};
 }  // namespace igb
 
 // Per-element data of a discretised geometry.
@@ -187,6 +207,13 @@ struct NearTile {
 // operators (coupling and near product)
 constexpr int MF64_MIN_COLS = 16;
 
+// a touching near pair: its index, target and source element, quadrature class (the
+// kind of igb_op_near_pairs)
+struct NearTouch {
+    int64_t k;
+    int e, f, kind, pad;
+};
+
 struct igb_op_s {
     igb_geom geom = nullptr;
     igb_op_params prm{};
@@ -208,21 +235,23 @@ struct igb_op_s {
     int64_t nfar = 0;
     int far_lmin = 0;                 // coarsest level with admissible pairs (L + 1: none); moments and
                                       // expansions of coarser levels are neither formed nor transferred
-    // near field: per target element the sorted near source elements
+    // near field: every element of a leaf has the same near source elements (those of
+    // the leaf's inadmissible leaves), sorted, once per leaf; near pair k of target
+    // element e in leaf l has the source leaf_src[leaf_src_ptr[l] + k - near_ptr[e]]
     std::vector<int64_t> near_ptr;    // [E+1]
-    std::vector<int> near_src;
+    std::vector<int> leaf_src;
+    std::vector<int64_t> leaf_src_ptr;        // [leaves+1]
     std::vector<std::vector<int>> near_leaf;  // per leaf (local index): sorted inadmissible leaves
-    std::vector<int> near_kind;       // per near pair: 0 regular (order in bits 8..), 1 vertex,
-                                      // 2 edge, 4 identical; transforms in bits 16.. / 20..
-    std::vector<int2> near_touch;         // touching pairs (near pair, target element) by target element
+    // per near pair the Gauss orders of a regular one (4 bits each: u and v of the test
+    // element, of the trial element), 0 for a touching one
+    std::vector<unsigned short, igb::UninitAlloc<unsigned short>> near_code;
+    std::vector<NearTouch> near_touch;    // touching pairs by target element
     std::vector<int64_t> near_touch_ptr;  // [E+1]
     int near_points_max = 0;              // most points per element of a regular pair's rules
-    // near CSR in the solution space
+    // near CSR in the solution space; rows with the same leaves have the same
+    // columns: each such list once (near_dcol) and per row the offset of its list
     std::vector<int64_t> row_ptr;
-    std::vector<int> col;
     int64_t nnz = 0;
-    // rows with the same leaves have the same columns: each such list once (near_dcol)
-    // and per row the offset of its list (the near products read columns from here)
     std::vector<int> near_dcol;
     std::vector<int64_t> row_coff;
     // the one-column near product by groups: workgroups of up to
@@ -243,14 +272,14 @@ struct igb_op_s {
     // its factors (complex entries) and the factors u_k [k][nq], v_k^T [nq][rank]
     igb::DevBuf d_lr, d_lr_rank, d_lr_off;
     int64_t lr_entries = 0;
-    igb::DevBuf d_rowptr, d_col, d_val, d_dcol, d_row_coff, d_near_wgs, d_near_grp_rows;
+    igb::DevBuf d_rowptr, d_val, d_dcol, d_row_coff, d_near_wgs, d_near_grp_rows;
     // bf16 operators: fp32 near-field values and fp32 copies of the columns for the
     // near product of the inner (refinement) matvecs
     igb::DevBuf d_val_lo, d_xnear_lo, d_near_tiles, d_near_tile_cols;
     // fp64 operators: fp64 near-field values in the same tiles, for the near
     // product of blocks of >= 16 columns on the fp64 matrix cores
     igb::DevBuf d_val64;
-    igb::DevBuf d_near_ptr, d_near_src;
+    igb::DevBuf d_near_ptr;
     igb::DevBuf d_s2_to_s0, d_s0_ptr, d_s0_reps;
     igb::DevBuf d_far_src;
     // reduced-precision path: source vectors rounded per matvec, fp32 partials
@@ -365,6 +394,7 @@ void gauss01_host(int n, std::vector<double>& x, std::vector<double>& w);
 igb_status geometry_build(igb_ctx ctx, const igb_patch* patches, int npatch, int m, int p,
                           igb_geom g);
 igb_status tree_build(igb_op op);
+int64_t leaf_of_element(const igb_op_s* op, int64_t e);
 igb_status near_classify(igb_op op);
 igb_status near_pattern(igb_op op);
 
@@ -428,25 +458,6 @@ int smooth_order(igb_op op, int base);
 // box's points directly) and the inadmissible clusters of level lmax (near,
 // direct quadrature).
 constexpr int POT_LEAF_POINTS = 128;
-// allocator whose resize leaves ints uninitialised (for lists filled right after)
-template <class T>
-struct UninitAlloc : std::allocator<T> {
-    template <class U>
-    struct rebind {
-        using other = UninitAlloc<U>;
-    };
-    UninitAlloc() = default;
-    template <class U>
-    UninitAlloc(const UninitAlloc<U>&) {}
-    template <class U>
-    void construct(U* p) noexcept {
-        ::new (static_cast<void*>(p)) U;
-    }
-    template <class U, class... A>
-    void construct(U* p, A&&... a) {
-        ::new (static_cast<void*>(p)) U(std::forward<A>(a)...);
-    }
-};
 using IdList = std::vector<int, UninitAlloc<int>>;
 
 struct PotentialPlan {

@@ -1922,7 +1922,8 @@ __global__ __launch_bounds__(64 * NWV) void spmv_groups(const NearGroupWG* __res
 // One thread per row walks the tile's list and the row's (both sorted; the
 // tile's list holds the row's).
 __global__ void near_tile_values(const NearTile* __restrict__ tiles, const int* __restrict__ tcol,
-                                 const int64_t* __restrict__ row_ptr, const int* __restrict__ col,
+                                 const int64_t* __restrict__ row_ptr, const int64_t* __restrict__ row_coff,
+                                 const int* __restrict__ dcol,
                                  const double2* __restrict__ val, float2* __restrict__ vt) {
     const NearTile& T = tiles[blockIdx.x];
     const int i = threadIdx.x;
@@ -1932,6 +1933,7 @@ __global__ void near_tile_values(const NearTile* __restrict__ tiles, const int* 
     const int r = T.rows[i];
     int64_t q = row_ptr[r];
     const int64_t qe = row_ptr[r + 1];
+    const int* col = dcol + row_coff[r] - q;   // the row's column list, indexed like its values
     const int nk = (nc + NEAR_TILE_K - 1) / NEAR_TILE_K * NEAR_TILE_K;
     for (int k = 0; k < nk; ++k) {
         float2 v = make_float2(0.f, 0.f);
@@ -2062,7 +2064,8 @@ __global__ __launch_bounds__(64 * NEAR_TILE_WAVES) void near_tiles_mfma(const Ne
 // lists as the fp32 layout, at the same offsets: a tile's fp64 region is no
 // longer than its fp32 one).
 __global__ void near_tile_values64(const NearTile* __restrict__ tiles, const int* __restrict__ tcol,
-                                   const int64_t* __restrict__ row_ptr, const int* __restrict__ col,
+                                   const int64_t* __restrict__ row_ptr, const int64_t* __restrict__ row_coff,
+                                 const int* __restrict__ dcol,
                                    const double2* __restrict__ val, double2* __restrict__ vt) {
     const NearTile& T = tiles[blockIdx.x];
     const int i = threadIdx.x;
@@ -2072,6 +2075,7 @@ __global__ void near_tile_values64(const NearTile* __restrict__ tiles, const int
     const int r = T.rows[i];
     int64_t q = row_ptr[r];
     const int64_t qe = row_ptr[r + 1];
+    const int* col = dcol + row_coff[r] - q;   // the row's column list, indexed like its values
     const int nk = (nc + MfmaF64::KB - 1) / MfmaF64::KB * MfmaF64::KB;
     for (int k = 0; k < nk; ++k) {
         double2 v = make_double2(0.0, 0.0);
@@ -2816,7 +2820,8 @@ igb_status assemble_near_device(igb_op op, hipStream_t s) {
         if ((st = upload(op->d_near_tile_cols, op->near_tile_cols.data(), op->near_tile_cols.size(), acct))) return st;
         if ((st = alloc(op->d_val64, size_t(op->near_tile_vals) * sizeof(double2), acct))) return st;
         hipLaunchKernelGGL(near_tile_values64, dim3(unsigned(nt)), dim3(64), 0, s, op->d_near_tiles.as<NearTile>(),
-                           op->d_near_tile_cols.as<int>(), op->d_rowptr.as<int64_t>(), op->d_col.as<int>(),
+                           op->d_near_tile_cols.as<int>(), op->d_rowptr.as<int64_t>(),
+                           op->d_row_coff.as<int64_t>(), op->d_dcol.as<int>(),
                            op->d_val.as<double2>(), op->d_val64.as<double2>());
         IGB_HIP(hipGetLastError());
         IGB_HIP(hipStreamSynchronize(s));
@@ -2831,7 +2836,8 @@ igb_status assemble_near_device(igb_op op, hipStream_t s) {
         if ((st = upload(op->d_near_tile_cols, op->near_tile_cols.data(), op->near_tile_cols.size(), acct))) return st;
         if ((st = alloc(op->d_val_lo, size_t(op->near_tile_vals) * sizeof(float2), acct))) return st;
         hipLaunchKernelGGL(near_tile_values, dim3(unsigned(nt)), dim3(64), 0, s, op->d_near_tiles.as<NearTile>(),
-                           op->d_near_tile_cols.as<int>(), op->d_rowptr.as<int64_t>(), op->d_col.as<int>(),
+                           op->d_near_tile_cols.as<int>(), op->d_rowptr.as<int64_t>(),
+                           op->d_row_coff.as<int64_t>(), op->d_dcol.as<int>(),
                            op->d_val.as<double2>(), op->d_val_lo.as<float2>());
         IGB_HIP(hipGetLastError());
         IGB_HIP(hipStreamSynchronize(s));

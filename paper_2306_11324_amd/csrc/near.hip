@@ -62,9 +62,10 @@ struct NearArgs {
     const double* C1;
     const double* gl;        // [NGMAX+1][2][NGMAX]: Gauss nodes / weights on [0,1] per order
     NearSlots slots;
-    const int* pair_f;       // near pair -> source element
-    const int* pair_kind;
-    const int2* touch;       // touching pairs handled by this launch: (pair, target element)
+    const int* leaf_src;           // near source elements of each leaf, sorted
+    const int64_t* leaf_src_ptr;   // [leaves + 1]
+    const unsigned short* code;    // near pair -> Gauss orders, 0 for a touching pair
+    const NearTouch* touch;        // touching pairs handled by this launch
     int64_t slot0;           // first staged pair
     double2* stage;          // [pairs][nloc*nloc], order: NearSlots
     int nel1;
@@ -179,8 +180,8 @@ __device__ __forceinline__ void point_data(const ElemRef& R, const double* Cu, c
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // points of the larger of a regular pair's two rules
-__host__ __device__ inline int regular_points(int kind) {
-    const int nx = ((kind >> 8) & 15) * ((kind >> 12) & 15), ny = ((kind >> 16) & 15) * ((kind >> 20) & 15);
+__device__ __forceinline__ int regular_points(int code) {
+    const int nx = (code & 15) * ((code >> 4) & 15), ny = ((code >> 8) & 15) * (code >> 12);
     return nx > ny ? nx : ny;
 }
 constexpr int REG_POINTS_SMALL = 36;   // rules of up to 6 x 6 points take the form with less LDS
@@ -267,13 +268,14 @@ __global__ __launch_bounds__(64, 2) void near_regular(NearArgs A, int e0) {
     const int np = int(min(int64_t(REG_SEG), A.slots.near_ptr[e + 1] - kb));
     if (np <= 0) return;
     const int tl = leaf_of(A.slots, e);
+    const int* src = A.leaf_src + A.leaf_src_ptr[tl] + int64_t(blockIdx.y) * REG_SEG;   // sources of the segment's pairs
     const ElemRef Re = elem_ref(A.bez, A.pg, A.nel1, e);
     constexpr int NONE = 0xffff;   // (orders are at most 12: no rule has this code)
     int next = NONE;
     for (int k = lane; k < np; k += 64) {
-        const int kd = A.pair_kind[kb + k];
-        const bool mine = (kd & 15) == 0 && (regular_points(kd) <= REG_POINTS_SMALL) == (MX == REG_POINTS_SMALL);
-        const int c = mine ? (kd >> 8) & 0xffff : NONE;
+        const int kd = A.code[kb + k];
+        const bool mine = kd != 0 && (regular_points(kd) <= REG_POINTS_SMALL) == (MX == REG_POINTS_SMALL);
+        const int c = mine ? kd : NONE;
         code[k] = (unsigned short)c;
         next = min(next, c);
     }
@@ -334,7 +336,7 @@ __global__ __launch_bounds__(64, 2) void near_regular(NearArgs A, int e0) {
             const int nb = min(nbmax, nsrc - s0), je = nb * ny4;
             __syncthreads();   // the batch before is read
             if (lane < nb) {
-                const int f = A.pair_f[kb + list[s0 + lane]];
+                const int f = src[list[s0 + lane]];
                 lsrc[lane] = f;
                 lslot[lane] = stage_slot(A.slots, tl, f);
             }
@@ -469,9 +471,8 @@ __global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 && G == 2 ? 2 : 1) vo
     double2* red = &Tb[0][0][0];              // [NW][NL][NL] after the loop
     static_assert(sizeof(double2) * NW * NL * NL <= sizeof(Tb), "the waves' sums fit");
 
-    const int64_t item = blockIdx.x;
-    const int kp = A.touch[item].x;
-    const int kind = A.pair_kind[kp];
+    const NearTouch pair = A.touch[blockIdx.x];
+    const int kind = pair.kind;
     const int cls = kind & 15;
     const int ri = cls == 4 ? 2 : cls == 2 ? 1 : 0;
     const double* rule = A.rule[ri];
@@ -480,7 +481,7 @@ __global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 && G == 2 ? 2 : 1) vo
     const double* gw = gx + NGMAX;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, g = lane >> 4;
     const int code[2] = {(kind >> 16) & 7, (kind >> 20) & 7};
-    const ElemRef R[2] = {elem_ref(A.bez, A.pg, A.nel1, A.touch[item].y), elem_ref(A.bez, A.pg, A.nel1, A.pair_f[kp])};
+    const ElemRef R[2] = {elem_ref(A.bez, A.pg, A.nel1, pair.e), elem_ref(A.bez, A.pg, A.nel1, pair.f)};
 
     // canonical nets and extraction rows (dim 1 = u unless swapped; flips reverse)
     for (int t = tid; t < 2 * G1 * G1 * 4; t += NEAR_THREADS) {
@@ -731,9 +732,8 @@ __global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 && G == 2 ? 2 : 1) vo
             s.x += A.cm.x * m;
             s.y += A.cm.y * m;
         }
-        const int e = A.touch[item].y;
-        const int slot = stage_slot(A.slots, leaf_of(A.slots, e), A.pair_f[kp]);
-        A.stage[stage_row(A.slots, e, A.slot0, NL, oa) + int64_t(slot) * NL + ob] = s;
+        const int slot = stage_slot(A.slots, leaf_of(A.slots, pair.e), pair.f);
+        A.stage[stage_row(A.slots, pair.e, A.slot0, NL, oa) + int64_t(slot) * NL + ob] = s;
     }
 }
 
@@ -751,6 +751,7 @@ __global__ __launch_bounds__(NEAR_THREADS, !HARD && P <= 2 && G == 2 ? 2 : 1) vo
 // --------------------------------------------------------------------------
 struct CsrArgs {
     const int64_t* row_ptr;
+    const int64_t* row_coff;     // first entry of the row's column list in col
     const int* col;
     double2* val;
     NearSlots slots;
@@ -768,11 +769,12 @@ __global__ __launch_bounds__(256) void near_gather_csr(CsrArgs A) {
     constexpr int P1 = P + 1, NL = P1 * P1;
     const int64_t row = A.row0 + blockIdx.x;
     const int64_t beg = A.row_ptr[row], end = A.row_ptr[row + 1];
+    const int* col = A.col + A.row_coff[row] - beg;
     const int kk = A.k * A.k, d = A.slots.d, s1 = (1 << d) - 1, n1 = A.nel1 - 1;
     const int r0 = A.s0_ptr ? A.s0_ptr[row] : int(row);
     const int r1 = A.s0_ptr ? A.s0_ptr[row + 1] : int(row) + 1;
     for (int64_t idx = beg + threadIdx.x; idx < end; idx += blockDim.x) {
-        const int colv = A.col[idx];
+        const int colv = col[idx];
         const int c0 = A.s0_ptr ? A.s0_ptr[colv] : colv;
         const int c1 = A.s0_ptr ? A.s0_ptr[colv + 1] : colv + 1;
         double2 acc = make_double2(0, 0);
@@ -937,8 +939,11 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
     const int64_t npairs = op->near_ptr[E];
     size_t* acct = &op->dev_bytes;
     igb_status st;
-    DevBuf d_kind, d_gl, d_rules[3], d_touch, d_stage;
-    if ((st = upload(d_kind, op->near_kind.data(), op->near_kind.size(), nullptr))) return st;
+    DevBuf d_code, d_leaf_src, d_leaf_src_ptr, d_gl, d_rules[3], d_touch, d_stage;
+    if ((st = upload(d_code, op->near_code.data(), op->near_code.size(), nullptr)) ||
+        (st = upload(d_leaf_src, op->leaf_src.data(), op->leaf_src.size(), nullptr)) ||
+        (st = upload(d_leaf_src_ptr, op->leaf_src_ptr.data(), op->leaf_src_ptr.size(), nullptr)))
+        return st;
     std::vector<double> gl = gauss_table();
     if ((st = upload(d_gl, gl.data(), gl.size(), nullptr))) return st;
     const int raise = op->prm.quad_extra + kd_boost(op->kd_elem) + aspect_boost(op->aspect_max);
@@ -953,9 +958,7 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
         A.rule_ord[c] = ord[c];
     }
     if ((st = upload(op->d_near_ptr, op->near_ptr.data(), op->near_ptr.size(), acct))) return st;
-    if ((st = upload(op->d_near_src, op->near_src.data(), op->near_src.size(), acct))) return st;
     if ((st = upload(op->d_rowptr, op->row_ptr.data(), op->row_ptr.size(), acct))) return st;
-    if ((st = upload(op->d_col, op->col.data(), op->col.size(), acct))) return st;
     if ((st = upload(op->d_dcol, op->near_dcol.data(), op->near_dcol.size(), acct))) return st;
     if ((st = upload(op->d_row_coff, op->row_coff.data(), op->row_coff.size(), acct))) return st;
     if ((st = upload(op->d_near_wgs, op->near_wgs.data(), op->near_wgs.size(), acct))) return st;
@@ -979,8 +982,9 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
     A.C1 = g->d_C1.as<double>();
     A.gl = d_gl.as<double>();
     A.slots = slots;
-    A.pair_f = op->d_near_src.as<int>();
-    A.pair_kind = d_kind.as<int>();
+    A.leaf_src = d_leaf_src.as<int>();
+    A.leaf_src_ptr = d_leaf_src_ptr.as<int64_t>();
+    A.code = d_code.as<unsigned short>();
     A.nel1 = g->nel1;
     A.kappa = op->kappa;
     A.eta = op->eta;
@@ -1016,7 +1020,7 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
         IGB_HIP(hipGetLastError());
         // touching pairs (the nets are read at the largest geometry degree, 2 or 3)
         const int64_t t0 = op->near_touch_ptr[e0], nt = op->near_touch_ptr[e1] - t0;
-        A.touch = d_touch.as<int2>() + t0;
+        A.touch = d_touch.as<NearTouch>() + t0;
         if (nt > 0 && geo_deg <= 2)
             hipLaunchKernelGGL((near_singular<P, HARD, 2>), dim3(unsigned(nt)), dim3(NEAR_THREADS), 0, s, A);
         else if (nt > 0)
@@ -1039,7 +1043,8 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
         }
         CsrArgs C{};
         C.row_ptr = op->d_rowptr.as<int64_t>();
-        C.col = op->d_col.as<int>();
+        C.row_coff = op->d_row_coff.as<int64_t>();
+        C.col = op->d_dcol.as<int>();
         C.val = op->d_val.as<double2>();
         C.slots = slots;
         C.stage = d_stage.as<double2>();

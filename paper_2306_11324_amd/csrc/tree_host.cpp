@@ -47,6 +47,12 @@ int d4_code(int c0, int c1 /* -1: unused */) {
 
 }  // namespace
 
+// leaf (local index) holding element e
+int64_t leaf_of_element(const igb_op_s* op, int64_t e) {
+    const int64_t nel1 = op->geom->nel1, n2 = nel1 * nel1;
+    return clu_local(0, op->L, int(e / n2), int(e % n2 % nel1) >> op->d, int(e % n2 / nel1) >> op->d);
+}
+
 // Splits every target's far list (pairs sorted by target within a level) into
 // chunks of at most `ch` consecutive pairs.
 static void build_chunks(igb_op op, int ch, M2LChunks& out) {
@@ -202,23 +208,21 @@ igb_status tree_build(igb_op op) {
     const int s = 1 << op->d;   // elements per leaf side
     const int nl = 1 << L;
     op->near_ptr.assign(E + 1, 0);
-    for (auto& v : near_leaf) std::sort(v.begin(), v.end());
-    for (int64_t e = 0; e < E; ++e) {
-        int j = int(e / (int64_t(nel1) * nel1));
-        int rem = int(e % (int64_t(nel1) * nel1));
-        int ey = rem / nel1, ex = rem % nel1;
-        int leaf = int(clu_local(np, L, j, ex / s, ey / s));
-        op->near_ptr[e + 1] = op->near_ptr[e] + int64_t(near_leaf[leaf].size()) * s * s;
+    const int64_t nleaf = int64_t(near_leaf.size());
+    op->leaf_src_ptr.assign(nleaf + 1, 0);
+    for (int64_t lf = 0; lf < nleaf; ++lf) {
+        std::sort(near_leaf[lf].begin(), near_leaf[lf].end());
+        op->leaf_src_ptr[lf + 1] = op->leaf_src_ptr[lf] + int64_t(near_leaf[lf].size()) * s * s;
     }
-    op->near_src.resize(op->near_ptr[E]);
-    parallel_for(E, 256, [&](int64_t e) {
-        int j = int(e / (int64_t(nel1) * nel1));
-        int rem = int(e % (int64_t(nel1) * nel1));
-        int ey = rem / nel1, ex = rem % nel1;
-        int leaf = int(clu_local(np, L, j, ex / s, ey / s));
-        int* src = op->near_src.data() + op->near_ptr[e];
+    for (int64_t e = 0; e < E; ++e) {
+        const int64_t lf = leaf_of_element(op, e);
+        op->near_ptr[e + 1] = op->near_ptr[e] + op->leaf_src_ptr[lf + 1] - op->leaf_src_ptr[lf];
+    }
+    op->leaf_src.resize(op->leaf_src_ptr[nleaf]);
+    parallel_for(nleaf, 1, [&](int64_t lf) {
+        int* src = op->leaf_src.data() + op->leaf_src_ptr[lf];
         int64_t c = 0;
-        for (int sl : near_leaf[leaf]) {
+        for (int sl : near_leaf[lf]) {
             int sj = sl >> (2 * L), sr = sl & ((1 << (2 * L)) - 1);
             int scy = sr >> L, scx = sr & (nl - 1);
             for (int fy = scy * s; fy < (scy + 1) * s; ++fy)
@@ -285,23 +289,28 @@ igb_status near_classify(igb_op op) {
     for (int64_t e = 0; e < E; ++e)
         op->aspect_max = std::max(op->aspect_max, std::max(side[2 * e], side[2 * e + 1]) /
                                                       std::max(1e-300, std::min(side[2 * e], side[2 * e + 1])));
-    op->near_kind.resize(op->near_src.size());
-    std::vector<std::vector<int2>> touch(E);   // touching pairs of each element
+    op->near_code.resize(op->near_ptr[E]);
+    std::vector<std::vector<NearTouch>> touch(E);   // touching pairs of each element
     std::vector<int> points(E, 0);             // most points of its regular rules
     std::atomic<int> bad_shared{-1};   // first inconsistency found: shared corner count (or 2)
     parallel_for(E, 64, [&](int64_t e) {
+        const int* src = op->leaf_src.data() + op->leaf_src_ptr[leaf_of_element(op, e)];
         for (int64_t k = op->near_ptr[e]; k < op->near_ptr[e + 1]; ++k) {
-            const int64_t f = op->near_src[k];
+            const int64_t f = src[k - op->near_ptr[e]];
+            double d2 = 0;
+            for (int c = 0; c < 3; ++c) d2 += (ctr[3 * e + c] - ctr[3 * f + c]) * (ctr[3 * e + c] - ctr[3 * f + c]);
             int shared = 0, ce[4], cf[4];
-            for (int a = 0; a < 4; ++a)
-                for (int b = 0; b < 4; ++b)
-                    if (g->vert[4 * e + a] == g->vert[4 * f + b]) {
-                        ce[shared] = a;
-                        cf[shared] = b;
-                        ++shared;
-                    }
+            // (elements that share a corner lie within their boxes' diagonals of each other)
+            const double reach = 1.0001 * (diag[e] + diag[f]);
+            if (!(d2 > reach * reach))
+                for (int a = 0; a < 4; ++a)
+                    for (int b = 0; b < 4; ++b)
+                        if (g->vert[4 * e + a] == g->vert[4 * f + b]) {
+                            ce[shared] = a;
+                            cf[shared] = b;
+                            ++shared;
+                        }
             int kind = 0;
-            if (shared > 0) touch[e].push_back(make_int2(int(k), int(e)));
             if (e == f) {
                 kind = 4;
             } else if (shared == 2) {
@@ -315,8 +324,6 @@ igb_status near_classify(igb_op op) {
                 int te = d4_code(ce[0], -1), tf = d4_code(cf[0], -1);
                 kind = 1 | (te << 16) | (tf << 20);
             } else if (shared == 0) {
-                double d2 = 0;
-                for (int c = 0; c < 3; ++c) d2 += (ctr[3 * e + c] - ctr[3 * f + c]) * (ctr[3 * e + c] - ctr[3 * f + c]);
                 const double dmax = std::max(diag[e], diag[f]);
                 const double dist = std::sqrt(d2);
                 // raised with kappa * diameter (oscillation of e^{i kappa r} across the pair)
@@ -343,7 +350,8 @@ igb_status near_classify(igb_op op) {
                 int expect = -1;
                 bad_shared.compare_exchange_strong(expect, shared);
             }
-            op->near_kind[k] = kind;
+            op->near_code[k] = shared > 0 ? 0 : (unsigned short)(kind >> 8);
+            if (shared > 0) touch[e].push_back(NearTouch{k, int(e), int(f), kind, 0});
         }
     });
     if (bad_shared.load() == 2) {
@@ -358,7 +366,7 @@ igb_status near_classify(igb_op op) {
     op->near_touch_ptr.assign(E + 1, 0);
     for (int64_t e = 0; e < E; ++e) op->near_touch_ptr[e + 1] = op->near_touch_ptr[e] + int64_t(touch[e].size());
     op->near_touch.reserve(op->near_touch_ptr[E]);
-    for (const std::vector<int2>& v : touch) op->near_touch.insert(op->near_touch.end(), v.begin(), v.end());
+    for (const std::vector<NearTouch>& v : touch) op->near_touch.insert(op->near_touch.end(), v.begin(), v.end());
     return IGB_OK;
 }
 
@@ -424,31 +432,6 @@ igb_status near_pattern(igb_op op) {
         }
     };
 
-    op->row_ptr.assign(N + 1, 0);
-    parallel_for(N, 256, [&](int64_t r) {
-        thread_local std::vector<int> leaves, buf, tmp;
-        row_leaves(r, leaves);
-        if (leaves.size() == 1) {
-            op->row_ptr[r + 1] = int64_t(leaf_cols[leaves[0]].size());
-        } else {
-            merge(leaves, buf, tmp);
-            op->row_ptr[r + 1] = int64_t(buf.size());
-        }
-    });
-    for (int64_t r = 0; r < N; ++r) op->row_ptr[r + 1] += op->row_ptr[r];
-    op->nnz = op->row_ptr[N];
-    op->col.resize(op->nnz);
-    parallel_for(N, 256, [&](int64_t r) {
-        thread_local std::vector<int> leaves, buf, tmp;
-        row_leaves(r, leaves);
-        const std::vector<int>* src = &leaf_cols[leaves[0]];
-        if (leaves.size() > 1) {
-            merge(leaves, buf, tmp);
-            src = &buf;
-        }
-        std::copy(src->begin(), src->end(), op->col.begin() + op->row_ptr[r]);
-    });
-
     // rows with the same leaves (hence the same column list) form
     // groups, taken in order of their first row; up to 16 rows of neighbouring
     // groups share a tile whose columns are the union of theirs, as long as the
@@ -465,35 +448,50 @@ igb_status near_pattern(igb_op op) {
             groups[leaves].push_back(int(r));
         }
     }
-    std::vector<const std::vector<int>*> order;
-    for (const auto& kv : groups) order.push_back(&kv.second);
+    using Group = std::pair<const std::vector<int>, std::vector<int>>;   // leaves, rows
+    std::vector<const Group*> order;
+    for (const Group& kv : groups) order.push_back(&kv);
     std::sort(order.begin(), order.end(),
-              [](const std::vector<int>* a, const std::vector<int>* b) { return a->front() < b->front(); });
+              [](const Group* a, const Group* b) { return a->second.front() < b->second.front(); });
     // each group's column list once; every row points at its group's list
-    op->near_dcol.clear();
+    const int64_t ng = int64_t(order.size());
+    std::vector<int64_t> list_off(ng + 1, 0);
+    std::vector<std::vector<int>> lists(ng);
+    parallel_for(ng, 4, [&](int64_t i) {
+        thread_local std::vector<int> tmp;
+        merge(order[i]->first, lists[i], tmp);
+    });
+    for (int64_t i = 0; i < ng; ++i) list_off[i + 1] = list_off[i] + int64_t(lists[i].size());
+    op->near_dcol.resize(list_off[ng]);
+    parallel_for(ng, 4, [&](int64_t i) {
+        std::copy(lists[i].begin(), lists[i].end(), op->near_dcol.begin() + list_off[i]);
+        std::vector<int>().swap(lists[i]);
+    });
+    op->row_ptr.assign(N + 1, 0);
     op->row_coff.assign(N, 0);
     op->near_wgs.clear();
     op->near_grp_rows.clear();
     op->near_list_max = 0;
-    for (const std::vector<int>* g : order) {
-        const int64_t off = int64_t(op->near_dcol.size());
-        const int len = int(op->row_ptr[g->front() + 1] - op->row_ptr[g->front()]);
-        op->near_dcol.insert(op->near_dcol.end(), op->col.begin() + op->row_ptr[g->front()],
-                             op->col.begin() + op->row_ptr[g->front() + 1]);
+    for (int64_t i = 0; i < ng; ++i) {
+        const std::vector<int>& rows = order[i]->second;
+        const int len = int(list_off[i + 1] - list_off[i]);
         op->near_list_max = std::max(op->near_list_max, len);
-        for (size_t i = 0; i < g->size(); i += NEAR_GROUP_ROWS) {
+        for (size_t j = 0; j < rows.size(); j += NEAR_GROUP_ROWS) {
             NearGroupWG w{};
-            w.list_off = off;
+            w.list_off = list_off[i];
             w.list_len = len;
-            w.row0 = int(op->near_grp_rows.size() + i);
-            w.nrows = int(std::min<size_t>(NEAR_GROUP_ROWS, g->size() - i));
+            w.row0 = int(op->near_grp_rows.size() + j);
+            w.nrows = int(std::min<size_t>(NEAR_GROUP_ROWS, rows.size() - j));
             op->near_wgs.push_back(w);
         }
-        for (int r : *g) {
-            op->row_coff[r] = off;
+        for (int r : rows) {
+            op->row_ptr[r + 1] = len;
+            op->row_coff[r] = list_off[i];
             op->near_grp_rows.push_back(r);
         }
     }
+    for (int64_t r = 0; r < N; ++r) op->row_ptr[r + 1] += op->row_ptr[r];
+    op->nnz = op->row_ptr[N];
     {
         // bf16 operators use the tiles with fp32 values (inner matvecs), fp64
         // operators with fp64 values (blocks of >= 16 columns); built for every
@@ -515,9 +513,10 @@ igb_status near_pattern(igb_op op) {
             cols.clear();
             longest = 0;
         };
-        for (const std::vector<int>* g : order) {
-            const int* c0 = op->col.data() + op->row_ptr[g->front()];
-            const size_t nc = size_t(op->row_ptr[g->front() + 1] - op->row_ptr[g->front()]);
+        for (int64_t gi = 0; gi < ng; ++gi) {
+            const std::vector<int>* g = &order[gi]->second;
+            const int* c0 = op->near_dcol.data() + list_off[gi];
+            const size_t nc = size_t(list_off[gi + 1] - list_off[gi]);
             for (size_t i0 = 0; i0 < g->size(); i0 += NEAR_TILE_ROWS) {
                 const size_t nr = std::min<size_t>(NEAR_TILE_ROWS, g->size() - i0);
                 if (!rows.empty()) {
