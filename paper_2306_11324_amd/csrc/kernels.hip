@@ -641,6 +641,23 @@ struct MfmaF64 {
         return make_uint4(x.z, x.w, x.x, x.y);
     }
 };
+// the complex products of one A fragment with NC column tiles: the real parts of
+// A first, then the imaginary ones, so that no product waits for the one before it
+// (each sum as MfmaF64::step forms it)
+template <int NC>
+__device__ __forceinline__ void step64(uint4 a, const uint4 (&x)[NC], f64x4 (&acc)[NC][2]) {
+    const double ar = MfmaF64::lo(a), ai = MfmaF64::hi(a);
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+        acc[j][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, MfmaF64::lo(x[j]), acc[j][0], 0, 0, 0);
+        acc[j][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, MfmaF64::hi(x[j]), acc[j][1], 0, 0, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+        acc[j][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, -MfmaF64::hi(x[j]), acc[j][0], 0, 0, 0);
+        acc[j][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, MfmaF64::lo(x[j]), acc[j][1], 0, 0, 0);
+    }
+}
 template <class PT> __device__ __forceinline__ PT make_pt(double re, double im);
 template <> __device__ __forceinline__ float2 make_pt<float2>(double re, double im) {
     return make_float2(float(re), float(im));
@@ -821,27 +838,37 @@ __global__ __launch_bounds__(512 / RPW) void m2l_mfma(const typename OPS::LT* __
 // cache serves once.  Each column sums the chunk's pairs and k blocks in
 // order in its own accumulator, so its result does not depend on NC or on the
 // other columns.  KU steps are loaded per group, two groups in flight.
+struct M2l64Args {
+    const double2* coup;
+    int nkc;
+    const double2* xlo;
+    int kbp, ncolp;
+    const int* far_src_g;
+    const int64_t* chunk_pair;
+    const int* chunk_len;
+    int64_t nchunk;
+    int ncg, nq, ncol;   // ncg: groups of NC column tiles
+    double2* part;
+};
 template <int NC, int KU>
-__global__ __launch_bounds__(512) void m2l_mfma64_soft(const double2* __restrict__ coup, int nkc,
-                                                       const double2* __restrict__ xlo, int kbp, int ncolp,
-                                                       const int* __restrict__ far_src_g,
-                                                       const int64_t* __restrict__ chunk_pair,
-                                                       const int* __restrict__ chunk_len, int64_t nchunk, int nq,
-                                                       int ncol, double2* __restrict__ part) {
+__device__ __forceinline__ void m2l_wave64(const M2l64Args& M, int64_t ch, int cg, int rt) {
     using OPS = MfmaF64;
     constexpr int KB = OPS::KB;
-    const int64_t ch = xcd_chunk(blockIdx.x, nchunk);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nkc = M.nkc, kbp = M.kbp, ncolp = M.ncolp, nq = M.nq, ncol = M.ncol;
+    const double2* __restrict__ coup = M.coup;
+    const double2* __restrict__ xlo = M.xlo;
+    double2* __restrict__ part = M.part;
+    const int lane = threadIdx.x & 63;
     const int li = lane & 15, g = lane >> 4;
     // A row of this lane; rows past nq re-read the last row (outputs not stored)
-    const int a = min(wave * 16 + li, nq - 1);
-    const int c0 = blockIdx.y * 16 * NC;
-    const int64_t p0 = chunk_pair[ch];
-    const int len = chunk_len[ch];
+    const int a = min(rt * 16 + li, nq - 1);
+    const int c0 = cg * 16 * NC;
+    const int64_t p0 = M.chunk_pair[ch];
+    const int len = M.chunk_len[ch];
     const int nkb = (nq + KB - 1) / KB;
     const int64_t tile_el = int64_t(nkc) * nq;
     const int nstep = len * nkb;
-    const int srcv = lane < len ? far_src_g[p0 + lane] : 0;
+    const int srcv = lane < len ? M.far_src_g[p0 + lane] : 0;
     const int64_t vstride = int64_t(ncolp) * kbp;
     const unsigned offB = unsigned(g * ncolp + c0 + li);
     OPS::ACC acc[NC][2];
@@ -869,11 +896,7 @@ __global__ __launch_bounds__(512) void m2l_mfma64_soft(const double2* __restrict
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
             if (j0 + u >= nstep) break;
-#pragma unroll
-            for (int j = 0; j < NC; ++j) {
-                acc[j][0] = OPS::step(A[u], OPS::re_part(X[u][j]), acc[j][0]);
-                acc[j][1] = OPS::step(A[u], OPS::im_part(X[u][j]), acc[j][1]);
-            }
+            step64<NC>(A[u], X[u], acc);
         }
     };
     uint4 A0[KU], X0[KU][NC], A1[KU], X1[KU][NC];
@@ -890,10 +913,17 @@ __global__ __launch_bounds__(512) void m2l_mfma64_soft(const double2* __restrict
         if (c >= ncol) continue;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int ar = wave * 16 + OPS::orow(g, r);
+            const int ar = rt * 16 + OPS::orow(g, r);
             if (ar < nq) part[(ch * nq + ar) * ncol + c] = make_double2(acc[j][0][r], acc[j][1][r]);
         }
     }
+}
+
+template <int NC, int KU>
+__global__ __launch_bounds__(512) void m2l_mfma64_soft(M2l64Args M) {
+    // (the column groups of a chunk on neighbouring workgroups: they read the same tiles)
+    const int64_t wg = xcd_chunk(blockIdx.x, gridDim.x), ch = wg / M.ncg;
+    m2l_wave64<NC, KU>(M, ch, int(wg - ch * M.ncg), threadIdx.x >> 6);
 }
 
 // Sound-soft coupling on the matrix cores with B reuse: the 4 waves of a
@@ -2105,105 +2135,144 @@ __global__ void columns_t64(const double2* __restrict__ x, int64_t nrows, int nc
 // column results (which differ from the one-column CSR product by rounding:
 // another summation order).
 constexpr int NEAR64_WAVES = 8;
+struct Near64Args {
+    const NearTile* tiles;
+    int64_t ntile;
+    int ncg;   // groups of NC column tiles
+    const int* tcol;
+    const double2* vt;
+    const double2* xt;
+    int64_t nrows;
+    int ncol;
+    double2* y;
+};
+constexpr int NEAR64_PASS = 2;   // column tiles whose sums meet in LDS at a time
 template <int NC>
-__global__ __launch_bounds__(64 * NEAR64_WAVES) void near_tiles_mfma64(
-    const NearTile* __restrict__ tiles, int64_t ntile, const int* __restrict__ tcol, const double2* __restrict__ vt,
-    const double2* __restrict__ xt, int64_t nrows, FarLeaves F,
-    const int* __restrict__ s0_ptr, const int* __restrict__ s0_reps, int use_near, int ncol,
-    double2* __restrict__ y) {
-    constexpr int NW = NEAR64_WAVES, KB = MfmaF64::KB;
-    __shared__ f64x4 red[NW - 1][2][64];
-    __shared__ int cidx[NEAR_TILE_CHUNK];
-    const int64_t t = xcd_chunk(blockIdx.x, ntile);
+struct Near64Lds {
+    static constexpr int JP = NC < NEAR64_PASS ? NC : NEAR64_PASS;
+    double2 sum[NEAR64_WAVES * JP * 4][64];
+};
+template <int NC>
+__device__ __forceinline__ void near_tile64(const Near64Args& A, int64_t wg, Near64Lds<NC>& lds) {
+    constexpr int NW = NEAR64_WAVES, KB = MfmaF64::KB, JP = Near64Lds<NC>::JP;
+    double2 (*red)[64] = lds.sum;
+    int* const cidx = reinterpret_cast<int*>(lds.sum);   // (before the sums meet there)
+    static_assert(sizeof(lds) >= NEAR_TILE_CHUNK * sizeof(int), "column indices and sums share the LDS");
+    const int64_t t = wg / A.ncg, nrows = A.nrows;
+    const int cg = int(wg - t * A.ncg), ncol = A.ncol;
+    const double2* __restrict__ xt = A.xt;
+    const double2* __restrict__ vt = A.vt;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, g = lane >> 4;
-    const NearTile& T = tiles[t];
+    const NearTile& T = A.tiles[t];
     const int nr = T.nrows, nc = T.ncols;
     const int nkb = (nc + KB - 1) / KB;
-    // column tile j of this workgroup: block (NC blockIdx.y + j) of the
-    // transposed columns [block][row][16]
-    const double2* xb = xt + int64_t(blockIdx.y) * NC * nrows * 16 + li;
-    const int* cl = tcol + T.col_off;
+    // column tile j of this workgroup: block (NC cg + j) of the transposed
+    // columns [block][row][16]
+    const double2* xb = xt + int64_t(cg) * NC * nrows * 16 + li;
+    const int* __restrict__ cl = A.tcol + T.col_off;
     const int ra = li < nr ? li : 0;
     const double2* va = vt + T.val_off + ra * KB + g;
     const int64_t kbstride = int64_t(nr) * KB;
     f64x4 acc[NC][2];
 #pragma unroll
     for (int j = 0; j < NC; ++j) acc[j][0] = acc[j][1] = f64x4{0.0, 0.0, 0.0, 0.0};
-    auto load = [&](int kb, int kl, uint4& A, uint4 (&X)[NC]) {
-        A = *reinterpret_cast<const uint4*>(va + kb * kbstride);
+    auto load = [&](int kb, int kl, uint4& V, uint4 (&X)[NC]) {
+        V = *reinterpret_cast<const uint4*>(va + kb * kbstride);
         const int64_t o = int64_t(cidx[kl + g]) * 16;
 #pragma unroll
         for (int j = 0; j < NC; ++j) X[j] = *reinterpret_cast<const uint4*>(xb + int64_t(j) * nrows * 16 + o);
     };
-    auto compute = [&](const uint4& A, const uint4 (&X)[NC]) {
-#pragma unroll
-        for (int j = 0; j < NC; ++j) {
-            acc[j][0] = MfmaF64::step(A, MfmaF64::re_part(X[j]), acc[j][0]);
-            acc[j][1] = MfmaF64::step(A, MfmaF64::im_part(X[j]), acc[j][1]);
+    auto compute = [&](const uint4& V, const uint4 (&X)[NC]) { step64<NC>(V, X, acc); };
+    // chunks of columns: indices to LDS (past the list: its last column, whose
+    // tile values are zero there), then each wave's k blocks kb = wave mod NW
+    // in increasing order, two loads in flight
+    for (int k0 = 0; k0 < nkb * KB; k0 += NEAR_TILE_CHUNK) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < NEAR_TILE_CHUNK; i += blockDim.x) cidx[i] = cl[min(k0 + i, nc - 1)];
+        __syncthreads();
+        const int kb0 = k0 / KB, kb1 = min(nkb, kb0 + NEAR_TILE_CHUNK / KB);
+        int kb = kb0 + wave;
+        for (; kb + NW < kb1; kb += 2 * NW) {
+            uint4 A0, X0[NC], A1, X1[NC];
+            load(kb, (kb - kb0) * KB, A0, X0);
+            load(kb + NW, (kb + NW - kb0) * KB, A1, X1);
+            compute(A0, X0);
+            compute(A1, X1);
         }
-    };
-    if (use_near) {
-        // chunks of columns: indices to LDS (past the list: its last column, whose
-        // tile values are zero there), then each wave's k blocks kb = wave mod NW
-        // in increasing order, two loads in flight
-        for (int k0 = 0; k0 < nkb * KB; k0 += NEAR_TILE_CHUNK) {
-            __syncthreads();
-            for (int i = threadIdx.x; i < NEAR_TILE_CHUNK; i += blockDim.x) cidx[i] = cl[min(k0 + i, nc - 1)];
-            __syncthreads();
-            const int kb0 = k0 / KB, kb1 = min(nkb, kb0 + NEAR_TILE_CHUNK / KB);
-            int kb = kb0 + wave;
-            for (; kb + NW < kb1; kb += 2 * NW) {
-                uint4 A0, X0[NC], A1, X1[NC];
-                load(kb, (kb - kb0) * KB, A0, X0);
-                load(kb + NW, (kb + NW - kb0) * KB, A1, X1);
-                compute(A0, X0);
-                compute(A1, X1);
-            }
-            if (kb < kb1) {
-                uint4 A0, X0[NC];
-                load(kb, (kb - kb0) * KB, A0, X0);
-                compute(A0, X0);
-            }
+        if (kb < kb1) {
+            uint4 A0, X0[NC];
+            load(kb, (kb - kb0) * KB, A0, X0);
+            compute(A0, X0);
         }
     }
-    // the waves' sums meet in LDS in wave order, one column tile at a time
+    // the waves' sums meet in LDS, JP column tiles at a time; each wave then adds
+    // one row register of one of them over the waves in wave order (one wave for
+    // all rows, with the others idle, took a tenth of the kernel)
 #pragma unroll
-    for (int j = 0; j < NC; ++j) {
+    for (int j0 = 0; j0 < NC; j0 += JP) {
         __syncthreads();
-        if (wave > 0) {
-            red[wave - 1][0][lane] = acc[j][0];
-            red[wave - 1][1][lane] = acc[j][1];
-        }
+#pragma unroll
+        for (int j = 0; j < JP; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                red[(wave * JP + j) * 4 + r][lane] = make_double2(acc[j0 + j][0][r], acc[j0 + j][1][r]);
         __syncthreads();
-        if (wave == 0) {
-            f64x4 s0 = acc[j][0], s1 = acc[j][1];
+        for (int u = wave; u < 4 * JP; u += NW) {
+            const int r = u & 3, i = MfmaF64::orow(g, r), c = (cg * NC + j0 + (u >> 2)) * 16 + li;
+            if (i >= nr || c >= ncol) continue;
+            double2 a = red[u][lane];
 #pragma unroll
-            for (int w = 0; w < NW - 1; ++w) {
-                s0 += red[w][0][lane];
-                s1 += red[w][1][lane];
-            }
-            const int c = (blockIdx.y * NC + j) * 16 + li;
-            if (c < ncol) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = MfmaF64::orow(g, r);
-                    if (i >= nr) continue;
-                    const int row = T.rows[i];
-                    double2 a = make_double2(s0[r], s1[r]);
-                    if (F.leafbuf) {
-                        if (s0_ptr) {
-                            for (int q = s0_ptr[row]; q < s0_ptr[row + 1]; ++q)
-                                a = cadd(a, far_value(F, s0_reps[q], c));
-                        } else {
-                            a = cadd(a, far_value(F, row, c));
-                        }
-                    }
-                    y[int64_t(c) * nrows + row] = a;
-                }
-            }
+            for (int w = 1; w < NW; ++w) a = cadd(a, red[w * JP * 4 + u][lane]);
+            A.y[int64_t(c) * nrows + T.rows[i]] = a;
         }
     }
+}
+
+template <int NC>
+__global__ __launch_bounds__(64 * NEAR64_WAVES) void near_tiles_mfma64(Near64Args A) {
+    __shared__ Near64Lds<NC> lds;
+    near_tile64<NC>(A, xcd_chunk(blockIdx.x, gridDim.x), lds);
+}
+
+// Near field and coupling of a sound-soft fp64 block in one launch: neither
+// needs the other (both need the source vectors only), and each alone leaves a
+// fifth of the CU time idle, as a near workgroup takes up to half of the
+// kernel's time.  The near workgroups come first, the coupling's waves (a row
+// tile of a chunk's NM column tiles each) fill what they leave.  Level-5 sphere,
+// leaf depth 3, 64 columns, of which the matrix cores' share is 293 us:
+// JOINT0 us in two launches, JOINT1 in one.
+template <int NN, int NM>
+__global__ __launch_bounds__(64 * NEAR64_WAVES, 4) void near_far_mfma64(Near64Args A, int near_wgs8, M2l64Args M) {
+    __shared__ Near64Lds<NN> lds;
+    if (int(blockIdx.x) < near_wgs8) {
+        const int64_t n = A.ntile * A.ncg;
+        if (int64_t(blockIdx.x) < n) near_tile64<NN>(A, xcd_chunk(blockIdx.x, n), lds);
+        return;
+    }
+    const int nrt = (M.nq + 15) / 16;
+    const int64_t task = xcd_chunk(blockIdx.x - near_wgs8, gridDim.x - near_wgs8) * NEAR64_WAVES + (threadIdx.x >> 6);
+    const int64_t item = task / nrt, ch = item / M.ncg;
+    if (ch < M.nchunk) m2l_wave64<NM, NM == 1 ? 4 : 1>(M, ch, int(item - ch * M.ncg), int(task - item * nrt));
+}
+
+// adds the far values to the near products (near = 0: to zero), in the order of
+// the near kernels that gather them themselves
+__global__ void add_far(FarLeaves F, const int* __restrict__ s0_ptr, const int* __restrict__ s0_reps, int near,
+                        int64_t nrows, int ncol, double2* __restrict__ y) {
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= nrows * ncol) return;
+    const int c = int(i / nrows);
+    const int64_t row = i - c * nrows;
+    double2 a = near ? y[i] : make_double2(0.0, 0.0);
+    if (F.leafbuf) {
+        if (s0_ptr) {
+            for (int q = s0_ptr[row]; q < s0_ptr[row + 1]; ++q) a = cadd(a, far_value(F, s0_reps[q], c));
+        } else {
+            a = cadd(a, far_value(F, row, c));
+        }
+    }
+    y[i] = a;
 }
 
 // --------------------------------------------------------------------------
@@ -3264,8 +3333,33 @@ static void launch_m2l_lo_t(igb_op op, const MatvecWork& W, const double2* xh, i
     (void)timer_mark(op, 0, s);
 }
 
-// fp64 sound-soft blocks of >= 16 columns: up to 4 column tiles per wave
-static void launch_m2l_f64_soft(igb_op op, const MatvecWork& W, const double2* xh, int ncol, hipStream_t s) {
+// near products of a block of ncol columns on the fp64 matrix cores: its columns
+// transposed into 16-wide rows, and the kernel's arguments; returns the column
+// tiles per workgroup (each tile value read serves 16 of them): `most` or 2 or 1
+// such that it divides the column tile count and the grid keeps at least 512
+// workgroups (2 per CU), or the tuned shape; the column results do not depend on it
+static int prepare_near64(igb_op op, const MatvecWork& W, const double2* X, double2* Y, int ncol, int most,
+                          hipStream_t s, Near64Args& A) {
+    const int ncb = (ncol + 15) / 16;
+    const int64_t ntile = int64_t(op->near_tiles.size());
+    hipLaunchKernelGGL(columns_t64, dim3(unsigned((int64_t(ncb) * op->N * 16 + 255) / 256)), dim3(256), 0, s, X, op->N,
+                       ncol, ncb, W.xnear64);
+    int nct = 1;
+    for (int c : {4, 2})
+        if (c <= most && ncb % c == 0 && (c == 4 || ntile * (ncb / c) >= 512)) {
+            nct = c;
+            break;
+        }
+    if (op->tile_near_nct > 0 && ncb % op->tile_near_nct == 0) nct = op->tile_near_nct;   // tuned shape
+    A = Near64Args{op->d_near_tiles.as<NearTile>(), ntile, ncb / nct, op->d_near_tile_cols.as<int>(),
+                   op->d_val64.as<double2>(), W.xnear64, op->N, ncol, Y};
+    return nct;
+}
+
+// fp64 sound-soft blocks of >= 16 columns: up to 4 column tiles per wave; with
+// `near` (and its column tiles per workgroup nn) the near products in the same launch
+static void launch_m2l_f64_soft(igb_op op, const MatvecWork& W, const double2* xh, int ncol, const Near64Args* near,
+                                int nn, hipStream_t s) {
     const M2LChunks& C = op->chunks_mfma;
     const int64_t nchunk = int64_t(C.len.size());
     const int ncolp = (ncol + 15) / 16 * 16, kbp = lo_kbp(op), nq = op->nq;
@@ -3274,50 +3368,58 @@ static void launch_m2l_f64_soft(igb_op op, const MatvecWork& W, const double2* x
     hipLaunchKernelGGL((round_vectors<1, double2>), dim3(unsigned((nv + 255) / 256)), dim3(256), 0, s, xh, int64_t(0),
                        op->d_nodes.as<double>(), op->nclusters, nq, kbp, ncol, ncolp, xlo);
     (void)timer_mark(op, 0, s);
-    if (nchunk > 0) {
-        // NC column tiles per workgroup, NC dividing the padded tile count (the
-        // last workgroup's tiles stay inside the rounded source vectors)
-        // (the widest grouping that keeps at least 512 workgroups, 2 per CU: on
-        // the level-5 sphere the tuner's choice at 32 and 64 columns)
-        const int ntile = ncolp / 16;
-        int nc = 1;
-        for (int c : {4, 2})
-            if (ntile % c == 0 && nchunk * (ntile / c) >= 512) {
-                nc = c;
-                break;
-            }
-        if (op->tile_m2l_nc > 0 && ntile % op->tile_m2l_nc == 0) nc = op->tile_m2l_nc;   // tuned shape
-        const dim3 grid(unsigned(nchunk), unsigned((ntile + nc - 1) / nc)), block(64 * ((nq + 15) / 16));
-        const double2* cp = op->d_coupling.as<double2>();
-        double2* pp = static_cast<double2*>(W.part_lo);
-        const int* fs = op->d_far_src.as<int>();
-        const int64_t* cpair = C.d_pair.as<int64_t>();
-        const int* clen = C.d_len.as<int>();
-        if (nc == 4)
-            hipLaunchKernelGGL((m2l_mfma64_soft<4, 1>), grid, block, 0, s, cp, lo_nkc(op), xlo, kbp, ncolp, fs, cpair,
-                               clen, nchunk, nq, ncol, pp);
-        else if (nc == 2)
-            hipLaunchKernelGGL((m2l_mfma64_soft<2, 2>), grid, block, 0, s, cp, lo_nkc(op), xlo, kbp, ncolp, fs, cpair,
-                               clen, nchunk, nq, ncol, pp);
-        else
-            hipLaunchKernelGGL((m2l_mfma64_soft<1, 4>), grid, block, 0, s, cp, lo_nkc(op), xlo, kbp, ncolp, fs, cpair,
-                               clen, nchunk, nq, ncol, pp);
+    // NC column tiles per wave, NC dividing the padded tile count (the last
+    // wave's tiles stay inside the rounded source vectors): the widest grouping
+    // that keeps at least 512 workgroups, 2 per CU (on the level-5 sphere the
+    // tuner's choice at 32 and 64 columns)
+    const int ntile = ncolp / 16;
+    int nc = 1;
+    for (int c : {4, 2})
+        if (ntile % c == 0 && nchunk * (ntile / c) >= 512) {
+            nc = c;
+            break;
+        }
+    if (op->tile_m2l_nc > 0 && ntile % op->tile_m2l_nc == 0) nc = op->tile_m2l_nc;   // tuned shape
+    const int ncg = ntile / nc, nrt = (nq + 15) / 16;
+    const M2l64Args M{op->d_coupling.as<double2>(), lo_nkc(op), xlo, kbp, ncolp, op->d_far_src.as<int>(),
+                      C.d_pair.as<int64_t>(), C.d_len.as<int>(), nchunk, ncg, nq, ncol,
+                      static_cast<double2*>(W.part_lo)};
+    if (near) {
+        const int wgs8 = int((near->ntile * near->ncg + 7) / 8 * 8);   // (whole rounds of the 8 XCDs)
+        const dim3 grid(unsigned(wgs8 + (nchunk * ncg * nrt + NEAR64_WAVES - 1) / NEAR64_WAVES));
+        auto pick = [&](auto n) {
+            constexpr int NN = decltype(n)::value;
+            return nc == 4 ? near_far_mfma64<NN, 4> : nc == 2 ? near_far_mfma64<NN, 2> : near_far_mfma64<NN, 1>;
+        };
+        auto kern = nn == 4   ? pick(std::integral_constant<int, 4>{})
+                    : nn == 2 ? pick(std::integral_constant<int, 2>{})
+                              : pick(std::integral_constant<int, 1>{});
+        hipLaunchKernelGGL(kern, grid, dim3(64 * NEAR64_WAVES), 0, s, *near, wgs8, M);
+    } else if (nchunk > 0) {
+        auto kern = nc == 4 ? m2l_mfma64_soft<4, 1> : nc == 2 ? m2l_mfma64_soft<2, 2> : m2l_mfma64_soft<1, 4>;
+        hipLaunchKernelGGL(kern, dim3(unsigned(nchunk * ncg)), dim3(64 * nrt), 0, s, M);
     }
     (void)timer_mark(op, 0, s);
 }
 
-// coupling partials [chunk][nvec][nq][ncol] of the far pairs.  kind: 0 fp64
-// partials of the vector path, 1 fp32 partials of the matrix-core path at
-// reduced precision, 2 fp64 partials of the matrix-core path
-static igb_status launch_m2l(igb_op op, const MatvecWork& W, double2* xh, int64_t ks, bool low, int ncol, hipStream_t s, int& kind) {
-    const bool lo = low && op->prm.precision != IGB_FP64;
+// kind of the coupling's partials [chunk][nvec][nq][ncol]: 0 fp64 partials of the
+// vector path, 1 fp32 partials of the matrix-core path at reduced precision, 2
+// fp64 partials of the matrix-core path (the matrix cores pay off for blocks of
+// at least MF64_MIN_COLS columns; a single column is HBM-bound on the vector path)
+static int m2l_kind(igb_op op, bool low, int ncol) {
+    if (low && op->prm.precision != IGB_FP64) return 1;
+    return mf_fp64(op) && ncol >= MF64_MIN_COLS ? 2 : 0;
+}
+
+// coupling partials of the far pairs, of kind m2l_kind (near: see launch_m2l_f64_soft)
+static igb_status launch_m2l(igb_op op, const MatvecWork& W, double2* xh, int64_t ks, bool low, int ncol,
+                             const Near64Args* near, int nn, hipStream_t s, int& kind) {
     const bool hard = op->bc == IGB_HARD;
-    // fp64: the matrix cores pay off for blocks of at least MF64_MIN_COLS
-    // columns; a single column is HBM-bound on the vector path
-    kind = lo ? 1 : (mf_fp64(op) && ncol >= MF64_MIN_COLS) ? 2 : 0;
+    kind = m2l_kind(op, low, ncol);
+    const bool lo = kind == 1;
     if (kind == 2) {
         if (hard) launch_m2l_lo_t<MfmaF64, true>(op, W, xh, ks, ncol, s);
-        else launch_m2l_f64_soft(op, W, xh, ncol, s);
+        else launch_m2l_f64_soft(op, W, xh, ncol, near, nn, s);
     } else if (!lo) {
         if ((op->nq + 63) / 64 * 64 > 128) {
             set_error("h2_matvec: interpolation degree too large for the coupling kernel");
@@ -3530,6 +3632,11 @@ static igb_status matvec_launches(igb_op op, const MatvecWork& W, const double* 
     double2* yh = W.yhat;
     const int64_t N = op->N;
     const bool far = (parts & IGB_PART_FAR) && op->nfar > 0;
+    const int use_near = (parts & IGB_PART_NEAR) ? 1 : 0;
+    // near products on the fp64 matrix cores; joint: launched with the coupling
+    const bool near64 = !(low && op->d_val_lo.ptr) && op->d_val64.ptr && W.xnear64 &&
+                        (op->prm.precision == IGB_FP64 ? ncol >= MF64_MIN_COLS : low);
+    bool joint = false;
     if (far) {
         const double2* x2 = X;
         if (hard) {
@@ -3546,7 +3653,15 @@ static igb_status matvec_launches(igb_op op, const MatvecWork& W, const double* 
         launch_m2m_levels(op->d_T.as<double>(), q, L, g->npatch, op->clu_off, xh, ncol, s, op->far_lmin, kinds, ks);
         if ((st = timer_mark(op, 2, s))) return st;
         int pkind = 0;
-        if ((st = launch_m2l(op, W, xh, ks, low, ncol, s, pkind))) return st;
+        // one launch where the near field is a third of the products or more: level-5
+        // sphere at leaf depth 3 (61%) 503 -> 439 us at 64 columns, level-5 star (4%)
+        // 1262 -> 1371 us at 20, as the coupling's waves then run in the larger
+        // workgroups of the near field (timed apart when the operator profiles)
+        joint = near64 && use_near && !op->profile && !hard && m2l_kind(op, low, ncol) == 2 &&
+                op->near_tile_vals * 2 >= op->nfar * nq * ((nq + 15) / 16 * 16);
+        Near64Args na{};
+        const int nn = joint ? prepare_near64(op, W, X, Y, ncol, 4, s, na) : 0;
+        if ((st = launch_m2l(op, W, xh, ks, low, ncol, joint ? &na : nullptr, nn, s, pkind))) return st;
         if ((st = timer_mark(op, 3, s))) return st;
         // (the stored fp64 tiles' products of blocks below 16 columns carry the target factors)
         const int nvec = !hard ? 1 : pkind == 0 && !op->prm.far_on_the_fly ? HARD_VECS : 10;
@@ -3601,7 +3716,6 @@ static igb_status matvec_launches(igb_op op, const MatvecWork& W, const double* 
     const FarLeaves yfar{far ? W.leafbuf : nullptr, op->d, g->p, op->L, g->k, g->npatch, hard ? 3 : 1, ncol};
     const int* s0p = hard ? op->d_s0_ptr.as<int>() : nullptr;
     const int* s0r = hard ? op->d_s0_reps.as<int>() : nullptr;
-    const int use_near = (parts & IGB_PART_NEAR) ? 1 : 0;
     const dim3 sg(blocks_for(N * 64, 256)), sb(256);
     const int64_t* rp = op->d_rowptr.as<int64_t>();
     const int64_t* rco = op->d_row_coff.as<int64_t>();
@@ -3618,34 +3732,17 @@ static igb_status matvec_launches(igb_op op, const MatvecWork& W, const double* 
                            op->d_near_tiles.as<NearTile>(), int64_t(op->near_tiles.size()),
                            op->d_near_tile_cols.as<int>(),
                            op->d_val_lo.as<float2>(), xt, N, yfar, s0p, s0r, use_near, ncol, Y);
-    } else if (op->d_val64.ptr && W.xnear64 &&
-               (op->prm.precision == IGB_FP64 ? ncol >= MF64_MIN_COLS : low)) {
-        // fp64 matrix cores over the tiles: columns transposed into 16-wide rows once
-        const int ncb = (ncol + 15) / 16;
-        if (use_near)
-            hipLaunchKernelGGL(columns_t64, dim3(blocks_for(int64_t(ncb) * N * 16, 256)), dim3(256), 0, s, X, N,
-                               ncol, ncb, W.xnear64);
-        // NC column tiles per workgroup (each tile value read serves 16 NC columns):
-        // 2 when it divides the column tile count and the grid keeps at least
-        // 512 workgroups (2 per CU), else 1 (4 measured slower on the level-5
-        // sphere and the level-6 star); the column results do not depend on NC
-        const int64_t ntl0 = int64_t(op->near_tiles.size());
-        int nct = ncb % 2 == 0 && ntl0 * (ncb / 2) >= 512 ? 2 : 1;
-        if (op->tile_near_nct > 0 && ncb % op->tile_near_nct == 0) nct = op->tile_near_nct;   // tuned shape
-        const dim3 tg(unsigned(op->near_tiles.size()), unsigned(ncb / nct)), tb(64 * NEAR64_WAVES);
-        const NearTile* tl = op->d_near_tiles.as<NearTile>();
-        const int64_t ntl = int64_t(op->near_tiles.size());
-        const int* tcl = op->d_near_tile_cols.as<int>();
-        const double2* v64 = op->d_val64.as<double2>();
-        if (nct == 4)
-            hipLaunchKernelGGL(near_tiles_mfma64<4>, tg, tb, 0, s, tl, ntl, tcl, v64, W.xnear64, N, yfar, s0p,
-                               s0r, use_near, ncol, Y);
-        else if (nct == 2)
-            hipLaunchKernelGGL(near_tiles_mfma64<2>, tg, tb, 0, s, tl, ntl, tcl, v64, W.xnear64, N, yfar, s0p,
-                               s0r, use_near, ncol, Y);
-        else
-            hipLaunchKernelGGL(near_tiles_mfma64<1>, tg, tb, 0, s, tl, ntl, tcl, v64, W.xnear64, N, yfar, s0p,
-                               s0r, use_near, ncol, Y);
+    } else if (near64) {
+        if (use_near && !joint) {
+            // (4 column tiles a workgroup pay in the joint launch only)
+            Near64Args A{};
+            const int nn = prepare_near64(op, W, X, Y, ncol, 2, s, A);
+            auto kern = nn == 4 ? near_tiles_mfma64<4> : nn == 2 ? near_tiles_mfma64<2> : near_tiles_mfma64<1>;
+            hipLaunchKernelGGL(kern, dim3(unsigned(A.ntile * A.ncg)), dim3(64 * NEAR64_WAVES), 0, s, A);
+        }
+        if (far || !use_near)
+            hipLaunchKernelGGL(add_far, dim3(blocks_for(N * ncol, 256)), dim3(256), 0, s, yfar, s0p, s0r, use_near, N,
+                               ncol, Y);
     } else if (ncol == 1 && use_near && !op->near_wgs.empty() &&
                size_t(op->near_list_max) * sizeof(double2) <= size_t(g->ctx->lds_max)) {
         hipLaunchKernelGGL(spmv_groups<NEAR_GROUP_ROWS>, dim3(unsigned(op->near_wgs.size())),
