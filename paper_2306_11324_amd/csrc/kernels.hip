@@ -2453,13 +2453,20 @@ __device__ __forceinline__ double2 sum_kernel(const double* x, const double* g, 
 constexpr int LAYER_WAVES = 16;          // waves per workgroup
 constexpr int LAYER_GROUPS = 256;        // workgroups aimed at per column block
 constexpr int LAYER_TILE = 8;            // points staged at a time by a wave
-constexpr int LAYER_MIN_TARGETS = 24;    // fewer targets: lanes over the points (layer_sum_few)
 // segments of npts points for ntgt targets, with sums of at most `room` entries per
-// column (one: written in place)
+// column (one: written in place), or 0: lanes over the points (layer_sum_few).  The
+// times of one column decide (not the block's, as a column's sums must not depend on
+// the others), in us on a level-2 to level-4 sphere: a lane's serial share of the
+// points or the rate of all values for few, a wave's share of its segment and the
+// second launch for segments (level 2, 64 targets: 7 against 13 us, 1000 targets: 14
+// against 78; level 4, 8 targets: 84 against 13, 1000 targets: 165 against 114).
 static inline int layer_segments(int64_t npts, int64_t ntgt, int64_t room) {
-    if (ntgt < LAYER_MIN_TARGETS) return 1;
     const int64_t groups = (ntgt + 63) / 64;
-    return int(std::max<int64_t>(1, std::min(std::min(LAYER_GROUPS / groups, npts / (16 * LAYER_WAVES)), room / ntgt)));
+    const int64_t nseg =
+        std::max<int64_t>(1, std::min(std::min(LAYER_GROUPS / groups, npts / (16 * LAYER_WAVES)), room / ntgt));
+    const double few = std::max(0.4 * double(npts) / 256, 3.3e-6 * double(npts) * double(ntgt));
+    const double seg = 0.4 * double(npts) / double(nseg * LAYER_WAVES) * double((nseg * groups + 255) / 256) + 3;
+    return few <= seg ? 0 : int(nseg);
 }
 template <int KIND, int CB>
 __global__ __launch_bounds__(64 * LAYER_WAVES) void layer_sum(const double* __restrict__ geo,
@@ -2564,7 +2571,7 @@ __global__ __launch_bounds__(256) void layer_sum_few(const double* __restrict__ 
 template <int KIND>
 static void launch_layer_sum(const double* geo, const double2* dens, int64_t npts, const double* tgt, int ntgt,
                              double kappa, int ncol, int nseg, double2* part, double2* out, hipStream_t s) {
-    if (ntgt < LAYER_MIN_TARGETS) {
+    if (nseg == 0) {
         hipLaunchKernelGGL((layer_sum_few<KIND>), dim3(unsigned(ntgt), unsigned(ncol)), dim3(256), 0, s, geo, dens, npts,
                            tgt, ntgt, kappa, out);
         return;
@@ -3912,8 +3919,8 @@ igb_status potential_device(igb_op op, const double* coeffs, int ndir, const dou
              return IGB_OK;
          })))
         return st;
-    // segments' sums, small beside the densities; without room for them one segment
-    int nseg = layer_segments(npts, npt, npts / 4);
+    // segments' sums, at most half of the densities; without room for them one segment
+    int nseg = layer_segments(npts, npt, npts / 2);
     if (nseg > 1 && alloc(d_part, size_t(nseg) * ndir * npt * sizeof(double2), nullptr)) nseg = 1;
     auto sum = hard ? launch_layer_sum<SUM_POT_HARD> : launch_layer_sum<SUM_POT_SOFT>;
     sum(d_geo.as<double>(), d_dens.as<double2>(), npts, d_pts.as<double>(), npt, op->kappa, ndir, nseg,

@@ -1,7 +1,7 @@
 """Far field and direct potential at the edges of their target and column blocks.
 
-Targets are taken 64 to a wave over segments of the surface points (fewer than
-24: one workgroup each), columns 1, 4 or 16 at a time; a column's values must
+Targets are taken 64 to a wave over segments of the surface points (or, for little
+work, one workgroup each), columns 1, 4 or 16 at a time; a column's values must
 not depend on the other columns, and both forms must agree.
 """
 import numpy as np
@@ -44,3 +44,23 @@ def test_blocks_of_targets_and_columns(op, what, ntgt, ncol):
     k = min(ntgt, 5)
     few = evaluate(op, what, c, t[:k])
     assert np.abs(few - u[:, :k]).max() <= 1e-12 * np.abs(u).max()
+
+
+@pytest.mark.parametrize("what", ["farfield", "potential"])
+@pytest.mark.parametrize("m,ntgt", [(1, 1), (1, 200), (2, 64), (2, 500), (4, 3), (4, 200)])
+def test_few_targets_or_points_in_either_form(what, m, ntgt):
+    # a column's sums do not depend on the columns beside it on either side of the
+    # rule between the forms, and a subset of targets (which may take the other form)
+    # agrees to 1e-12 of the largest value
+    import torch
+    from paper_2306_11324_amd import binding as B
+    ctx = B.Context(0)
+    op = B.Operator(ctx, B.Geometry(ctx, I.sphere_patches(), m, 2), kappa=2.0, q=4, leaf_depth=1)
+    c = torch.from_numpy(I.random_complex(7, (6, op.n))).cuda()
+    t = I.random_directions(11, ntgt) * (1.0 if what == "farfield" else 2.5)
+    u = evaluate(op, what, c, t)
+    assert np.isfinite(u).all()
+    for k in (0, 5):
+        assert np.array_equal(evaluate(op, what, c[k:k + 1].contiguous(), t)[0], u[k])
+    few = evaluate(op, what, c, t[-1:])
+    assert np.abs(few - u[:, -1:]).max() <= 1e-12 * np.abs(u).max()
