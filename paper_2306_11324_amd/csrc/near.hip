@@ -171,11 +171,13 @@ __device__ __forceinline__ void point_data(const ElemRef& R, const double* Cu, c
 // (Sound-hard: the curl parts c_a . c_b as three more components with the kernel g.)
 // One wave per workgroup, so that no wave waits for another at the many small
 // rules of an element (16-20 of them, most with a few pairs).  Bound by fp64
-// issue: about 75 VALU instructions per point pair, 125 per source element to
+// issue: about 80 VALU instructions per point pair, 125 per source element to
 // place its points, and the padded matrix products, which run on the same fp64
-// units.  Level-5 sphere, p = 2, leaf depth 3, 17.6 million pairs: 128 -> 53 ms
+// units.  Level-5 sphere, p = 2, leaf depth 3, 17.6 million pairs: 128 -> 44 ms
 // (before: a workgroup per pair, values and products through LDS); level-5 hard
-// star, 5.3 million pairs: 73 -> 39 ms.
+// star, 5.3 million pairs: 73 -> 37 ms.  Segments of 1024 pairs left a quarter of
+// the CU time idle at the end of a launch (52 and 39 ms), of 128 set up their
+// rules too often (48).
 // --------------------------------------------------------------------------
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
@@ -185,7 +187,7 @@ __device__ __forceinline__ int regular_points(int code) {
     return nx > ny ? nx : ny;
 }
 constexpr int REG_POINTS_SMALL = 36;   // rules of up to 6 x 6 points take the form with less LDS
-constexpr int REG_SEG = 1024;          // pairs per workgroup
+constexpr int REG_SEG = 256;           // pairs per workgroup
 constexpr int REG_ORDER_MAX = 12;
 
 // point data of a regular rule: g[0..6] = x, n~, |n~|; sound-hard also F_s, F_t
@@ -258,7 +260,7 @@ __global__ __launch_bounds__(64, 2) void near_regular(NearArgs A, int e0) {
     static_assert(MX % 4 == 0 && MX <= REG_POINTS_MAX, "padded points of a rule");
     __shared__ unsigned short code[REG_SEG], list[REG_SEG];
     __shared__ double xg[MX][NG], yg[YC][NG];
-    __shared__ double px[HARD ? 1 : MX][NL];              // sound-soft: w phi_a at the test points
+    __shared__ double px[HARD ? 1 : MX][NL], py[HARD ? 1 : YC][NL];   // sound-soft: w phi at the test and source points
     __shared__ double bx[2 * REG_ORDER_MAX][ND];          // 1-D basis values (then derivatives) at the test points: u, v
     __shared__ double by[64][ND];                         // the same per source of a batch: [source][u, v]
     __shared__ int lsrc[16], lslot[16];
@@ -352,6 +354,16 @@ __global__ __launch_bounds__(64, 2) void near_regular(NearArgs A, int e0) {
                 basis(u ? nyu : nyv, u ? r : r - nyu, A.C1 + (u ? Rf.ex : Rf.ey) * P1 * P1, by[t]);
             }
             __syncthreads();
+            if constexpr (!HARD) {
+                for (int t = lane; t < je; t += 64) {
+                    const int q = t / ny4, j = t - q * ny4, jj = j < ny ? j : 0, jv = jj * invy >> 16;
+                    const double *pu = by[q * n1 + jj - jv * nyu], *pv = by[q * n1 + nyu + jv];
+                    const double on = j < ny ? 1.0 : 0.0;
+#pragma unroll
+                    for (int b = 0; b < NL; ++b) py[t][b] = on * (pu[b % P1] * pv[b / P1]);
+                }
+                __syncthreads();
+            }
             f64x4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0};
             int q = 0, qend = ny4;   // current source of the batch, its end
             auto store = [&]() {
@@ -397,6 +409,12 @@ __global__ __launch_bounds__(64, 2) void near_regular(NearArgs A, int e0) {
                         cr = ci = f64x4{0, 0, 0, 0};
                         ++q;
                         qend += ny4;
+                    }
+                    if constexpr (!HARD) {
+                        const double ph = py[jk + g][lc];
+                        cr = __builtin_amdgcn_mfma_f64_16x16x4f64(ph, tr[0][r], cr, 0, 0, 0);
+                        ci = __builtin_amdgcn_mfma_f64_16x16x4f64(ph, ti[0][r], ci, 0, 0, 0);
+                        continue;
                     }
                     const int j = jk + g - (qend - ny4), jv = j * invy >> 16;
                     const bool in = j < ny;
