@@ -2241,7 +2241,7 @@ __global__ __launch_bounds__(64 * NEAR64_WAVES) void near_tiles_mfma64(Near64Arg
 // kernel's time.  The near workgroups come first, the coupling's waves (a row
 // tile of a chunk's NM column tiles each) fill what they leave.  Level-5 sphere,
 // leaf depth 3, 64 columns, of which the matrix cores' share is 293 us:
-// JOINT0 us in two launches, JOINT1 in one.
+// 472 us in two launches, 400 in one (the whole product 500 and 437).
 template <int NN, int NM>
 __global__ __launch_bounds__(64 * NEAR64_WAVES, 4) void near_far_mfma64(Near64Args A, int near_wgs8, M2l64Args M) {
     __shared__ Near64Lds<NN> lds;
@@ -2743,16 +2743,20 @@ __device__ double2 pot_l2p(const double* x, const double* lo, const double* hi, 
 // clusters that act on the points directly (each node a source point carrying
 // the cluster's moment), plus direct quadrature over the elements of the box's
 // inadmissible finest clusters (level L, s x s elements each).  Source points
-// are staged in LDS a tile at a time and shared by the box's points.  One workgroup per (box, column); a box of
-// few points gives each point a group of lanes (a power of two) that split
-// every tile and add their partial sums in a fixed order, so a column's result
-// does not depend on the others.
+// are staged in LDS a tile at a time and shared by the box's points.  One workgroup
+// per (box, column, part of the box's sources); each point takes a group of lanes,
+// as many as fit, that split every tile and add their partial sums in a fixed
+// order, then pot_parts_add adds the parts (their number is a matter of the plan),
+// so a column's result does not depend on the others.
 // (A staged source holds its position and the density with every factor that does
 // not depend on the point: 5 doubles sound-soft, 8 with the normal sound-hard.
 // Bound by fp64 VALU issue, about 55 instructions per kernel value; 200,000
 // points around the level-5 sphere, kappa 8, q 6: 36.8 -> 19.1 ms with the short
-// reciprocal square root and sine / cosine.)
+// reciprocal square root and sine / cosine.  The boxes hold 1 to 128 points: in
+// whole workgroups with groups of a power of two lanes, 27% of the lanes idled and
+// the few full boxes ran on alone for a third of the kernel; -> 11.9 ms.)
 constexpr int POT_TILE = 256;   // source points per LDS tile
+constexpr int POT_WORKGROUPS = 32768;   // workgroups aimed at (5 thousand: 18.3 ms, 16 thousand 12.5, 65 thousand 11.5)
 template <bool HARD>
 __global__ __launch_bounds__(POT_LEAF_POINTS) void pot_l2p_near(
     const double* __restrict__ pts, const int* __restrict__ perm, const int* __restrict__ box_ptr,
@@ -2800,67 +2804,79 @@ __global__ __launch_bounds__(POT_LEAF_POINTS) void pot_l2p_near(
     const double2* D = dens + int64_t(r) * nqtot;
     const int n = 1 << L, s = 1 << d, per_leaf = s * s * nqp;
     const int p0 = box_ptr[b], p1 = box_ptr[b + 1];
-    // lanes per point: the largest power of two gs with gs * points <= the workgroup
-    int gs = 1;
-    while (gs < POT_LEAF_POINTS && 2 * gs * (p1 - p0) <= POT_LEAF_POINTS) gs *= 2;
-    const int slot = tid / gs, lane = tid % gs, per_round = POT_LEAF_POINTS / gs;
-    const int f0 = m2p_ptr[b], nm2p = (m2p_ptr[b + 1] - f0) * nq;
-    // (a box at the depth cap may hold more points than threads)
-    for (int base = p0; base < p1; base += per_round) {
-        const int i = base + slot;
-        const bool mine = i < p1;
-        const int pi = mine ? perm[i] : 0;
+    // sources: the nodes of the clusters that act on the points, then the near clusters'
+    // quadrature points; this workgroup's part of them
+    const int f0 = m2p_ptr[b], nm2p = (m2p_ptr[b + 1] - f0) * nq, n0 = near_ptr[b];
+    const int64_t nsrc = nm2p + int64_t(near_ptr[b + 1] - n0) * per_leaf, part = blockIdx.z, parts = gridDim.z;
+    const int64_t k0 = nsrc * part / parts, k1 = nsrc * (part + 1) / parts;
+    // rounds of points (most boxes: one); lanes per point
+    for (int base = p0; base < p1;) {
+        const int left = p1 - base;
+        // (65 to 106 points: 64 with two lanes each, then the rest with three or more, take
+        // less time than one lane each)
+        const int take = left > 106 ? min(left, POT_LEAF_POINTS) : left > 64 ? 64 : left;
+        const int gs = POT_LEAF_POINTS / take, slot = tid / gs, lane = tid - slot * gs;
+        const bool mine = slot < take;
+        const int pi = perm[base + min(slot, take - 1)];
         const double x[3] = {pts[3 * pi], pts[3 * pi + 1], pts[3 * pi + 2]};
         double2 acc = make_double2(0, 0);
         __syncthreads();   // the previous round's tiles and partial sums consumed
-        if (has_far) {
+        if (has_far && part == 0) {
             for (int a = tid; a < n3; a += POT_LEAF_POINTS) lx[a] = lbox[(int64_t(b) * n3 + a) * ncol + r];
             __syncthreads();
             if (mine && lane == 0) acc = pot_l2p(x, box_lo + 3 * b, box_hi + 3 * b, tch, q, lx);
             __syncthreads();   // lx consumed before the tiles overwrite it
         }
-        // cluster nodes evaluated at the points: position, n~, a, weight 1, the moment as density
-        for (int t0 = 0; t0 < nm2p; t0 += POT_TILE) {
-            const int cnt = min(POT_TILE, nm2p - t0);
+        for (int64_t t0 = k0; t0 < k1; t0 += POT_TILE) {
+            const int cnt = int(min(int64_t(POT_TILE), k1 - t0));
             for (int k = tid; k < cnt; k += POT_LEAF_POINTS) {
-                const int64_t sc = m2p_src[f0 + (t0 + k) / nq];
-                const int64_t ni = sc * nq + (t0 + k) % nq;
-                put(k, nodes + ni * 16, 1.0, xh[ni * ncol + r]);
+                const int64_t i = t0 + k;
+                if (i < nm2p) {
+                    // a cluster node: position, n~, a, weight 1, the moment as density
+                    const int c = int(i) / nq;
+                    const int64_t ni = int64_t(m2p_src[f0 + c]) * nq + (int(i) - c * nq);
+                    put(k, nodes + ni * 16, 1.0, xh[ni * ncol + r]);
+                } else {
+                    const int64_t j = i - nm2p, f = j / per_leaf, loc = near_leaf[n0 + f];
+                    const int li = int(j - f * per_leaf), el = li / nqp, g = li % nqp;
+                    const int64_t patch = loc / (int64_t(n) * n);
+                    const int cy = int((loc / n) % n), cx = int(loc % n);
+                    const int64_t e = (patch * nel1 + cy * s + el / s) * nel1 + cx * s + el % s;
+                    const int64_t gi = e * nqp + g;
+                    put(k, geo + gi * 8, geo[gi * 8 + 7], D[gi]);
+                }
             }
             __syncthreads();
             if (mine)
                 for (int k = lane; k < cnt; k += gs) acc = term(x, tg[k], acc);
             __syncthreads();
         }
-        for (int f = near_ptr[b]; f < near_ptr[b + 1]; ++f) {
-            const int64_t loc = near_leaf[f];
-            const int64_t patch = loc / (int64_t(n) * n);
-            const int cy = int((loc / n) % n), cx = int(loc % n);
-            for (int t0 = 0; t0 < per_leaf; t0 += POT_TILE) {
-                const int cnt = min(POT_TILE, per_leaf - t0);
-                for (int k = tid; k < cnt; k += POT_LEAF_POINTS) {
-                    const int li = t0 + k, el = li / nqp, g = li % nqp;
-                    const int64_t e = (patch * nel1 + cy * s + el / s) * nel1 + cx * s + el % s;
-                    const int64_t gi = e * nqp + g;
-                    put(k, geo + gi * 8, geo[gi * 8 + 7], D[gi]);
-                }
-                __syncthreads();
-                if (mine)
-                    for (int k = lane; k < cnt; k += gs) acc = term(x, tg[k], acc);
-                __syncthreads();
-            }
-        }
+        double2* o = u + (part * ncol + r) * npt;
         if (gs == 1) {
-            if (mine) u[int64_t(r) * npt + pi] = acc;
+            if (mine) o[pi] = acc;
         } else {
             smem[tid] = acc;
             __syncthreads();
-            if (mine && lane == 0) {
-                for (int l = 1; l < gs; ++l) acc = cadd(acc, smem[tid + l]);
-                u[int64_t(r) * npt + pi] = acc;
+            int st = 1;
+            while (2 * st < gs) st *= 2;
+            for (; st > 0; st /= 2) {
+                if (lane < st && lane + st < gs) smem[tid] = cadd(smem[tid], smem[tid + st]);
+                __syncthreads();
             }
+            if (mine && lane == 0) o[pi] = smem[tid];
         }
+        base += take;
     }
+}
+
+// u[column][point] = sum of its parts, in order
+__global__ __launch_bounds__(256) void pot_parts_add(const double2* __restrict__ part, int parts, int64_t n,
+                                                     double2* __restrict__ u) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= n) return;
+    double2 s = part[i];
+    for (int k = 1; k < parts; ++k) s = cadd(s, part[k * n + i]);
+    u[i] = s;
 }
 
 // ==========================================================================
@@ -4005,12 +4021,24 @@ igb_status potential_h2_device(igb_op op, const double* coeffs, int ndir, const 
                            d_fsrc.as<int>(), ndir, op->kappa, hard ? 1 : 0, d_lbox.as<double2>());
         IGB_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(hard ? pot_l2p_near<true> : pot_l2p_near<false>, dim3(unsigned(nbox), unsigned(ndir)), dim3(POT_LEAF_POINTS), 0, s,
+    // parts of each box's sources: enough workgroups that the fullest boxes don't run on
+    // alone, parts of two tiles or more on average
+    const int64_t sources = (int64_t(P.m2p_src.size()) * nq +
+                             int64_t(P.near_leaf.size()) * (nqtot / clusters_on_level(g->npatch, lmax))) / nbox;
+    int parts = int(std::max<int64_t>(1, std::min<int64_t>({32, (POT_WORKGROUPS + nbox - 1) / nbox, sources / (2 * POT_TILE)})));
+    DevBuf d_part;   // (without room for the parts' sums: one part)
+    if (parts > 1 && alloc(d_part, size_t(parts) * ndir * npt * sizeof(double2), nullptr)) parts = 1;
+    double2* sum = parts > 1 ? d_part.as<double2>() : reinterpret_cast<double2*>(u);
+    hipLaunchKernelGGL(hard ? pot_l2p_near<true> : pot_l2p_near<false>, dim3(unsigned(nbox), unsigned(ndir), unsigned(parts)),
+                       dim3(POT_LEAF_POINTS), 0, s,
                        d_pts.as<double>(), d_perm.as<int>(), d_bptr.as<int>(), d_blo.as<double>(), d_bhi.as<double>(),
                        d_tch.as<double>(), q, any_far ? d_lbox.as<double2>() : nullptr, ndir, d_mptr.as<int>(),
                        d_msrc.as<int>(), d_nodes.as<double>(), mom, d_nptr.as<int>(), d_nleaf.as<int>(),
                        g->m - lmax, lmax, g->nel1, nqd * nqd, d_geo.as<double>(), d_dens.as<double2>(), nqtot,
-                       op->kappa, npt, reinterpret_cast<double2*>(u));
+                       op->kappa, npt, sum);
+    if (parts > 1)
+        hipLaunchKernelGGL(pot_parts_add, dim3(unsigned((int64_t(ndir) * npt + 255) / 256)), dim3(256), 0, s, sum, parts,
+                           int64_t(ndir) * npt, reinterpret_cast<double2*>(u));
     IGB_HIP(hipGetLastError());
     IGB_HIP(hipStreamSynchronize(s));   // temporaries are freed on return
     return IGB_OK;
