@@ -33,14 +33,16 @@ bool charge(igb_ctx_s* c, size_t bytes) {
 // turn is 0.105 s an operator, but 0.1-3 s where their memory goes back to the
 // driver each time (it stalls at some 100 GB/s of allocations and frees; slower
 // assembly, 0.45 s an operator, did not meet it).  Contexts without a budget
-// only; blocks of POOL_MIN bytes and more, POOL_BLOCKS of them and an eighth of
-// the device's memory at most (the longest kept go first), and none while less
+// only; blocks of POOL_MIN bytes and more (smaller ones don't stall, and keeping the
+// 191 MB of a level-3 operator slowed its near product of 15 columns, 26 -> 36 us,
+// though none of its arrays moved), POOL_BLOCKS of them and an eighth of the
+// device's memory at most (the longest kept go first), and none while less
 // than half of the device's memory is free.  Everything kept is freed when an
 // allocation fails and with the device's last context.  A buffer is kept after a
 // device synchronisation (hipFree implies one too), so a kept block is idle
 // whatever stream its last user or its next one runs on.
 namespace {
-constexpr size_t POOL_MIN = size_t(1) << 20, POOL_STEP = size_t(2) << 20;
+constexpr size_t POOL_MIN = size_t(512) << 20;
 constexpr int POOL_BLOCKS = 64;
 struct DevPool {
     struct Block {
@@ -116,8 +118,7 @@ igb_status dev_malloc(DevBuf& b, size_t bytes, const char* who) {
         return IGB_ERR_BUDGET;
     }
     DevPool* p = c ? pool_of(c->device) : nullptr;
-    // (whole steps, which the driver takes anyway: equal sizes are what repeats)
-    const size_t size = p && c->budget == 0 && bytes >= POOL_MIN ? (bytes + POOL_STEP - 1) / POOL_STEP * POOL_STEP : 0;
+    const size_t size = p && c->budget == 0 && bytes >= POOL_MIN ? bytes : 0;   // of a block that may be kept, else 0
     if (size) {
         std::lock_guard<std::mutex> lk(p->mu);
         for (int i = p->n - 1; i >= 0 && !b.ptr; --i)
@@ -125,13 +126,13 @@ igb_status dev_malloc(DevBuf& b, size_t bytes, const char* who) {
     }
     hipError_t e = hipSuccess;
     if (!b.ptr) {
-        e = hipMalloc(&b.ptr, size ? size : bytes);
+        e = hipMalloc(&b.ptr, bytes);
         if (e != hipSuccess && p) {
             std::lock_guard<std::mutex> lk(p->mu);
             if (p->n > 0) {   // once more without the kept blocks
                 (void)hipGetLastError();
                 p->clear();
-                e = hipMalloc(&b.ptr, size ? size : bytes);
+                e = hipMalloc(&b.ptr, bytes);
             }
         }
     }
@@ -142,7 +143,7 @@ igb_status dev_malloc(DevBuf& b, size_t bytes, const char* who) {
         return IGB_ERR_HIP;
     }
 #ifdef IGB_POISON
-    (void)hipMemset(b.ptr, 0xff, size ? size : bytes);
+    (void)hipMemset(b.ptr, 0xff, bytes);
     (void)hipDeviceSynchronize();
 #endif
     b.bytes = bytes;
