@@ -1806,6 +1806,7 @@ __global__ void m2l_reduce(const PT* part, const int* tgt_chunk_ptr, int64_t ncl
     yh[gid] = s;
 }
 
+constexpr size_t NEAR_GROUP_MIN_WGS = 64;   // fewer: several columns by spmv_combine
 constexpr int SPMV_U1 = 4;   // row strides in flight per lane of the one-column near product
 
 // y[r][row] = sum_j val x[r][col] (+ far part mapped to the solution space); one
@@ -1892,57 +1893,85 @@ __global__ __launch_bounds__(256) void spmv_combine(const int64_t* __restrict__ 
     }
 }
 
-// The one-column near product by groups: a workgroup takes up to
-// NEAR_GROUP_ROWS rows of one group, gathers the group's x entries into LDS in
-// list order (every row of the group has exactly the group's columns, entry j
-// of a row belonging to list entry j), and then each wave forms one row's sum
-// against LDS: no column index and no x gather per nonzero.  The lanes, trips
-// and butterfly are those of spmv_combine<1>, with the same x values, so the
-// rows equal spmv_combine's bitwise.
-template <int NWV>
+// The near product of 1 to 15 columns by groups: a workgroup takes up to
+// NEAR_GROUP_ROWS rows of one group, gathers the group's x entries of RB columns
+// into LDS in list order (every row of the group has exactly the group's columns,
+// entry j of a row belonging to list entry j), and then each wave forms one row's
+// sums against LDS: no column index and no x gather per nonzero.  The lanes,
+// trips and butterfly of each column are those of spmv_combine, with the same x
+// values, so the rows equal spmv_combine's bitwise for every RB.
+// (As many columns a pass as fit the LDS, up to 8, so that the values are read once
+// or twice; the gathers of every wave set the time of spmv_combine.  Level-5 sphere
+// at leaf depth 3, 2 / 5 / 15 columns: 131 / 302 / 772 -> 67 / 182 / 478 us, level-5
+// star 50 / 118 / 291 -> 35 / 89 / 192 us.)
+template <int NWV, int RB>
 __global__ __launch_bounds__(64 * NWV) void spmv_groups(const NearGroupWG* __restrict__ wgs,
                                                         const int* __restrict__ grp_rows,
                                                         const int64_t* __restrict__ row_ptr,
                                                         const int* __restrict__ col,
                                                         const double2* __restrict__ val,
-                                                        const double2* __restrict__ x,
+                                                        const double2* __restrict__ x, int64_t nrows, int ncol,
                                                         FarLeaves F, const int* __restrict__ s0_ptr,
                                                         const int* __restrict__ s0_reps, double2* __restrict__ y) {
     extern __shared__ double2 xs[];
     // consecutive workgroups (the same or neighbouring groups) on one XCD
     const NearGroupWG W = wgs[xcd_chunk(blockIdx.x, gridDim.x)];
-    for (int j = threadIdx.x; j < W.list_len; j += 64 * NWV) xs[j] = x[col[W.list_off + j]];
-    __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (wave >= W.nrows) return;
-    const int row = grp_rows[W.row0 + wave];
-    const double2* v0 = val + row_ptr[row];
-    const int len = W.list_len;
-    constexpr int U = SPMV_U1;
-    double2 acc = make_double2(0, 0);
-    int j = lane;
-    for (; j + (U - 1) * 64 < len; j += U * 64) {
-        double2 v[U];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, len = W.list_len;
+    for (int c0 = 0; c0 < (RB == 1 ? 1 : ncol); c0 += RB) {
+        if (RB > 1 && c0 > 0) __syncthreads();   // the pass before is read
+        for (int j = threadIdx.x; j < len; j += 64 * NWV) {
+            const int64_t cc = col[W.list_off + j];
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = ld_nt(v0 + j + u * 64);
+            for (int cb = 0; cb < RB; ++cb)
+                xs[cb * len + j] = c0 + cb < ncol ? x[int64_t(c0 + cb) * nrows + cc] : make_double2(0, 0);
+        }
+        __syncthreads();
+        if (wave >= W.nrows) {
+            if (RB == 1) return;
+            continue;
+        }
+        const int row = grp_rows[W.row0 + wave];
+        const double2* v0 = val + row_ptr[row];
+        constexpr int U = SPMV_U1;
+        double2 acc[RB];
 #pragma unroll
-        for (int u = 0; u < U; ++u) acc = cfma(v[u], xs[j + u * 64], acc);
-    }
-    for (; j < len; j += 64) acc = cfma(ld_nt(v0 + j), xs[j], acc);
+        for (int cb = 0; cb < RB; ++cb) acc[cb] = make_double2(0, 0);
+        int j = lane;
+        for (; j + (U - 1) * 64 < len; j += U * 64) {
+            double2 v[U];
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        acc.x += __shfl_xor(acc.x, off, 64);
-        acc.y += __shfl_xor(acc.y, off, 64);
-    }
-    if (lane == 0) {
-        if (F.leafbuf) {
-            if (s0_ptr) {
-                for (int q = s0_ptr[row]; q < s0_ptr[row + 1]; ++q) acc = cadd(acc, far_value(F, s0_reps[q], 0));
-            } else {
-                acc = cadd(acc, far_value(F, row, 0));
+            for (int u = 0; u < U; ++u) v[u] = ld_nt(v0 + j + u * 64);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int cb = 0; cb < RB; ++cb) acc[cb] = cfma(v[u], xs[cb * len + j + u * 64], acc[cb]);
+        }
+        for (; j < len; j += 64) {
+            const double2 v = ld_nt(v0 + j);
+#pragma unroll
+            for (int cb = 0; cb < RB; ++cb) acc[cb] = cfma(v, xs[cb * len + j], acc[cb]);
+        }
+#pragma unroll
+        for (int cb = 0; cb < RB; ++cb) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                acc[cb].x += __shfl_xor(acc[cb].x, off, 64);
+                acc[cb].y += __shfl_xor(acc[cb].y, off, 64);
+            }
+            // (each column's far values by a lane of its own)
+            if (lane == cb && c0 + cb < ncol) {
+                double2 a = acc[cb];
+                if (F.leafbuf) {
+                    if (s0_ptr) {
+                        for (int q = s0_ptr[row]; q < s0_ptr[row + 1]; ++q)
+                            a = cadd(a, far_value(F, s0_reps[q], c0 + cb));
+                    } else {
+                        a = cadd(a, far_value(F, row, c0 + cb));
+                    }
+                }
+                y[int64_t(c0 + cb) * nrows + row] = a;
             }
         }
-        y[row] = acc;
     }
 }
 
@@ -3744,6 +3773,18 @@ static igb_status matvec_launches(igb_op op, const MatvecWork& W, const double* 
     const int64_t* rco = op->d_row_coff.as<int64_t>();
     const int* dcl = op->d_dcol.as<int>();
     const double2* vl = op->d_val.as<double2>();
+    // columns per pass of the product by groups: as many as fit the LDS (at most 8), in
+    // passes of equal width; none where a single column does not fit, or (several columns)
+    // fewer than two, or too few workgroups hide the passes' latency (level-3 sphere, 38
+    // workgroups, 15 columns: 28 against 26 us; level 4, over 100 workgroups: 53 against 94)
+    int group_cols = 0;
+    if (use_near && !op->near_wgs.empty() && (ncol == 1 || op->near_wgs.size() >= NEAR_GROUP_MIN_WGS)) {
+        const int fit = int(std::min<size_t>(8, size_t(g->ctx->lds_max) / (size_t(op->near_list_max) * sizeof(double2))));
+        if (fit >= std::min(ncol, 2)) {
+            const int passes = (ncol + fit - 1) / fit;
+            group_cols = (ncol + passes - 1) / passes;
+        }
+    }
     if (low && op->d_val_lo.ptr) {
         const int ncb = (ncol + 15) / 16;
         float2* xt = W.xnear_lo;
@@ -3766,12 +3807,23 @@ static igb_status matvec_launches(igb_op op, const MatvecWork& W, const double* 
         if (far || !use_near)
             hipLaunchKernelGGL(add_far, dim3(blocks_for(N * ncol, 256)), dim3(256), 0, s, yfar, s0p, s0r, use_near, N,
                                ncol, Y);
-    } else if (ncol == 1 && use_near && !op->near_wgs.empty() &&
-               size_t(op->near_list_max) * sizeof(double2) <= size_t(g->ctx->lds_max)) {
-        hipLaunchKernelGGL(spmv_groups<NEAR_GROUP_ROWS>, dim3(unsigned(op->near_wgs.size())),
-                           dim3(64 * NEAR_GROUP_ROWS), size_t(op->near_list_max) * sizeof(double2), s,
-                           op->d_near_wgs.as<NearGroupWG>(), op->d_near_grp_rows.as<int>(), rp, dcl, vl, X, yfar,
-                           s0p, s0r, Y);
+    } else if (group_cols > 0) {
+        auto kern = [&] {
+            switch (group_cols) {
+                case 1: return spmv_groups<NEAR_GROUP_ROWS, 1>;
+                case 2: return spmv_groups<NEAR_GROUP_ROWS, 2>;
+                case 3: return spmv_groups<NEAR_GROUP_ROWS, 3>;
+                case 4: return spmv_groups<NEAR_GROUP_ROWS, 4>;
+                case 5: return spmv_groups<NEAR_GROUP_ROWS, 5>;
+                case 6: return spmv_groups<NEAR_GROUP_ROWS, 6>;
+                case 7: return spmv_groups<NEAR_GROUP_ROWS, 7>;
+                default: return spmv_groups<NEAR_GROUP_ROWS, 8>;
+            }
+        }();
+        hipLaunchKernelGGL(kern, dim3(unsigned(op->near_wgs.size())), dim3(64 * NEAR_GROUP_ROWS),
+                           size_t(op->near_list_max) * group_cols * sizeof(double2), s,
+                           op->d_near_wgs.as<NearGroupWG>(), op->d_near_grp_rows.as<int>(), rp, dcl, vl, X, N, ncol,
+                           yfar, s0p, s0r, Y);
     } else if (ncol == 1) {
         hipLaunchKernelGGL(spmv_combine<1>, sg, sb, 0, s, rp, rco, dcl, vl, X, N, yfar, s0p, s0r, use_near,
                            ncol, Y);
