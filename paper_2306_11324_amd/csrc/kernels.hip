@@ -3929,8 +3929,11 @@ igb_status farfield_device(igb_op op, const double* coeffs, int ndir, const doub
         return st;
     // the segments' sums go where the right-hand side's element contributions do
     const int64_t room = g->nelem * (g->p + 1) * (g->p + 1);
-    const int nseg = layer_segments(npts, nobs, room);
-    if (nseg > 1 && (st = op_reserve(op, op->d_q_loc, size_t(ndir) * room * sizeof(double2), "farfield"))) return st;
+    int nseg = layer_segments(npts, nobs, room);
+    if (nseg > 1 && op_reserve(op, op->d_q_loc, size_t(ndir) * room * sizeof(double2), "farfield")) {
+        (void)hipGetLastError();
+        nseg = 0;   // without room for them the form that needs none
+    }
     IGB_HIP(hipStreamSynchronize(s));   // earlier work on s may still read these buffers
     IGB_HIP(hipMemcpy(op->d_q_obs.ptr, on.data(), on.size() * sizeof(double), hipMemcpyHostToDevice));
     const DevBuf& d_obs = op->d_q_obs;
@@ -3989,7 +3992,10 @@ igb_status potential_device(igb_op op, const double* coeffs, int ndir, const dou
         return st;
     // segments' sums, at most half of the densities; without room for them one segment
     int nseg = layer_segments(npts, npt, npts / 2);
-    if (nseg > 1 && alloc(d_part, size_t(nseg) * ndir * npt * sizeof(double2), nullptr)) nseg = 1;
+    if (nseg > 1 && alloc(d_part, size_t(nseg) * ndir * npt * sizeof(double2), nullptr)) {
+        (void)hipGetLastError();
+        nseg = 1;
+    }
     auto sum = hard ? launch_layer_sum<SUM_POT_HARD> : launch_layer_sum<SUM_POT_SOFT>;
     sum(d_geo.as<double>(), d_dens.as<double2>(), npts, d_pts.as<double>(), npt, op->kappa, ndir, nseg,
         d_part.as<double2>(), reinterpret_cast<double2*>(u), s);
@@ -4079,7 +4085,10 @@ igb_status potential_h2_device(igb_op op, const double* coeffs, int ndir, const 
                              int64_t(P.near_leaf.size()) * (nqtot / clusters_on_level(g->npatch, lmax))) / nbox;
     int parts = int(std::max<int64_t>(1, std::min<int64_t>({32, (POT_WORKGROUPS + nbox - 1) / nbox, sources / (2 * POT_TILE)})));
     DevBuf d_part;   // (without room for the parts' sums: one part)
-    if (parts > 1 && alloc(d_part, size_t(parts) * ndir * npt * sizeof(double2), nullptr)) parts = 1;
+    if (parts > 1 && alloc(d_part, size_t(parts) * ndir * npt * sizeof(double2), nullptr)) {
+        (void)hipGetLastError();
+        parts = 1;
+    }
     double2* sum = parts > 1 ? d_part.as<double2>() : reinterpret_cast<double2*>(u);
     hipLaunchKernelGGL(hard ? pot_l2p_near<true> : pot_l2p_near<false>, dim3(unsigned(nbox), unsigned(ndir), unsigned(parts)),
                        dim3(POT_LEAF_POINTS), 0, s,
