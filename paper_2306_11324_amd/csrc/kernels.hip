@@ -2270,7 +2270,7 @@ __global__ __launch_bounds__(64 * NEAR64_WAVES) void near_tiles_mfma64(Near64Arg
 // kernel's time.  The near workgroups come first, the coupling's waves (a row
 // tile of a chunk's NM column tiles each) fill what they leave.  Level-5 sphere,
 // leaf depth 3, 64 columns, of which the matrix cores' share is 293 us:
-// 472 us in two launches, 400 in one (the whole product 500 and 437).
+// 472 us in two launches, 420 in one by the profiler (the whole product 500 and 436).
 template <int NN, int NM>
 __global__ __launch_bounds__(64 * NEAR64_WAVES, 4) void near_far_mfma64(Near64Args A, int near_wgs8, M2l64Args M) {
     __shared__ Near64Lds<NN> lds;
