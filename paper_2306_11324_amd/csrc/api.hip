@@ -142,10 +142,6 @@ igb_status dev_malloc(DevBuf& b, size_t bytes, const char* who) {
         set_error("%s: hipMalloc of %zu bytes: %s", who, bytes, hipGetErrorString(e));
         return IGB_ERR_HIP;
     }
-#ifdef IGB_POISON
-    (void)hipMemset(b.ptr, 0xff, bytes);
-    (void)hipDeviceSynchronize();
-#endif
     b.bytes = bytes;
     b.kept = size;
     b.ctx = c;
