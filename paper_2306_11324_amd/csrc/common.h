@@ -439,7 +439,6 @@ igb_status potential_device(igb_op op, const double* coeffs, int ndir, const dou
 // Extra Gauss points per direction for a wavenumber-scaled size kd = kappa * diameter:
 // one more for each doubling of kd beyond 1.5 (oscillation of e^{i kappa r} across it).
 inline int kd_boost(double kd) { return (kd >= 1.5) + (kd >= 3.0) + (kd >= 6.0); }
-constexpr int REG_POINTS_MAX = 100;  // Gauss points per element of a regular near pair
 // Extra points per direction of the touching-pair rules for elements much longer
 // in one direction than in the other (the rules see the singularity through the
 // reference square, where such an element squeezes it along one axis).

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "common.h"
+#include "near_rules.h"
 #include "quadrature_device.h"
 
 namespace igb {
@@ -186,9 +187,7 @@ __device__ __forceinline__ int regular_points(int code) {
     const int nx = (code & 15) * ((code >> 4) & 15), ny = ((code >> 8) & 15) * (code >> 12);
     return nx > ny ? nx : ny;
 }
-constexpr int REG_POINTS_SMALL = 36;   // rules of up to 6 x 6 points take the form with less LDS
 constexpr int REG_SEG = 256;           // pairs per workgroup
-constexpr int REG_ORDER_MAX = 12;
 
 // point data of a regular rule: g[0..6] = x, n~, |n~|; sound-hard also F_s, F_t
 template <bool HARD>
@@ -256,14 +255,14 @@ __device__ __forceinline__ void surface_point(const ElemRef& R, double s, double
 template <int P, bool HARD, int MX>
 __global__ __launch_bounds__(64, 2) void near_regular(NearArgs A, int e0) {
     constexpr int P1 = P + 1, NL = P1 * P1, NV = HARD ? 4 : 1, NG = HARD ? 13 : 7, ND = HARD ? 2 * P1 : P1;
-    constexpr int YC = MX <= 64 ? 64 : MX;   // source points per batch (at least one source)
+    constexpr int YC = regular_batch_points(MX);   // source points per batch (at least one source)
     static_assert(MX % 4 == 0 && MX <= REG_POINTS_MAX, "padded points of a rule");
     __shared__ unsigned short code[REG_SEG], list[REG_SEG];
     __shared__ double xg[MX][NG], yg[YC][NG];
     __shared__ double px[HARD ? 1 : MX][NL], py[HARD ? 1 : YC][NL];   // sound-soft: w phi at the test and source points
     __shared__ double bx[2 * REG_ORDER_MAX][ND];          // 1-D basis values (then derivatives) at the test points: u, v
-    __shared__ double by[64][ND];                         // the same per source of a batch: [source][u, v]
-    __shared__ int lsrc[16], lslot[16];
+    __shared__ double by[REG_BASIS_ROWS][ND];             // the same per source of a batch: [source][u, v]
+    __shared__ int lsrc[REG_BATCH_MAX], lslot[REG_BATCH_MAX];
     const int e = e0 + blockIdx.x, lane = threadIdx.x, li = lane & 15, g = lane >> 4;
     const int lc = min(li, NL - 1), lu = lc % P1, lv = lc / P1;   // basis index of this lane (past NL: not read)
     const int64_t kb = A.slots.near_ptr[e] + int64_t(blockIdx.y) * REG_SEG;
@@ -304,7 +303,7 @@ __global__ __launch_bounds__(64, 2) void near_regular(NearArgs A, int e0) {
         const int cur = next;
         if (cur == NONE) break;
         const int nxu = cur & 15, nxv = (cur >> 4) & 15, nyu = (cur >> 8) & 15, nyv = cur >> 12;
-        const int nx = nxu * nxv, ny = nyu * nyv, nx4 = (nx + 3) & ~3, ny4 = (ny + 3) & ~3, n1 = nyu + nyv;
+        const int nx = nxu * nxv, ny = nyu * nyv, nx4 = regular_padded(nx), ny4 = regular_padded(ny), n1 = nyu + nyv;
         const double *gxu = A.gl + nxu * 2 * NGMAX, *gxv = A.gl + nxv * 2 * NGMAX;
         const double *gyu = A.gl + nyu * 2 * NGMAX, *gyv = A.gl + nyv * 2 * NGMAX;
         __syncthreads();   // the rule before is done with the LDS
@@ -332,7 +331,7 @@ __global__ __launch_bounds__(64, 2) void near_regular(NearArgs A, int e0) {
                 const int i = t / NL, a = t % NL;
                 px[i][a] = i < nx ? bx[i % nxu][a % P1] * bx[nxu + i / nxu][a / P1] : 0.0;
             }
-        const int nbmax = min(16, YC / ny4);
+        const int nbmax = regular_batch(MX, nyu, nyv);
         const int invx = (65536 + nxu - 1) / nxu, invy = (65536 + nyu - 1) / nyu;   // i / n = i * inv >> 16 for i < 144
         for (int s0 = 0; s0 < nsrc; s0 += nbmax) {
             const int nb = min(nbmax, nsrc - s0), je = nb * ny4;

@@ -8,6 +8,7 @@
 #include <map>
 
 #include "common.h"
+#include "near_rules.h"
 
 namespace igb {
 
@@ -261,7 +262,7 @@ static int regular_order(double r) {
 //             bits 16..19 / 20..23: the same on the trial element
 //   touching: bits 16..18: square symmetry of the test element, 20..22: of the trial element
 // Regular orders per direction (regular_order), raised with kappa * diagonal and
-// quad_extra, each in [2, 12] and at most REG_POINTS_MAX points per element (the
+// quad_extra, each in [2, REG_ORDER_MAX] and at most REG_POINTS_MAX points per element (the
 // shorter direction gives way).
 igb_status near_classify(igb_op op) {
     igb_geom g = op->geom;
@@ -333,8 +334,8 @@ igb_status near_classify(igb_op op) {
                     const int64_t el = x ? f : e;
                     int nu = regular_order(dist / (std::sqrt(2.0) * side[2 * el])) + raise;
                     int nv = regular_order(dist / (std::sqrt(2.0) * side[2 * el + 1])) + raise;
-                    nu = std::max(2, std::min(nu, 12));
-                    nv = std::max(2, std::min(nv, 12));
+                    nu = std::max(2, std::min(nu, REG_ORDER_MAX));
+                    nv = std::max(2, std::min(nv, REG_ORDER_MAX));
                     if (nu * nv > REG_POINTS_MAX) {
                         if (nu >= nv)
                             nv = REG_POINTS_MAX / nu;
