@@ -43,21 +43,34 @@ __device__ __forceinline__ double rsqrt_fast(double x) {
     return fma(y * h, fma(h, 0.375, 0.5), y);
 }
 
-// sin(x) and cos(x) to about an ulp of 1 for |x| < 2^50: x reduced by the nearest
-// multiple of pi/2 (read off the low bits of x 2/pi + 1.5 2^52) in two fused
-// steps with pi/2 = A + B to 107 bits, then polynomials on [-pi/4, pi/4]
+// the 32-bit words of a double
+struct Words {
+    unsigned lo, hi;
+};
+__host__ __device__ __forceinline__ unsigned low_word(double x) { return __builtin_bit_cast(Words, x).lo; }
+__host__ __device__ __forceinline__ unsigned high_word(double x) { return __builtin_bit_cast(Words, x).hi; }
+__host__ __device__ __forceinline__ double from_words(unsigned hi, unsigned lo) {
+    return __builtin_bit_cast(double, Words{lo, hi});
+}
+
+// sin(x) and cos(x) to 2e-16 for |x| < 2^48 and 1e-15 for |x| < 2^50: x reduced by
+// the nearest multiple of pi/2 (read off the low bits of x 2/pi + 1.5 2^52) in two
+// fused steps with pi/2 = A + B to 107 bits, then polynomials on [-pi/4, pi/4]
 // (interpolants of (sin r - r)/r^3 and (cos r - 1 + r^2/2)/r^4 in r^2 at six
 // Chebyshev points; truncation below 1.4e-17).  Without the libm function's
-// branch for huge arguments: beyond 2^50, where the spacing of doubles
-// approaches a radian, the values are only bounded (the reduced argument is
-// clamped).  About 35 instructions.
-__device__ __forceinline__ void sincos_fast(double x, double& sn, double& cs) {
+// branch for huge arguments: from 2^44 the rounding of 2/pi can pick the
+// neighbouring multiple, which leaves |r| a little above pi/4 (up to 0.85 at 2^50);
+// from 2^51, where the spacing of doubles approaches a radian, the values are only
+// bounded: an |r| above 1 has its high word cleared, which leaves 0 (a comparison and
+// one select, the price of two clamps; unlike fmin and fmax they leave a NaN a
+// NaN, and NaN and infinite arguments give NaN).  About 35 instructions.
+__host__ __device__ __forceinline__ void sincos_fast(double x, double& sn, double& cs) {
     const double MAGIC = 6755399441055744.0;   // 1.5 * 2^52
     const double t = fma(x, 0x1.45f306dc9c883p-1, MAGIC);
     const double n = t - MAGIC;
     double r = fma(n, -0x1.921fb54442d18p+0, x);
     r = fma(n, -0x1.1a62633145c07p-54, r);
-    r = fmin(fmax(r, -0.7863), 0.7863);
+    r = from_words(fabs(r) > 1.0 ? 0u : high_word(r), low_word(r));
     const double z = r * r;
     double S = fma(z, 0x1.5e0af186af739p-33, -0x1.ae600a926c89ap-26);
     S = fma(z, S, 0x1.71de37961e4c6p-19);
@@ -71,10 +84,10 @@ __device__ __forceinline__ void sincos_fast(double x, double& sn, double& cs) {
     C = fma(z, C, -0x1.6c16c16c16966p-10);
     C = fma(z, C, 0x1.5555555555555p-5);
     const double c = fma(z * z, C, fma(z, -0.5, 1.0));
-    const int q = __double2loint(t);
+    const unsigned q = low_word(t);
     const double a = (q & 1) ? c : s, b = (q & 1) ? s : c;
-    sn = __hiloint2double(__double2hiint(a) ^ ((q & 2) << 30), __double2loint(a));
-    cs = __hiloint2double(__double2hiint(b) ^ (((q + 1) & 2) << 30), __double2loint(b));
+    sn = from_words(high_word(a) ^ ((q & 2) << 30), low_word(a));
+    cs = from_words(high_word(b) ^ (((q + 1) & 2) << 30), low_word(b));
 }
 
 // Bernstein polynomials of degree p <= 3 on [0,1] and their derivatives
