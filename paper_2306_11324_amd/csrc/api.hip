@@ -7,7 +7,6 @@
 #include <cstring>
 #include <mutex>
 #include <new>
-#include <system_error>
 #include <thread>
 
 #include "common.h"
@@ -374,11 +373,8 @@ static Coefs coefs_for(const igb_op_params* prm) {
 
 // One H^2 matrix: tree, near field, couplings (everything but the composite case)
 static igb_status build_one(igb_ctx ctx, igb_geom g, const igb_op_params* prm, const Coefs& c, igb_op* out) {
-    igb_op op = new (std::nothrow) igb_op_s();
-    if (!op) {
-        set_error("assemble_nearfield: out of host memory");
-        return IGB_ERR_ARG;
-    }
+    std::unique_ptr<igb_op_s> owned(new igb_op_s());   // until it is built
+    const igb_op op = owned.get();
     op->geom = g;
     op->prm = *prm;
     op->kappa = prm->kappa;
@@ -394,23 +390,33 @@ static igb_status build_one(igb_ctx ctx, igb_geom g, const igb_op_params* prm, c
     op->nq = (prm->q + 1) * (prm->q + 1);
     op->N = op->bc == IGB_SOFT ? g->n2 : g->n0;
     igb_status st;
-    st = tree_build(op);
-    if (!st) {
+    if ((st = tree_build(op))) return st;
+    {
         // the pattern and the quadrature classes need the tree alone: side by side
+        // (joined on every path; what the pattern throws is thrown here)
         igb_status sp = IGB_OK;
-        std::thread pattern;
+        std::exception_ptr lost;
+        struct Joined {
+            std::thread t;
+            ~Joined() {
+                if (t.joinable()) t.join();
+            }
+        } pattern;
         try {
-            pattern = std::thread([&] { sp = near_pattern(op); });
-        } catch (const std::system_error&) {   // no thread to be had: one after the other
+            pattern.t = std::thread([&]() noexcept {
+                try {
+                    sp = near_pattern(op);
+                } catch (...) {
+                    lost = std::current_exception();
+                }
+            });
+        } catch (const std::exception&) {   // no thread to be had: one after the other
             sp = near_pattern(op);
         }
         st = near_classify(op);
-        if (pattern.joinable()) pattern.join();
-        if (!st) st = sp;
-    }
-    if (st) {
-        delete op;
-        return st;
+        if (pattern.t.joinable()) pattern.t.join();
+        if (lost) std::rethrow_exception(lost);
+        if (st || (st = sp)) return st;
     }
     // device bytes of the operator (checked against the budget before allocating)
     const int nl = (g->p + 1) * (g->p + 1);
@@ -446,26 +452,32 @@ static igb_status build_one(igb_ctx ctx, igb_geom g, const igb_op_params* prm, c
     if (!budget_ok(ctx, need + transient)) {
         set_error("assemble_nearfield: HBM budget exceeded (%zu + %zu > %zu bytes)", ctx->used.load(),
                   need + transient, ctx->budget);
-        delete op;
         return IGB_ERR_BUDGET;
     }
     hipStream_t s = ctx->stream;
-    if (host_only(ctx)) {
-        ++g->refs;
-        *out = op;
-        return IGB_OK;
-    }
-    if ((st = assemble_near_device(op, s)) || (st = assemble_far_device(op, s)) || (st = alloc_work(op, 1))) {
-        delete op;
+    if (!host_only(ctx) &&
+        ((st = assemble_near_device(op, s)) || (st = assemble_far_device(op, s)) || (st = alloc_work(op, 1))))
         return st;
-    }
     ++g->refs;
-    *out = op;
+    *out = owned.release();
     return IGB_OK;
 }
 
+static igb_status assemble(igb_ctx ctx, igb_geom g, const igb_op_params* prm, igb_op* out);
 
+// what the host's allocator throws (on any thread of the plan) is an error of the call
 igb_status assemble_nearfield(igb_ctx ctx, igb_geom g, const igb_op_params* prm, igb_op* out) {
+    try {
+        return assemble(ctx, g, prm, out);
+    } catch (const std::bad_alloc&) {
+        set_error("assemble_nearfield: out of host memory");
+    } catch (const std::exception& e) {
+        set_error("assemble_nearfield: %s", e.what());
+    }
+    return IGB_ERR_ARG;
+}
+
+static igb_status assemble(igb_ctx ctx, igb_geom g, const igb_op_params* prm, igb_op* out) {
     if (!ctx || !g || !prm || !out) {
         set_error("assemble_nearfield: NULL argument");
         return IGB_ERR_ARG;
@@ -527,20 +539,15 @@ igb_status assemble_nearfield(igb_ctx ctx, igb_geom g, const igb_op_params* prm,
         c0.hmix = HardMix{make_double2(-1.0, 0), make_double2(0, 0)};
         c1.hmix = HardMix{make_double2(0, 0), make_double2(1.0, 0)};
     }
-    igb_op p0 = nullptr, p1 = nullptr;
+    struct Part {   // until the sum holds them
+        igb_op op = nullptr;
+        ~Part() { igb_op_destroy(op); }
+    } h0, h1;
     igb_status st;
-    if ((st = build_one(ctx, g, prm, c0, &p0))) return st;
-    if ((st = build_one(ctx, g, prm, c1, &p1))) {
-        igb_op_destroy(p0);
-        return st;
-    }
-    igb_op op = new (std::nothrow) igb_op_s();
-    if (!op) {
-        igb_op_destroy(p0);
-        igb_op_destroy(p1);
-        set_error("assemble_nearfield: out of host memory");
-        return IGB_ERR_ARG;
-    }
+    if ((st = build_one(ctx, g, prm, c0, &h0.op)) || (st = build_one(ctx, g, prm, c1, &h1.op))) return st;
+    const igb_op p0 = h0.op, p1 = h1.op;
+    std::unique_ptr<igb_op_s> owned(new igb_op_s());
+    const igb_op op = owned.get();
     op->geom = g;
     op->prm = *prm;
     op->kappa = prm->kappa;
@@ -561,8 +568,9 @@ igb_status assemble_nearfield(igb_ctx ctx, igb_geom g, const igb_op_params* prm,
     op->sum_coef = {make_double2(1.0, 0.0), make_double2(0.0, -c.eta)};
     op->estimated_data = p0->estimated_data + p1->estimated_data;
     op->estimated_bytes = solve_model_bytes(op, 30, 1);
+    h0.op = h1.op = nullptr;
     ++g->refs;
-    *out = op;
+    *out = owned.release();
     return IGB_OK;
 }
 

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <exception>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -497,7 +498,9 @@ inline int64_t clusters_on_level(int npatch, int l) { return int64_t(npatch) << 
 int host_threads();
 
 // f(i) for every i in [0, n), in blocks of `grain` handed out dynamically to
-// host_threads() threads (the calling thread is one of them).
+// host_threads() threads (the calling thread is one of them; those that cannot be
+// started are done without).  An exception of f ends the loop on every thread and is
+// thrown to the caller once all have ended.
 template <class F>
 void parallel_for(int64_t n, int64_t grain, const F& f) {
     const int64_t blocks = (n + grain - 1) / grain;
@@ -507,18 +510,29 @@ void parallel_for(int64_t n, int64_t grain, const F& f) {
         return;
     }
     std::atomic<int64_t> next{0};
-    auto run = [&]() {
-        for (;;) {
-            const int64_t a = next.fetch_add(grain);
-            if (a >= n) return;
-            const int64_t b = std::min(n, a + grain);
-            for (int64_t i = a; i < b; ++i) f(i);
+    std::atomic<bool> failed{false};
+    std::exception_ptr error;   // the first one
+    auto run = [&]() noexcept {
+        try {
+            while (!failed.load(std::memory_order_relaxed)) {
+                const int64_t a = next.fetch_add(grain);
+                if (a >= n) return;
+                const int64_t b = std::min(n, a + grain);
+                for (int64_t i = a; i < b; ++i) f(i);
+            }
+        } catch (...) {
+            if (!failed.exchange(true)) error = std::current_exception();
         }
     };
     std::vector<std::thread> pool;
-    for (int t = 1; t < nt; ++t) pool.emplace_back(run);
+    pool.reserve(nt - 1);
+    try {
+        for (int t = 1; t < nt; ++t) pool.emplace_back(run);
+    } catch (...) {
+    }
     run();
     for (auto& t : pool) t.join();
+    if (error) std::rethrow_exception(error);
 }
 
 // Chebyshev points of the first kind on [0,1]
