@@ -16,9 +16,10 @@
  *     stream, IGB_CONTEXT_STREAM = the context's own non-blocking stream) and
  *     return before the device work completes.
  *   - The caller owns every buffer it passes; the library copies what it keeps.
- *     Handles own their device memory until destroyed; they may be destroyed in
- *     any order (an operator keeps its geometry, a geometry its context alive
- *     until the last dependent handle is destroyed).  Calls on one operator
+ *     Handles own their device memory until destroyed (what the library may keep
+ *     of it afterwards, and how it is given back: igb_ctx_trim); they may be
+ *     destroyed in any order (an operator keeps its geometry, a geometry its
+ *     context alive until the last dependent handle is destroyed).  Calls on one operator
  *     (h2_matvec, cfie_rhs, cfie_solve, farfield, potential, potential_h2) use
  *     its internal work vectors and must not overlap; different operators may
  *     run concurrently on different streams.  Work buffers grow on demand and
@@ -247,6 +248,22 @@ igb_status igb_ctx_create(int device, size_t hbm_budget_bytes, igb_ctx* out);
 void igb_ctx_destroy(igb_ctx ctx);
 /* Bytes currently held by the context's geometries and operators. */
 size_t igb_ctx_used_bytes(igb_ctx ctx);
+/* Kept device memory.  On contexts without a budget, device memory blocks of 512
+ * MiB and more that are released (by destroyed operators and geometries, and the
+ * staging of an assembly) are not returned to the driver at once but kept for
+ * later blocks of the same size, on the device's contexts without a budget alike:
+ * at most 64 blocks and an eighth of the device's memory, and only while at
+ * least half of the device's memory is free when a block is released.  Other
+ * allocators of the process, and other processes, cannot use kept memory, and
+ * igb_ctx_used_bytes does not count it.  It is returned to the driver by
+ * igb_ctx_trim, when an allocation of the library fails (which is then tried
+ * again), when a block is released with less than half of the memory free, and
+ * when the device's last context is destroyed.
+ * igb_ctx_kept_bytes: bytes kept now on the context's device, for all of its
+ * contexts (0 for host-only contexts).  igb_ctx_trim: returns all of them.  Both
+ * may be called at any time from any thread. */
+size_t igb_ctx_kept_bytes(igb_ctx ctx);
+igb_status igb_ctx_trim(igb_ctx ctx);
 
 /* ---------------------------------------------------------------- geometry */
 

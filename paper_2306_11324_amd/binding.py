@@ -75,6 +75,8 @@ _SIGS = {
     "igb_ctx_create": (C.c_int, [C.c_int, C.c_size_t, C.POINTER(_P)]),
     "igb_ctx_destroy": (None, [_P]),
     "igb_ctx_used_bytes": (C.c_size_t, [_P]),
+    "igb_ctx_kept_bytes": (C.c_size_t, [_P]),
+    "igb_ctx_trim": (C.c_int, [_P]),
     "build_geometry": (C.c_int, [_P, C.POINTER(IgbPatch), C.c_int, C.c_int, C.c_int, C.POINTER(_P)]),
     "igb_geom_destroy": (None, [_P]),
     "igb_geom_dims": (C.c_int, [_P, C.POINTER(C.c_int64)]),
@@ -171,6 +173,14 @@ class Context:
 
     def used_bytes(self) -> int:
         return _lib.igb_ctx_used_bytes(self.h)
+
+    def kept_bytes(self) -> int:
+        """Device memory of released handles that the library keeps for later ones."""
+        return _lib.igb_ctx_kept_bytes(self.h)
+
+    def trim(self) -> None:
+        """Returns the kept device memory, for other allocators of the process."""
+        _check("igb_ctx_trim", _lib.igb_ctx_trim(self.h))
 
     def __del__(self, _destroy=_lib.igb_ctx_destroy):
         if getattr(self, "h", None):

@@ -32,12 +32,14 @@ bool charge(igb_ctx_s* c, size_t bytes) {
 // turn is 0.105 s an operator, but 0.1-3 s where their memory goes back to the
 // driver each time (it stalls at some 100 GB/s of allocations and frees; slower
 // assembly, 0.45 s an operator, did not meet it).  Contexts without a budget
-// only; blocks of POOL_MIN bytes and more (smaller ones don't stall, and keeping the
-// 191 MB of a level-3 operator slowed its near product of 15 columns, 26 -> 36 us,
-// though none of its arrays moved), POOL_BLOCKS of them and an eighth of the
+// only; blocks of POOL_MIN bytes and more (smaller ones don't stall.  The limit is a
+// workaround as well: keeping the 191 MB of a level-3 operator slowed its near product
+// of 15 columns, 26 -> 36 us, though none of its arrays moved; why was not found),
+// POOL_BLOCKS of them and an eighth of the
 // device's memory at most (the longest kept go first), and none while less
 // than half of the device's memory is free.  Everything kept is freed when an
-// allocation fails and with the device's last context.  A buffer is kept after a
+// allocation fails, on igb_ctx_trim (other allocators cannot ask for it) and with the
+// device's last context.  A buffer is kept after a
 // device synchronisation (hipFree implies one too), so a kept block is idle
 // whatever stream its last user or its next one runs on.
 namespace {
@@ -77,6 +79,20 @@ void pool_leave(int device) {
     if (DevPool* p = pool_of(device)) {
         std::lock_guard<std::mutex> lk(p->mu);
         if (--p->contexts == 0) p->clear();
+    }
+}
+
+static size_t pool_bytes(int device) {
+    DevPool* p = pool_of(device);
+    if (!p) return 0;
+    std::lock_guard<std::mutex> lk(p->mu);
+    return p->held;
+}
+
+static void pool_trim(int device) {
+    if (DevPool* p = pool_of(device)) {
+        std::lock_guard<std::mutex> lk(p->mu);
+        p->clear();
     }
 }
 
@@ -265,6 +281,17 @@ void geom_release(igb_geom g) {
 void igb_ctx_destroy(igb_ctx ctx) { ctx_release(ctx); }
 
 size_t igb_ctx_used_bytes(igb_ctx ctx) { return ctx ? ctx->used.load() : 0; }
+
+size_t igb_ctx_kept_bytes(igb_ctx ctx) { return ctx && !host_only(ctx) ? pool_bytes(ctx->device) : 0; }
+
+igb_status igb_ctx_trim(igb_ctx ctx) {
+    if (!ctx) {
+        set_error("igb_ctx_trim: NULL context");
+        return IGB_ERR_ARG;
+    }
+    if (!host_only(ctx)) pool_trim(ctx->device);
+    return IGB_OK;
+}
 
 igb_status build_geometry(igb_ctx ctx, const igb_patch* patches, int npatch, int level_m, int degree_p,
                           igb_geom* out) {
