@@ -432,7 +432,17 @@ igb_status cfie_solve(igb_op op, const double* dirs, int ndir, const igb_solve_p
  * columns (device coeffs [ndir][n]) at nobs unit directions (host obs
  * [nobs][3]) into the device array uinf [ndir][nobs].  Sound-soft:
  * u_inf(x) = -(1/4pi) int e^{-i kappa x.y} t(y); sound-hard:
- * u_inf(x) = -(i kappa/4pi) int (x.n_y) e^{-i kappa x.y} g(y).  Stream-ordered. */
+ * u_inf(x) = -(i kappa/4pi) int (x.n_y) e^{-i kappa x.y} g(y).  The directions are
+ * normalised here: IGB_ERR_ARG for a norm below 1e-12 or NaN; the values at a
+ * direction with an infinite component are NaN.  Ordered on the stream, and
+ * complete on return.
+ * Order of the sums (here, in potential and potential_h2): a column's values do
+ * not depend on the other columns; the number of directions or points of the call
+ * decides how the surface's points are split into partial sums, so the same
+ * target in calls of different size differs by rounding (1e-15 of the largest
+ * value measured).  Where device memory (or the budget) is short the columns go
+ * in passes, with the same values; where it does not hold the partial sums of
+ * one column, another order of the sums is taken, again within rounding. */
 igb_status farfield(igb_op op, const double* coeffs, int ndir, const double* obs, int nobs,
                     double* uinf, void* hip_stream);
 

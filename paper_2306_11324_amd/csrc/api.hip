@@ -129,7 +129,8 @@ igb_status dev_malloc(DevBuf& b, size_t bytes, const char* who) {
     if (bytes == 0) return IGB_OK;
     igb_ctx_s* c = alloc_ctx();
     if (c && !charge(c, bytes)) {
-        set_error("%s: HBM budget exceeded (%zu held + %zu > %zu bytes)", who, c->used.load(), bytes, c->budget);
+        if (who)
+            set_error("%s: HBM budget exceeded (%zu held + %zu > %zu bytes)", who, c->used.load(), bytes, c->budget);
         return IGB_ERR_BUDGET;
     }
     DevPool* p = c ? pool_of(c->device) : nullptr;
@@ -154,7 +155,8 @@ igb_status dev_malloc(DevBuf& b, size_t bytes, const char* who) {
     if (e != hipSuccess) {
         if (c) uncharge(c, bytes);
         b.ptr = nullptr;
-        set_error("%s: hipMalloc of %zu bytes: %s", who, bytes, hipGetErrorString(e));
+        if (who) set_error("%s: hipMalloc of %zu bytes: %s", who, bytes, hipGetErrorString(e));
+        else (void)hipGetLastError();
         return IGB_ERR_HIP;
     }
     b.bytes = bytes;

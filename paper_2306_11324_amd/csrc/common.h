@@ -99,7 +99,8 @@ struct DevBuf {
 
 // Releases b, then allocates `bytes` charged to alloc_ctx(): IGB_ERR_BUDGET
 // (message naming `who`) if that context's budget would be exceeded,
-// IGB_ERR_HIP if hipMalloc fails; b is empty after either.
+// IGB_ERR_HIP if hipMalloc fails; b is empty after either.  Without a `who`, for memory
+// that a call can do without, a failure leaves no message and no HIP error.
 igb_status dev_malloc(DevBuf& b, size_t bytes, const char* who);
 // a context of the device begins, ends (what is kept of released buffers goes with the last)
 void pool_enter(int device);
@@ -365,6 +366,13 @@ inline igb_status upload(DevBuf& b, const T* src, size_t n, size_t* acct) {
     if (acct) *acct += b.bytes;
     if (src) IGB_HIP(hipMemcpy(b.ptr, src, n * sizeof(T), hipMemcpyHostToDevice));
     return IGB_OK;
+}
+
+// A buffer for as many columns as can be had, `ncol` or halves of it down to 1, of
+// `bytes` each; returns their number (0: not one), without an error
+inline int alloc_columns(DevBuf& b, size_t bytes, int ncol) {
+    while (ncol > 0 && dev_malloc(b, bytes * ncol, nullptr)) ncol /= 2;
+    return ncol;
 }
 
 inline igb_status alloc(DevBuf& b, size_t bytes, size_t* acct) {

@@ -2470,8 +2470,11 @@ __device__ __forceinline__ double2 sum_kernel(const double* x, const double* g, 
 // few at a time in the wave's own LDS (the next ones loading meanwhile) and read
 // as broadcasts, so that a kernel value costs no global access and serves CB
 // columns.  The waves' sums are added in order, then the segments'
-// (layer_sum_reduce); both numbers are fixed by the targets and points alone,
-// so a column's result does not depend on the other columns.
+// (layer_sum_reduce); both numbers are fixed by the number of targets and points
+// alone, so a column's result does not depend on the other columns.  (Where memory
+// is short the columns go in passes, as many at a time as there is room for the
+// segments' sums of; only where there is none for one column is another form
+// taken, which differs by rounding.)
 // Bound by fp64 VALU issue (about 50 instructions per kernel value and 4 per
 // column), at 16 columns by the LDS broadcasts.  (A workgroup per target and
 // column, lanes over the points, with libm's sine and cosine per column
@@ -2597,9 +2600,16 @@ __global__ __launch_bounds__(256) void layer_sum_few(const double* __restrict__ 
     if (threadIdx.x == 0) out[int64_t(col) * ntgt + o] = red[0];
 }
 
+// part: room for the segments' sums of npass columns, several segments only
 template <int KIND>
 static void launch_layer_sum(const double* geo, const double2* dens, int64_t npts, const double* tgt, int ntgt,
-                             double kappa, int ncol, int nseg, double2* part, double2* out, hipStream_t s) {
+                             double kappa, int ncol, int nseg, double2* part, int npass, double2* out, hipStream_t s) {
+    if (nseg > 1 && ncol > npass) {
+        for (int c0 = 0; c0 < ncol; c0 += npass)
+            launch_layer_sum<KIND>(geo, dens + int64_t(c0) * npts, npts, tgt, ntgt, kappa, std::min(npass, ncol - c0),
+                                   nseg, part, npass, out + int64_t(c0) * ntgt, s);
+        return;
+    }
     if (nseg == 0) {
         hipLaunchKernelGGL((layer_sum_few<KIND>), dim3(unsigned(ntgt), unsigned(ncol)), dim3(256), 0, s, geo, dens, npts,
                            tgt, ntgt, kappa, out);
@@ -2776,7 +2786,8 @@ __device__ double2 pot_l2p(const double* x, const double* lo, const double* hi, 
 // per (box, column, part of the box's sources); each point takes a group of lanes,
 // as many as fit, that split every tile and add their partial sums in a fixed
 // order, then pot_parts_add adds the parts (their number is a matter of the plan),
-// so a column's result does not depend on the others.
+// so a column's result does not depend on the others (the exception as at layer_sum:
+// no memory for one column's parts).
 // (A staged source holds its position and the density with every factor that does
 // not depend on the point: 5 doubles sound-soft, 8 with the normal sound-hard.
 // Bound by fp64 VALU issue, about 55 instructions per kernel value; 200,000
@@ -2793,7 +2804,7 @@ __global__ __launch_bounds__(POT_LEAF_POINTS) void pot_l2p_near(
     const double2* __restrict__ lbox, int ncol, const int* __restrict__ m2p_ptr, const int* __restrict__ m2p_src,
     const double* __restrict__ nodes, const double2* __restrict__ xh, const int* __restrict__ near_ptr,
     const int* __restrict__ near_leaf, int d, int L, int nel1, int nqp, const double* __restrict__ geo,
-    const double2* __restrict__ dens, int64_t nqtot, double kappa, int npt, double2* __restrict__ u) {
+    const double2* __restrict__ dens, int64_t nqtot, double kappa, int npt, int col0, double2* __restrict__ u) {
     // the box expansion, the source tiles and the partial sums share the LDS (one after the other)
     constexpr int W = HARD ? 8 : 6;   // doubles per staged source (sound-soft: one unused)
     constexpr int LX = (QMAX + 1) * (QMAX + 1) * (QMAX + 1), TL = POT_TILE * W / 2;
@@ -2827,7 +2838,7 @@ __global__ __launch_bounds__(POT_LEAF_POINTS) void pot_l2p_near(
         }
         return cfma(z, make_double2(t[W - 2], t[W - 1]), acc);
     };
-    const int b = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
+    const int b = blockIdx.x, r = col0 + int(blockIdx.y), tid = threadIdx.x;
     const int q1 = q + 1, nq = q1 * q1, n3 = nq * q1;
     const bool has_far = lbox != nullptr;
     const double2* D = dens + int64_t(r) * nqtot;
@@ -2880,7 +2891,7 @@ __global__ __launch_bounds__(POT_LEAF_POINTS) void pot_l2p_near(
                 for (int k = lane; k < cnt; k += gs) acc = term(x, tg[k], acc);
             __syncthreads();
         }
-        double2* o = u + (part * ncol + r) * npt;
+        double2* o = u + (part * gridDim.y + blockIdx.y) * npt;
         if (gs == 1) {
             if (mine) o[pi] = acc;
         } else {
@@ -3927,12 +3938,26 @@ igb_status farfield_device(igb_op op, const double* coeffs, int ndir, const doub
         (st = op_reserve(op, op->d_q_geo, size_t(npts) * 8 * sizeof(double), "farfield")) ||
         (st = op_reserve(op, op->d_q_dens, size_t(ndir) * npts * sizeof(double2), "farfield")))
         return st;
-    // the segments' sums go where the right-hand side's element contributions do
+    // the segments' sums go where the right-hand side's element contributions do, which
+    // an operator keeps; on a context with a budget, if those were not made yet (or for
+    // fewer columns), to memory that is released on return, so that the call holds no
+    // more than its quadrature buffers after it
     const int64_t room = g->nelem * (g->p + 1) * (g->p + 1);
-    int nseg = layer_segments(npts, nobs, room);
-    if (nseg > 1 && op_reserve(op, op->d_q_loc, size_t(ndir) * room * sizeof(double2), "farfield")) {
-        (void)hipGetLastError();
-        nseg = 0;   // without room for them the form that needs none
+    int nseg = layer_segments(npts, nobs, room), npass = ndir;
+    DevBuf d_part;
+    double2* part = nullptr;
+    if (nseg > 1) {
+        const size_t column = size_t(nseg) * nobs * sizeof(double2);
+        if (g->ctx->budget == 0) (void)op_reserve(op, op->d_q_loc, size_t(ndir) * room * sizeof(double2), nullptr);
+        const size_t held = op->d_q_loc.bytes / column;
+        npass = int(std::min<size_t>(ndir, held));
+        part = op->d_q_loc.as<double2>();
+        if (npass < ndir)
+            if (const int n = alloc_columns(d_part, column, ndir); n > npass) {
+                npass = n;
+                part = d_part.as<double2>();
+            }
+        if (npass == 0) nseg = 0;   // without room for one column's the form that needs none
     }
     IGB_HIP(hipStreamSynchronize(s));   // earlier work on s may still read these buffers
     IGB_HIP(hipMemcpy(op->d_q_obs.ptr, on.data(), on.size() * sizeof(double), hipMemcpyHostToDevice));
@@ -3954,7 +3979,7 @@ igb_status farfield_device(igb_op op, const double* coeffs, int ndir, const doub
         return st;
     auto sum = hard ? launch_layer_sum<SUM_FAR_HARD> : launch_layer_sum<SUM_FAR_SOFT>;
     sum(d_geo.as<double>(), d_dens.as<double2>(), npts, d_obs.as<double>(), nobs, op->kappa, ndir,
-        nseg, op->d_q_loc.as<double2>(), reinterpret_cast<double2*>(uinf), s);
+        nseg, part, npass, reinterpret_cast<double2*>(uinf), s);
     IGB_HIP(hipGetLastError());
     IGB_HIP(hipStreamSynchronize(s));
     return IGB_OK;
@@ -3990,15 +4015,12 @@ igb_status potential_device(igb_op op, const double* coeffs, int ndir, const dou
              return IGB_OK;
          })))
         return st;
-    // segments' sums, at most half of the densities; without room for them one segment
-    int nseg = layer_segments(npts, npt, npts / 2);
-    if (nseg > 1 && alloc(d_part, size_t(nseg) * ndir * npt * sizeof(double2), nullptr)) {
-        (void)hipGetLastError();
-        nseg = 1;
-    }
+    // segments' sums, at most half of the densities; without room for one column's one segment
+    int nseg = layer_segments(npts, npt, npts / 2), npass = ndir;
+    if (nseg > 1 && (npass = alloc_columns(d_part, size_t(nseg) * npt * sizeof(double2), ndir)) == 0) nseg = 1;
     auto sum = hard ? launch_layer_sum<SUM_POT_HARD> : launch_layer_sum<SUM_POT_SOFT>;
     sum(d_geo.as<double>(), d_dens.as<double2>(), npts, d_pts.as<double>(), npt, op->kappa, ndir, nseg,
-        d_part.as<double2>(), reinterpret_cast<double2*>(u), s);
+        d_part.as<double2>(), npass, reinterpret_cast<double2*>(u), s);
     IGB_HIP(hipGetLastError());
     IGB_HIP(hipStreamSynchronize(s));
     return IGB_OK;
@@ -4084,22 +4106,27 @@ igb_status potential_h2_device(igb_op op, const double* coeffs, int ndir, const 
     const int64_t sources = (int64_t(P.m2p_src.size()) * nq +
                              int64_t(P.near_leaf.size()) * (nqtot / clusters_on_level(g->npatch, lmax))) / nbox;
     int parts = int(std::max<int64_t>(1, std::min<int64_t>({32, (POT_WORKGROUPS + nbox - 1) / nbox, sources / (2 * POT_TILE)})));
-    DevBuf d_part;   // (without room for the parts' sums: one part)
-    if (parts > 1 && alloc(d_part, size_t(parts) * ndir * npt * sizeof(double2), nullptr)) {
-        (void)hipGetLastError();
+    DevBuf d_part;   // the parts' sums of the columns of a pass (without room for one column's: one part)
+    int npass = ndir;
+    if (parts > 1 && (npass = alloc_columns(d_part, size_t(parts) * npt * sizeof(double2), ndir)) == 0) {
         parts = 1;
+        npass = ndir;
     }
-    double2* sum = parts > 1 ? d_part.as<double2>() : reinterpret_cast<double2*>(u);
-    hipLaunchKernelGGL(hard ? pot_l2p_near<true> : pot_l2p_near<false>, dim3(unsigned(nbox), unsigned(ndir), unsigned(parts)),
-                       dim3(POT_LEAF_POINTS), 0, s,
-                       d_pts.as<double>(), d_perm.as<int>(), d_bptr.as<int>(), d_blo.as<double>(), d_bhi.as<double>(),
-                       d_tch.as<double>(), q, any_far ? d_lbox.as<double2>() : nullptr, ndir, d_mptr.as<int>(),
-                       d_msrc.as<int>(), d_nodes.as<double>(), mom, d_nptr.as<int>(), d_nleaf.as<int>(),
-                       g->m - lmax, lmax, g->nel1, nqd * nqd, d_geo.as<double>(), d_dens.as<double2>(), nqtot,
-                       op->kappa, npt, sum);
-    if (parts > 1)
-        hipLaunchKernelGGL(pot_parts_add, dim3(unsigned((int64_t(ndir) * npt + 255) / 256)), dim3(256), 0, s, sum, parts,
-                           int64_t(ndir) * npt, reinterpret_cast<double2*>(u));
+    for (int c0 = 0; c0 < ndir; c0 += npass) {
+        const int nc = std::min(npass, ndir - c0);
+        double2* const uc = reinterpret_cast<double2*>(u) + int64_t(c0) * npt;
+        double2* const sum = parts > 1 ? d_part.as<double2>() : uc;
+        hipLaunchKernelGGL(hard ? pot_l2p_near<true> : pot_l2p_near<false>, dim3(unsigned(nbox), unsigned(nc), unsigned(parts)),
+                           dim3(POT_LEAF_POINTS), 0, s,
+                           d_pts.as<double>(), d_perm.as<int>(), d_bptr.as<int>(), d_blo.as<double>(), d_bhi.as<double>(),
+                           d_tch.as<double>(), q, any_far ? d_lbox.as<double2>() : nullptr, ndir, d_mptr.as<int>(),
+                           d_msrc.as<int>(), d_nodes.as<double>(), mom, d_nptr.as<int>(), d_nleaf.as<int>(),
+                           g->m - lmax, lmax, g->nel1, nqd * nqd, d_geo.as<double>(), d_dens.as<double2>(), nqtot,
+                           op->kappa, npt, c0, sum);
+        if (parts > 1)
+            hipLaunchKernelGGL(pot_parts_add, dim3(unsigned((int64_t(nc) * npt + 255) / 256)), dim3(256), 0, s, sum, parts,
+                               int64_t(nc) * npt, uc);
+    }
     IGB_HIP(hipGetLastError());
     IGB_HIP(hipStreamSynchronize(s));   // temporaries are freed on return
     return IGB_OK;
