@@ -348,8 +348,10 @@ igb_status igb_op_use_graphs(igb_op op, int enable);
  * coupling carries (every tile value read serves that many column tiles),
  * near_col_tiles = the same for the fp64 matrix-core near product; 1, 2 or 4,
  * or 0 for the automatic choice (coupling: the widest that keeps at least 512
- * workgroups; near product: 2 where that keeps 512 workgroups, else 1).  A value that does not divide a block's column tile count
- * falls back to the automatic choice for that block.  Every column's result
+ * workgroups; near product: 2 where that keeps 512 workgroups, else 1, and where
+ * it shares a launch with the coupling the widest that keeps 200 workgroups times
+ * the near field's share of the products).  A value that does not divide a
+ * block's column tile count falls back to the automatic choice for that block.  Every column's result
  * is bitwise the same for every shape.  Drops the operator's captured graphs.
  * IGB_ERR_ARG for other values. */
 igb_status igb_op_set_tile_shape(igb_op op, int coupling_col_tiles, int near_col_tiles);

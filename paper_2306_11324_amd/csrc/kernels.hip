@@ -3396,23 +3396,45 @@ static void launch_m2l_lo_t(igb_op op, const MatvecWork& W, const double2* xh, i
     (void)timer_mark(op, 0, s);
 }
 
+// share of the near tiles in the matrix-core products of a sound-soft fp64 block
+// (the coupling's rows padded to 16)
+static double near64_share(igb_op op) {
+    const double near = double(op->near_tile_vals), far = double(op->nfar) * op->nq * ((op->nq + 15) / 16 * 16);
+    return near / std::max(near + far, 1.0);
+}
+
+// Near products and coupling of such a block in one launch: where the near field is a
+// third of the products or more (level-5 star at leaf depth 2, 4% of them, 20 columns: 1262 us
+// apart, 1371 in one, as the coupling's waves then run in the larger workgroups of
+// the near field; above a third, 32 to 128 columns on spheres, stars and tori of levels 2 to 5: 2 to 22%
+// less in one) up to 0.95, beyond which the coupling has little to fill the gaps with (level-4
+// torus, p = 1, 0.998, 64 columns: 299 us apart, 290 in one; 32 columns: 179 and
+// 196) -- except for few near workgroups, where a launch less counts (level-3 torus,
+// 0.98, 200 workgroups of a column tile: 53 us apart, 47 in one).
+static bool near64_joint(igb_op op, int ncol) {
+    const double share = near64_share(op);
+    return share >= 1.0 / 3 && (share <= 0.95 || int64_t(op->near_tiles.size()) * ((ncol + 15) / 16) <= 512);
+}
+
 // near products of a block of ncol columns on the fp64 matrix cores: its columns
 // transposed into 16-wide rows, and the kernel's arguments; returns the column
-// tiles per workgroup (each tile value read serves 16 of them): `most` or 2 or 1
-// such that it divides the column tile count and the grid keeps at least 512
-// workgroups (2 per CU), or the tuned shape; the column results do not depend on it
-static int prepare_near64(igb_op op, const MatvecWork& W, const double2* X, double2* Y, int ncol, int most,
+// tiles per workgroup (each tile value read serves 16 of them), which divide the
+// column tile count; the column results do not depend on it.  A launch of its own: 2
+// where that keeps 512 workgroups (2 per CU), else 1.  Joint with the coupling: the most
+// of 4, 2, 1 that keeps 200 workgroups times the near share, as the fewer and longer
+// they are the more of the kernel's time the coupling has to fill (64 columns, 4 / 2 / 1 tiles:
+// level-4 sphere, 122 tiles, 0.36: 106 / 114 / 121 us; level-3 torus, 100 tiles, 0.98: 81 / 61 /
+// 66; level-2 torus, 36 tiles, 0.87: 44 / 36 / 32; level-5 sphere, 434 tiles, 0.86: 321 /
+// 329 / 388).  Or the tuned shape.
+static int prepare_near64(igb_op op, const MatvecWork& W, const double2* X, double2* Y, int ncol, bool joint,
                           hipStream_t s, Near64Args& A) {
     const int ncb = (ncol + 15) / 16;
     const int64_t ntile = int64_t(op->near_tiles.size());
     hipLaunchKernelGGL(columns_t64, dim3(unsigned((int64_t(ncb) * op->N * 16 + 255) / 256)), dim3(256), 0, s, X, op->N,
                        ncol, ncb, W.xnear64);
-    int nct = 1;
-    for (int c : {4, 2})
-        if (c <= most && ncb % c == 0 && (c == 4 || ntile * (ncb / c) >= 512)) {
-            nct = c;
-            break;
-        }
+    const double keep = joint ? 200 * near64_share(op) : 512;
+    int nct = joint ? 4 : 2;
+    while (nct > 1 && (ncb % nct != 0 || double(ntile * (ncb / nct)) < keep)) nct /= 2;
     if (op->tile_near_nct > 0 && ncb % op->tile_near_nct == 0) nct = op->tile_near_nct;   // tuned shape
     A = Near64Args{op->d_near_tiles.as<NearTile>(), ntile, ncb / nct, op->d_near_tile_cols.as<int>(),
                    op->d_val64.as<double2>(), W.xnear64, op->N, ncol, Y};
@@ -3716,14 +3738,10 @@ static igb_status matvec_launches(igb_op op, const MatvecWork& W, const double* 
         launch_m2m_levels(op->d_T.as<double>(), q, L, g->npatch, op->clu_off, xh, ncol, s, op->far_lmin, kinds, ks);
         if ((st = timer_mark(op, 2, s))) return st;
         int pkind = 0;
-        // one launch where the near field is a third of the products or more: level-5
-        // sphere at leaf depth 3 (61%) 503 -> 439 us at 64 columns, level-5 star (4%)
-        // 1262 -> 1371 us at 20, as the coupling's waves then run in the larger
-        // workgroups of the near field (timed apart when the operator profiles)
-        joint = near64 && use_near && !op->profile && !hard && m2l_kind(op, low, ncol) == 2 &&
-                op->near_tile_vals * 2 >= op->nfar * nq * ((nq + 15) / 16 * 16);
+        // (timed apart when the operator profiles)
+        joint = near64 && use_near && !op->profile && !hard && m2l_kind(op, low, ncol) == 2 && near64_joint(op, ncol);
         Near64Args na{};
-        const int nn = joint ? prepare_near64(op, W, X, Y, ncol, 4, s, na) : 0;
+        const int nn = joint ? prepare_near64(op, W, X, Y, ncol, true, s, na) : 0;
         if ((st = launch_m2l(op, W, xh, ks, low, ncol, joint ? &na : nullptr, nn, s, pkind))) return st;
         if ((st = timer_mark(op, 3, s))) return st;
         // (the stored fp64 tiles' products of blocks below 16 columns carry the target factors)
@@ -3809,9 +3827,8 @@ static igb_status matvec_launches(igb_op op, const MatvecWork& W, const double* 
                            op->d_val_lo.as<float2>(), xt, N, yfar, s0p, s0r, use_near, ncol, Y);
     } else if (near64) {
         if (use_near && !joint) {
-            // (4 column tiles a workgroup pay in the joint launch only)
             Near64Args A{};
-            const int nn = prepare_near64(op, W, X, Y, ncol, 2, s, A);
+            const int nn = prepare_near64(op, W, X, Y, ncol, false, s, A);
             auto kern = nn == 4 ? near_tiles_mfma64<4> : nn == 2 ? near_tiles_mfma64<2> : near_tiles_mfma64<1>;
             hipLaunchKernelGGL(kern, dim3(unsigned(A.ntile * A.ncg)), dim3(64 * NEAR64_WAVES), 0, s, A);
         }
