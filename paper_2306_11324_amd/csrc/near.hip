@@ -70,7 +70,7 @@ struct NearArgs {
     int64_t slot0;           // first staged pair
     double2* stage;          // [pairs][nloc*nloc], order: NearSlots
     int nel1;
-    double kappa, eta;       // eta: coupling of the sound-hard CFIE
+    double kappa;
     SoftMix mix;             // kernel of the sound-soft family
     HardMix hmix;            // kernel of the sound-hard family
     double2 cm;              // multiple of the mass matrix added on identical pairs
@@ -121,37 +121,6 @@ __device__ __forceinline__ KVal kernel_pair(const double* X, const double* NX, d
     k.s = cadd(cmul(hmix.ck, kk), cmul(hmix.cw, w));
     k.g = cmul(hmix.cw, g);
     return k;
-}
-
-// Point data of one element at local (s,t): position, n~, a and, per local basis
-// function, w*phi (component 0) and for the hypersingular part w*c with
-// c = d_s phi F_t - d_t phi F_s (components 1..3).
-template <int P, bool HARD>
-__device__ __forceinline__ void point_data(const ElemRef& R, const double* Cu, const double* Cv, double s,
-                                           double t, double w, double* g7, double* ph /*[NL][NV]*/) {
-    constexpr int NV = HARD ? 4 : 1;
-    GeoPt G;
-    eval_geo(R.bez, R.pu, R.pv, s, t, G);
-    double nt[3];
-    cross3(G.fs, G.ft, nt);
-    g7[0] = G.x[0]; g7[1] = G.x[1]; g7[2] = G.x[2];
-    g7[3] = nt[0]; g7[4] = nt[1]; g7[5] = nt[2];
-    g7[6] = sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
-    double bu[P + 1], bv[P + 1], dbu[P + 1], dbv[P + 1];
-    eval_basis1<P>(Cu, s, bu, dbu);
-    eval_basis1<P>(Cv, t, bv, dbv);
-#pragma unroll
-    for (int av = 0; av <= P; ++av)
-#pragma unroll
-        for (int au = 0; au <= P; ++au) {
-            double* o = ph + (av * (P + 1) + au) * NV;
-            o[0] = w * bv[av] * bu[au];
-            if (HARD) {
-                const double ds = bv[av] * dbu[au], dt = dbv[av] * bu[au];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) o[1 + c] = w * (ds * G.ft[c] - dt * G.fs[c]);
-            }
-        }
 }
 
 // --------------------------------------------------------------------------
@@ -457,13 +426,6 @@ __global__ __launch_bounds__(64, 2) void near_regular(NearArgs A, int e0) {
 // pairs): 79 -> 17 ms sound-soft, 287 -> 37.5 ms sound-hard (the sound-hard form
 // keeps 72 accumulators and runs one wave per SIMD).
 // --------------------------------------------------------------------------
-// Bernstein polynomials of compile-time degree
-template <int P>
-__device__ __forceinline__ void bern(double s, double* b) {
-    double db[4];
-    bernstein(P, s, b, db);
-}
-
 // entry (k, i) of the degree elevation from p to q >= p: b^q_k = sum_i E(k, i) b^p_i
 __device__ __forceinline__ double elevation(int p, int q, int k, int i) {
     constexpr double C[4][4] = {{1, 0, 0, 0}, {1, 1, 0, 0}, {1, 2, 1, 0}, {1, 3, 3, 1}};
@@ -1004,7 +966,6 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
     A.code = d_code.as<unsigned short>();
     A.nel1 = g->nel1;
     A.kappa = op->kappa;
-    A.eta = op->eta;
     A.mix = op->mix;
     A.hmix = op->hmix;
     A.cm = op->cm;

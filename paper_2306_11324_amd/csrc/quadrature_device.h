@@ -169,18 +169,6 @@ __device__ __forceinline__ void eval_basis1(const double* __restrict__ C, double
     }
 }
 
-__device__ __forceinline__ void d4_apply(int code, double s, double t, double& a, double& b) {
-    a = s;
-    b = t;
-    if (code & 4) {
-        double x = a;
-        a = b;
-        b = x;
-    }
-    if (code & 1) a = 1.0 - a;
-    if (code & 2) b = 1.0 - b;
-}
-
 struct ElemRef {
     const double* bez;
     int pu, pv, ex, ey;
