@@ -441,8 +441,9 @@ igb_status cfie_solve(igb_op op, const double* dirs, int ndir, const igb_solve_p
  * Order of the sums (here, in potential and potential_h2): a column's values do
  * not depend on the other columns; the number of directions or points of the call
  * decides how the surface's points are split into partial sums, so the same
- * target in calls of different size differs by rounding (1e-15 of the largest
- * value measured).  Where device memory (or the budget) is short the columns go
+ * target in calls of different size differs by rounding (at most 6e-15 of the
+ * largest value measured; potential_h2 besides by its interpolation error, as its
+ * boxes are made for the points of the call).  Where device memory (or the budget) is short the columns go
  * in passes, with the same values; where it does not hold the partial sums of
  * one column, another order of the sums is taken, again within rounding. */
 igb_status farfield(igb_op op, const double* coeffs, int ndir, const double* obs, int nobs,
