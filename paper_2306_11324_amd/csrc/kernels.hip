@@ -1806,7 +1806,6 @@ __global__ void m2l_reduce(const PT* part, const int* tgt_chunk_ptr, int64_t ncl
     yh[gid] = s;
 }
 
-constexpr size_t NEAR_GROUP_MIN_WGS = 64;   // fewer: several columns by spmv_combine
 constexpr int SPMV_U1 = 4;   // row strides in flight per lane of the one-column near product
 
 // y[r][row] = sum_j val x[r][col] (+ far part mapped to the solution space); one
@@ -3396,6 +3395,25 @@ static void launch_m2l_lo_t(igb_op op, const MatvecWork& W, const double2* xh, i
     (void)timer_mark(op, 0, s);
 }
 
+// Near product of 2 and more columns by row groups (spmv_groups, `cols` columns in each of
+// `passes`) or row by row (spmv_combine, 4 columns a pass), bitwise the same.  A
+// group's workgroup gathers its list once whatever rows it has, and its waves past
+// the rows idle, so what it does besides has to carry it: the near values per workgroup, times the
+// passes saved, 2000 for up to 5 columns a pass and 4000 for more (whose registers
+// leave a workgroup alone on its CU to the end).  us by rows / by groups:
+// level-5 sphere, leaf depth 1, p = 2 (1,480 values) 4 columns 25 / 24, 5 columns 37 / 25, 7 columns
+// 42 / 49; p = 1, sound-hard (267) 2 columns 14 / 34, 15 columns 52 / 259; level-4 star, p = 3,
+// leaf depth 1 (714) 15 columns 34 / 70; leaf depth 2, p = 1, sound-hard (3,590) 7 columns 80 / 75;
+// p = 2 (4,420) 15 columns 242 / 177.  Up to 256 workgroups, one a CU, are through in one round
+// (level-2 torus, leaf depth 1, p = 2, sound-hard, 250 workgroups, 640 values: 20 / 13), but fewer than 64
+// don't hide the passes' latency (level-3 sphere, 38 workgroups, 15 columns: 26 / 28).
+static bool near_by_groups(igb_op op, int ncol, int passes, int cols) {
+    const size_t wgs = op->near_wgs.size();
+    if (wgs <= 256) return wgs >= 64;
+    const double values = double(op->nnz) / double(wgs) * ((ncol + 3) / 4) / passes;
+    return values >= (cols <= 5 ? 2000 : 4000);
+}
+
 // share of the near tiles in the matrix-core products of a sound-soft fp64 block
 // (the coupling's rows padded to 16)
 static double near64_share(igb_op op) {
@@ -3804,14 +3822,14 @@ static igb_status matvec_launches(igb_op op, const MatvecWork& W, const double* 
     const double2* vl = op->d_val.as<double2>();
     // columns per pass of the product by groups: as many as fit the LDS (at most 8), in
     // passes of equal width; none where a single column does not fit, or (several columns)
-    // fewer than two, or too few workgroups hide the passes' latency (level-3 sphere, 38
-    // workgroups, 15 columns: 28 against 26 us; level 4, over 100 workgroups: 53 against 94)
+    // near_by_groups says no
     int group_cols = 0;
-    if (use_near && !op->near_wgs.empty() && (ncol == 1 || op->near_wgs.size() >= NEAR_GROUP_MIN_WGS)) {
+    if (use_near && !op->near_wgs.empty()) {
         const int fit = int(std::min<size_t>(8, size_t(g->ctx->lds_max) / (size_t(op->near_list_max) * sizeof(double2))));
         if (fit >= std::min(ncol, 2)) {
             const int passes = (ncol + fit - 1) / fit;
             group_cols = (ncol + passes - 1) / passes;
+            if (ncol > 1 && !near_by_groups(op, ncol, passes, group_cols)) group_cols = 0;
         }
     }
     if (low && op->d_val_lo.ptr) {
