@@ -70,6 +70,7 @@ struct NearArgs {
     int64_t slot0;           // first staged pair
     double2* stage;          // [pairs][nloc*nloc], order: NearSlots
     int nel1;
+    int seg;                 // pairs per workgroup of the regular kernel, at most REG_SEG
     double kappa;
     SoftMix mix;             // kernel of the sound-soft family
     HardMix hmix;            // kernel of the sound-hard family
@@ -156,7 +157,9 @@ __device__ __forceinline__ int regular_points(int code) {
     const int nx = (code & 15) * ((code >> 4) & 15), ny = ((code >> 8) & 15) * (code >> 12);
     return nx > ny ? nx : ny;
 }
-constexpr int REG_SEG = 256;           // pairs per workgroup
+constexpr int REG_SEG = 256;           // pairs per workgroup at most
+constexpr int REG_SEG_MIN = 16;        // and at least (a batch's sources), where there are few
+constexpr int REG_WAVES = 2048;        // waves that fill the device: 2 per SIMD
 
 // point data of a regular rule: g[0..6] = x, n~, |n~|; sound-hard also F_s, F_t
 template <bool HARD>
@@ -234,11 +237,11 @@ __global__ __launch_bounds__(64, 2) void near_regular(NearArgs A, int e0) {
     __shared__ int lsrc[REG_BATCH_MAX], lslot[REG_BATCH_MAX];
     const int e = e0 + blockIdx.x, lane = threadIdx.x, li = lane & 15, g = lane >> 4;
     const int lc = min(li, NL - 1), lu = lc % P1, lv = lc / P1;   // basis index of this lane (past NL: not read)
-    const int64_t kb = A.slots.near_ptr[e] + int64_t(blockIdx.y) * REG_SEG;
-    const int np = int(min(int64_t(REG_SEG), A.slots.near_ptr[e + 1] - kb));
+    const int64_t kb = A.slots.near_ptr[e] + int64_t(blockIdx.y) * A.seg;
+    const int np = int(min(int64_t(A.seg), A.slots.near_ptr[e + 1] - kb));
     if (np <= 0) return;
     const int tl = leaf_of(A.slots, e);
-    const int* src = A.leaf_src + A.leaf_src_ptr[tl] + int64_t(blockIdx.y) * REG_SEG;   // sources of the segment's pairs
+    const int* src = A.leaf_src + A.leaf_src_ptr[tl] + int64_t(blockIdx.y) * A.seg;   // sources of the segment's pairs
     const ElemRef Re = elem_ref(A.bez, A.pg, A.nel1, e);
     constexpr int NONE = 0xffff;   // (orders are at most 12: no rule has this code)
     int next = NONE;
@@ -991,7 +994,11 @@ static igb_status near_launch(igb_op op, hipStream_t s) {
         // regular pairs, a workgroup per target element and segment of its pairs
         int64_t longest = 0;
         for (int64_t e = e0; e < e1; ++e) longest = std::max(longest, op->near_ptr[e + 1] - op->near_ptr[e]);
-        const dim3 rgrid(unsigned(e1 - e0), unsigned((longest + REG_SEG - 1) / REG_SEG));
+        // (few elements: shorter segments until the waves fill the device, as a wave walks
+        // its pairs one batch after another; a pair's block does not depend on it)
+        A.seg = REG_SEG;
+        while (A.seg > REG_SEG_MIN && (e1 - e0) * ((longest + A.seg - 1) / A.seg) < REG_WAVES) A.seg /= 2;
+        const dim3 rgrid(unsigned(e1 - e0), unsigned((longest + A.seg - 1) / A.seg));
         hipLaunchKernelGGL((near_regular<P, HARD, REG_POINTS_SMALL>), rgrid, dim3(64), 0, s, A, int(e0));
         if (op->near_points_max > REG_POINTS_SMALL)
             hipLaunchKernelGGL((near_regular<P, HARD, REG_POINTS_MAX>), rgrid, dim3(64), 0, s, A, int(e0));
