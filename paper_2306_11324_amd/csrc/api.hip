@@ -421,8 +421,9 @@ static igb_status build_one(igb_ctx ctx, igb_geom g, const igb_op_params* prm, c
     igb_status st;
     if ((st = tree_build(op))) return st;
     {
-        // the pattern and the quadrature classes need the tree alone: side by side
-        // (joined on every path; what the pattern throws is thrown here)
+        // the pattern and the quadrature classes need the tree alone: side by side where
+        // they take longer than starting a thread (some ms for 10^6 pairs; joined on every
+        // path; what the pattern throws is thrown here)
         igb_status sp = IGB_OK;
         std::exception_ptr lost;
         struct Joined {
@@ -431,7 +432,9 @@ static igb_status build_one(igb_ctx ctx, igb_geom g, const igb_op_params* prm, c
                 if (t.joinable()) t.join();
             }
         } pattern;
-        try {
+        const bool beside = op->near_ptr[g->nelem] >= 1 << 16;
+        if (!beside) sp = near_pattern(op);
+        else try {
             pattern.t = std::thread([&]() noexcept {
                 try {
                     sp = near_pattern(op);

@@ -505,6 +505,13 @@ inline int64_t clusters_on_level(int npatch, int l) { return int64_t(npatch) << 
 // Host threads for the plan stages: the CPUs this process may run on, at most 16.
 int host_threads();
 
+// Items per block such that a block has some 16 thousand of the `steps` that all n items
+// take together (a step: a few ns; starting a thread takes some 30 us, so less work
+// than that stays on the calling thread)
+inline int64_t work_grain(int64_t n, int64_t steps) {
+    return std::max<int64_t>(1, int64_t(double(n) * 16384.0 / double(std::max<int64_t>(steps, 1))));
+}
+
 // f(i) for every i in [0, n), in blocks of `grain` handed out dynamically to
 // host_threads() threads (the calling thread is one of them; those that cannot be
 // started are done without).  An exception of f ends the loop on every thread and is

@@ -220,7 +220,7 @@ igb_status tree_build(igb_op op) {
         op->near_ptr[e + 1] = op->near_ptr[e] + op->leaf_src_ptr[lf + 1] - op->leaf_src_ptr[lf];
     }
     op->leaf_src.resize(op->leaf_src_ptr[nleaf]);
-    parallel_for(nleaf, 1, [&](int64_t lf) {
+    parallel_for(nleaf, work_grain(nleaf, 8 * op->leaf_src_ptr[nleaf]), [&](int64_t lf) {
         int* src = op->leaf_src.data() + op->leaf_src_ptr[lf];
         int64_t c = 0;
         for (int sl : near_leaf[lf]) {
@@ -458,13 +458,16 @@ igb_status near_pattern(igb_op op) {
     const int64_t ng = int64_t(order.size());
     std::vector<int64_t> list_off(ng + 1, 0);
     std::vector<std::vector<int>> lists(ng);
-    parallel_for(ng, 4, [&](int64_t i) {
+    int64_t merged = 0;
+    for (const Group* gr : order)
+        for (int lf : gr->first) merged += int64_t(leaf_cols[lf].size());
+    parallel_for(ng, work_grain(ng, merged), [&](int64_t i) {
         thread_local std::vector<int> tmp;
         merge(order[i]->first, lists[i], tmp);
     });
     for (int64_t i = 0; i < ng; ++i) list_off[i + 1] = list_off[i] + int64_t(lists[i].size());
     op->near_dcol.resize(list_off[ng]);
-    parallel_for(ng, 4, [&](int64_t i) {
+    parallel_for(ng, work_grain(ng, list_off[ng] / 4), [&](int64_t i) {
         std::copy(lists[i].begin(), lists[i].end(), op->near_dcol.begin() + list_off[i]);
         std::vector<int>().swap(lists[i]);
     });

@@ -43,12 +43,12 @@ int main() {
     prm.kappa = 2;
     prm.q = 3;
     prm.eta_adm = 1.6;
-    prm.leaf_depth = 1;
     int refused = 0;
     for (int separate = 0; separate < 2; ++separate)
         for (int bc = 0; bc < 2; ++bc) {
             prm.bc = bc;
             prm.separate = separate;
+            prm.leaf_depth = separate ? 1 : 3;   // (3: all pairs near, enough for the plan's threads)
             igb_op op;
             count = 0;
             fail_at = 1L << 40;
