@@ -1661,12 +1661,13 @@ __global__ __launch_bounds__(64 * NW) void m2l_chunks_lowrank(const double2* __r
 // One workgroup per (chunk, RB columns): thread (g, a) sums target node a over
 // the source nodes b = g mod NG, NG = 256 / nq groups, so that the lanes are full
 // at every degree (243 of 256 at q = 8, where one thread per node left 81 of
-// 128); the groups' sums meet in LDS in order.  A column's sums do not depend
-// on RB.
+// 128), but no more than there are source nodes (q = 1 and 2: 16 and 81 threads); the
+// groups' sums meet in LDS in order.  A column's sums do not depend on RB.
 // Bound by the tiles' HBM traffic (32 nq^2 bytes per pair) for a few columns.
 // Level-4 hard star, q = 8 (1.01 GB): one column 476 -> 224 us, 4 columns 642 ->
 // 500 us, 8 columns 1168 -> 778 us (before: one thread per node, 10 vectors).
 constexpr int HARD_VECS = 5;
+__host__ __device__ constexpr int hard_groups(int nq) { return 256 / nq < nq ? 256 / nq : nq; }
 template <int RB>
 __global__ __launch_bounds__(256) void m2l_hard_chunks(const double2* __restrict__ coup, const double2* __restrict__ xh,
                                                        int64_t kind_stride, const double* __restrict__ nodes,
@@ -1678,7 +1679,7 @@ __global__ __launch_bounds__(256) void m2l_hard_chunks(const double2* __restrict
     // source vectors xp, v_c [4][nq][RB] and nodes [nq][3]; afterwards the groups' sums [NG][nq][RB]
     extern __shared__ double2 sv[];
     const int64_t ch = blockIdx.x;
-    const int c0 = col0 + blockIdx.y * RB, tid = threadIdx.x, NG = 256 / nq;
+    const int c0 = col0 + blockIdx.y * RB, tid = threadIdx.x, nt = blockDim.x, NG = hard_groups(nq);
     const int g = min(tid / nq, NG - 1), a = min(tid - g * nq, nq - 1);   // (idle threads repeat a node)
     const int64_t p0 = chunk_pair[ch];
     const int len = chunk_len[ch], vs = nq * RB;
@@ -1698,7 +1699,7 @@ __global__ __launch_bounds__(256) void m2l_hard_chunks(const double2* __restrict
         const int64_t pr = p0 + i;
         const int64_t src = far_src_g[pr];
         __syncthreads();
-        for (int idx = tid; idx < vs; idx += 256) {
+        for (int idx = tid; idx < vs; idx += nt) {
             const int cb = idx % RB, b = idx / RB;
             const double* Y = nodes + (src * nq + b) * 16;
             double2 xp = make_double2(0, 0), xu = xp, xv = xp;
@@ -1743,7 +1744,7 @@ __global__ __launch_bounds__(256) void m2l_hard_chunks(const double2* __restrict
 #pragma unroll
             for (int cb = 0; cb < RB; ++cb) sv[(g * nq + a) * RB + cb] = acc[v][cb];
         __syncthreads();
-        for (int idx = tid; idx < vs; idx += 256) {
+        for (int idx = tid; idx < vs; idx += nt) {
             const int cb = idx % RB, b = idx / RB;
             double2 s = sv[idx];
             for (int h = 1; h < NG; ++h) s = cadd(s, sv[h * vs + idx]);
@@ -3326,9 +3327,10 @@ static void launch_m2l_fp64(igb_op op, const MatvecWork& W, double2* xh, int64_t
         for (int c0 = 0; c0 < ncol;) {
             const int left = ncol - c0, rb = left >= 3 ? 4 : left, nb = rb == 4 ? (left + 1) / 4 : 1;
             const size_t lds =
-                std::max<size_t>(size_t(4 * rb + 3), size_t(256 / op->nq) * rb) * op->nq * sizeof(double2);
+                std::max<size_t>(size_t(4 * rb + 3), size_t(hard_groups(op->nq)) * rb) * op->nq * sizeof(double2);
+            const int threads = (hard_groups(op->nq) * op->nq + 63) / 64 * 64;
             auto kern = rb == 1 ? m2l_hard_chunks<1> : rb == 2 ? m2l_hard_chunks<2> : m2l_hard_chunks<4>;
-            hipLaunchKernelGGL(kern, dim3(unsigned(nchunk), unsigned(nb)), dim3(256), lds, s, coup, xh, ks,
+            hipLaunchKernelGGL(kern, dim3(unsigned(nchunk), unsigned(nb)), dim3(threads), lds, s, coup, xh, ks,
                                op->d_nodes.as<double>(), op->d_far_src.as<int>(), C.d_tgt.as<int>(),
                                C.d_pair.as<int64_t>(), C.d_len.as<int>(), op->nq, ncol, c0, W.part);
             c0 += nb * rb;
