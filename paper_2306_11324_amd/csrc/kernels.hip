@@ -1679,11 +1679,11 @@ __global__ __launch_bounds__(256) void m2l_hard_chunks(const double2* __restrict
     // source vectors xp, v_c [4][nq][RB] and nodes [nq][3]; afterwards the groups' sums [NG][nq][RB]
     extern __shared__ double2 sv[];
     const int64_t ch = blockIdx.x;
-    const int c0 = col0 + blockIdx.y * RB, tid = threadIdx.x, nt = blockDim.x, NG = hard_groups(nq);
+    const int c0 = col0 + blockIdx.y * RB, tid = threadIdx.x, NG = hard_groups(nq);
     const int g = min(tid / nq, NG - 1), a = min(tid - g * nq, nq - 1);   // (idle threads repeat a node)
     const int64_t p0 = chunk_pair[ch];
     const int len = chunk_len[ch], vs = nq * RB;
-    double2* sn = sv + 4 * vs;
+    double2* sn = sv + 4 * vs;   // (workgroups of fewer than 256 threads have more than vs of them)
     double X[6];
     {
         const double* T = nodes + (int64_t(chunk_tgt[ch]) * nq + a) * 16;
@@ -1699,7 +1699,7 @@ __global__ __launch_bounds__(256) void m2l_hard_chunks(const double2* __restrict
         const int64_t pr = p0 + i;
         const int64_t src = far_src_g[pr];
         __syncthreads();
-        for (int idx = tid; idx < vs; idx += nt) {
+        for (int idx = tid; idx < vs; idx += 256) {
             const int cb = idx % RB, b = idx / RB;
             const double* Y = nodes + (src * nq + b) * 16;
             double2 xp = make_double2(0, 0), xu = xp, xv = xp;
@@ -1744,7 +1744,7 @@ __global__ __launch_bounds__(256) void m2l_hard_chunks(const double2* __restrict
 #pragma unroll
             for (int cb = 0; cb < RB; ++cb) sv[(g * nq + a) * RB + cb] = acc[v][cb];
         __syncthreads();
-        for (int idx = tid; idx < vs; idx += nt) {
+        for (int idx = tid; idx < vs; idx += 256) {
             const int cb = idx % RB, b = idx / RB;
             double2 s = sv[idx];
             for (int h = 1; h < NG; ++h) s = cadd(s, sv[h * vs + idx]);
