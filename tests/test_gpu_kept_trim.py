@@ -12,6 +12,7 @@ from paper_2306_11324_amd import inputs as I
 def test_kept_memory_is_reported_and_given_back():
     import torch
     from paper_2306_11324_amd import binding as B
+    gc.collect()
     ctx = B.Context(0)
     ctx.trim()
     assert ctx.kept_bytes() == 0
@@ -41,6 +42,7 @@ def test_kept_memory_is_reported_and_given_back():
 
 def test_contexts_with_a_budget_keep_nothing():
     from paper_2306_11324_amd import binding as B
+    gc.collect()
     ctx = B.Context(0, hbm_budget=64 << 30)
     ctx.trim()
     geo = B.Geometry(ctx, I.sphere_patches(), 5, 2)
